@@ -95,12 +95,14 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
     mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-    const float mn = fmaxf(m, mx);
-    const float corr = expf(m - mn);                    // the first tile: expf(-inf) = 0
+    // a wave's keys may all have the logit -inf so far (masked with the lowest value, or overflowed): the maximum then
+    // stays -inf and the exponents are taken against 0, so that the terms are expf(-inf) = 0 and not expf(-inf + inf)
+    const float mn = fmaxf(m, mx), ms = mn == -INFINITY ? 0.f : mn;
+    const float corr = expf(m - ms);                    // the first tile: expf(-inf) = 0
     m = mn;
     l *= corr;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) { s[r] = expf(s[r] - mn); l += s[r]; }
+    for (int r = 0; r < 4; ++r) { s[r] = expf(s[r] - ms); l += s[r]; }
 #pragma unroll
     for (int u = 0; u < NV; ++u)
 #pragma unroll
@@ -131,14 +133,15 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
   for (int i = threadIdx.x; i < 16 * DH / 4; i += 64 * NW) {
     const int row = i / (DH / 4), d = (i % (DH / 4)) * 4;
     if (q0 + row >= n) continue;
-    float M = red_m[0][row];                            // wave 0 always has tile 0
+    float M = red_m[0][row];
 #pragma unroll
     for (int w = 1; w < NW; ++w) M = fmaxf(M, red_m[w][row]);
+    const float Ms = M == -INFINITY ? 0.f : M;          // every logit of the row -inf: M = -inf, L = 0
     f32x4_t t = {0.f, 0.f, 0.f, 0.f};
     float L = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float f = expf(red_m[w][row] - M);          // a wave without tiles: expf(-inf) = 0
+      const float f = expf(red_m[w][row] - Ms);         // a wave without tiles, or without a finite logit: expf(-inf) = 0
       t = t + *(const f32x4_t*)&red_o[w][row][d] * f;
       L = fmaf(f, red_l[w][row], L);
     }

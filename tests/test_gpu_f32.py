@@ -49,6 +49,47 @@ def test_attention(dh, hq, hkv, lens):
             np.testing.assert_allclose(ml[b, h], [z.max(), np.exp(z - z.max()).sum()], rtol=2e-5, atol=2e-5)
 
 
+def _masked_attention(dh, n, masked):
+    """One fp32 sample whose keys of the ranges `masked` have the logit -inf for every query: q . k overflows to -inf there
+    (the first dimension is 3e38 on those keys against -4 on every query) and is ordinary elsewhere."""
+    rng = np.random.default_rng(dh + n)
+    q, k, v = (rng.standard_normal((n, h, dh)).astype(np.float32) for h in (4, 2, 2))
+    q[:, :, 0], k[:, :, 0] = -4.0, 0.0
+    off = np.zeros(n, dtype=bool)
+    for lo, hi in masked:
+        off[lo:hi] = True
+        k[lo:hi, :, 0] = 3.0e38
+    model = fa.make_model(1, 64, 4, 2, dh, 64, dtype=fa.F32)
+    got = fa.fastav_attention(model, dev(q, "f32"), dev(k, "f32"), dev(v, "f32"), torch.tensor([0, n], dtype=torch.int32, device="cuda"), n, want_last=True)
+    z = np.einsum("ihd,jhd->hij", q[:, :, 1:].astype(np.float64), k.repeat(2, axis=1)[:, :, 1:].astype(np.float64)) / np.sqrt(dh)
+    z[:, np.triu(np.ones((n, n), dtype=bool), 1)] = -np.inf
+    z[:, :, off] = -np.inf
+    return [host(t) for t in got], z, v.repeat(2, axis=1).astype(np.float64)
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("n,masked", [(512, [(32, 48)]), (300, [(16, 200)]), (130, [(64, 80), (112, 128)]), (40, [(0, 16)])])
+def test_attention_with_logits_of_minus_infinity(dh, n, masked):
+    """Whole 16-key tiles at -inf, among them the first ones a wave takes and the first of the sample: rows that see a finite
+    logit are what the softmax over their finite logits gives; rows that see none are 0 / 0."""
+    (o, ll, ml), z, v = _masked_attention(dh, n, masked)
+    m = z.max(axis=2)
+    live = m[0] > -np.inf
+    p = np.exp(z[:, live] - m[:, live, None])
+    want = np.einsum("hij,jhd->ihd", p / p.sum(axis=2, keepdims=True), v)
+    assert_close(o[live], want, "f32", what=f"attention {n}, -inf at {masked}")
+    assert np.isnan(o[~live]).all()
+    assert np.array_equal(np.isneginf(ll), np.isneginf(z[:, -1]))
+    np.testing.assert_allclose(ml[0, :, 0], m[:, -1], rtol=2e-5, atol=2e-5)
+    np.testing.assert_allclose(ml[0, :, 1], p[:, -1].sum(axis=1), rtol=2e-5)
+
+
+def test_attention_whose_last_row_sees_no_finite_logit():
+    """(max, sum) of such a row are (-inf, 0)."""
+    (o, _, ml), _, _ = _masked_attention(64, 70, [(0, 70)])
+    assert np.isnan(o).all() and np.isneginf(ml[0, :, 0]).all() and (ml[0, :, 1] == 0).all()
+
+
 @pytest.mark.parametrize("hidden,hq,hkv,dh,mlp,samples", [
     (100, 3, 1, 64, 76, [[(fi.VIDEO, 40), (fi.AUDIO, 29), (fi.TEXT, 6)]]),
     (132, 2, 2, 128, 90, [[(fi.VIDEO, 33), (fi.TEXT, 1)], [(fi.AUDIO, 150), (fi.TEXT, 20)]]),
