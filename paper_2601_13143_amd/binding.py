@@ -23,6 +23,7 @@ GLOBAL, FINE = 0, 1
 SEL_DEFAULT, SEL_LOW_ATTENTIVE, SEL_TOP_ATTENTIVE, SEL_LOW_INFORMATIVE, SEL_TOP_INFORMATIVE, SEL_RANDOM = range(6)
 BF16, F32 = 0, 1
 EPI_STORE, EPI_RESADD, EPI_SWIGLU = 0, 1, 2
+LINEAR_GENERIC, LINEAR_FEW_ROWS, LINEAR_TILES, LINEAR_RING, LINEAR_F32 = range(5)
 MAX_N_LAST, MAX_PRUNES, MAX_GATHER_TENSORS = 8, 128, 8
 
 
@@ -63,6 +64,10 @@ class PrefillOut(C.Structure):
 
 
 _lib = None
+
+class LinearPlan(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("kernel", "tile_rows", "tile_cols", "splits", "takes_rows")]
+
 
 class DecodeIn(C.Structure):
     _fields_ = [("batch", C.c_int32), ("x_new", C.c_void_p), ("pos_new", C.c_void_p),
@@ -108,6 +113,7 @@ _SIGS = {
     "fastav_linear_workspace_bytes": (C.c_size_t, []),
     "fastav_linear": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int32, C.c_int32,
                                 C.c_int32, C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "fastav_linear_plan": (C.c_int, [C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(LinearPlan)]),
     "fastav_attention": (C.c_int, [C.POINTER(Model), C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p,
                                    C.c_int64, C.c_void_p, C.c_int32, C.c_int64, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
     "fastav_profile_enable": (C.c_int, [C.c_uint32]),
@@ -472,6 +478,13 @@ def fastav_linear(a: torch.Tensor, w: torch.Tensor, epilogue: int = EPI_STORE, w
     _check(lib().fastav_linear(a.data_ptr(), w.data_ptr(), _ptr(w2), c.data_ptr(), m, n, k, epilogue, _dtype_code(a),
                                _ptr(ws), ws.numel() if ws is not None else 0, _stream()))
     return c
+
+
+def fastav_linear_plan(m: int, n: int, k: int, epilogue: int = EPI_STORE, dtype: int = BF16) -> LinearPlan:
+    """Host-side query: the kernel (LINEAR_*), tile and K shares fastav_linear takes for a shape."""
+    out = LinearPlan()
+    _check(lib().fastav_linear_plan(m, n, k, epilogue, dtype, C.byref(out)))
+    return out
 
 
 def fastav_attention(model: Model, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqlens_dev: torch.Tensor,

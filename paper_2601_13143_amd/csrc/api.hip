@@ -38,6 +38,7 @@ fastav_status_t launch_linear_mfma(const void* a, const void* const* w_seg, cons
                                    const void* w2, void* c, int64_t ldc, void* const* c_seg, const int64_t* ldc_seg,
                                    int64_t m, int n, int k, int epilogue, void* scratch, size_t scratch_bytes, hipStream_t s,
                                    const RopeFuse* rope = nullptr, SplitKPending* pend = nullptr, RowGather rows = RowGather());
+bool ring_linear_plan(int64_t m, int n, int k, int epilogue, fastav_linear_plan_t* out);
 bool mfma_linear_takes_rows(int k, int64_t n_src);
 bool mfma_linear_fuses_rope(int64_t m, const int* seg_rows, int n_seg, int rope_segs, int k, int dh, int dtype);
 size_t mfma_linear_scratch_bytes();
@@ -45,7 +46,8 @@ fastav_status_t launch_attention_generic(const void* q, int64_t q_stride, const 
                                          int64_t kv_stride, void* o, int64_t o_stride, const int32_t* cu, int batch,
                                          int64_t T, int max_seqlen, int Hq, int Hkv, int dh, float* last_logits,
                                          float* last_ml, int dtype, hipStream_t s);
-bool f32_linear_supported(const void* x, const void* const* w, const int* seg_rows, int n_seg, const void* w2, int64_t m, int k);
+bool f32_linear_takes(int64_t m, const int* seg_rows, int n_seg, int k);
+bool f32_linear_aligned(const void* x, const void* const* w, int n_seg, const void* w2);
 fastav_status_t launch_linear_f32(const float* x, const int32_t* rows, const void* const* w_seg, const int* seg_rows, int n_seg,
                                   const void* w2, float* const* c, const int64_t* ldc, int64_t m, int k, int epilogue,
                                   const float* norm_g, float eps, const RopeFuse* rope, hipStream_t s);
@@ -86,6 +88,19 @@ fastav_status_t launch_rollout_cutoff(const float* rt, int n, const uint8_t* pro
 fastav_status_t launch_rollout_step(float* rt, void* rt16, const void* a16, float* c, int n, float alpha,
                                     void* linear_ws, size_t linear_ws_bytes, hipStream_t s);
 
+// The kernel that a product's sizes ask for; the decode kernels also want packed rows in and out (few_ok).
+static fastav_linear_kernel_t linear_kernel(int64_t m, const int* seg_rows, int n_seg, int k, int epilogue, int dtype, int64_t ldc, bool few_ok) {
+  int n = 0;
+  bool few = few_ok && m <= FASTAV_MAX_DECODE_BATCH;
+  for (int i = 0; i < n_seg; ++i) { n += seg_rows[i]; few = few && seg_rows[i] % 16 == 0; }
+  if (few && skinny_linear_supported(m, n, k, dtype, ldc)) return FASTAV_LINEAR_FEW_ROWS;
+  bool tiles = mfma_linear_supported(m, n, k, epilogue, dtype);
+  for (int i = 0; i < n_seg && tiles; ++i) tiles = mfma_linear_supported(m, seg_rows[i], k, epilogue, dtype);
+  if (tiles) return FASTAV_LINEAR_TILES;
+  if (dtype == FASTAV_F32 && f32_linear_takes(m, seg_rows, n_seg, k)) return FASTAV_LINEAR_F32;
+  return FASTAV_LINEAR_GENERIC;
+}
+
 // One linear layer whose weight rows may come from up to three matrices stacked along N (Q|K|V).  With c_seg the
 // output columns of segment i go to their own matrix c_seg[i] (row pitch ldc_seg[i] elements) instead of columns
 // of c (plain-store epilogue only).
@@ -101,18 +116,14 @@ static fastav_status_t linear_segments(const void* a, const void* const* w_seg, 
   // a handful of rows (a decode step): stream the weights through the skinny kernel, which times itself
   if (c_seg != nullptr && epilogue != FASTAV_EPI_STORE) return fail(FASTAV_EINVAL, "per-segment outputs need the plain-store epilogue");
   if (rows.idx != nullptr && !linear_takes_rows(m, n, k, epilogue, dtype, rows.n_src)) return fail(FASTAV_EINVAL, "linear: this product cannot take a row list");
-  if (rows.idx == nullptr && rope == nullptr && c_seg == nullptr && m <= FASTAV_MAX_DECODE_BATCH && skinny_linear_supported(m, n, k, dtype, ldc)) {
-    bool sk = (((uintptr_t)a | (uintptr_t)c) % 16) == 0;
-    for (int i = 0; i < n_seg && sk; ++i) sk = seg_rows[i] % 16 == 0;
-    if (sk) return launch_skinny_linear(a, w_seg, seg_rows, n_seg, w2, c, ldc, (int)m, n, k, epilogue, s);
-  }
+  const bool few_ok = rows.idx == nullptr && rope == nullptr && c_seg == nullptr && (((uintptr_t)a | (uintptr_t)c) % 16) == 0;
+  const fastav_linear_kernel_t kernel = linear_kernel(m, seg_rows, n_seg, k, epilogue, dtype, ldc, few_ok);
+  if (kernel == FASTAV_LINEAR_FEW_ROWS) return launch_skinny_linear(a, w_seg, seg_rows, n_seg, w2, c, ldc, (int)m, n, k, epilogue, s);
   const int kind = epilogue == FASTAV_EPI_STORE ? FASTAV_PROF_LINEAR_STORE
                    : epilogue == FASTAV_EPI_RESADD ? FASTAV_PROF_LINEAR_RESADD : FASTAV_PROF_LINEAR_SWIGLU;
   ProfScope prof(kind, 2.0 * (double)m * n * k * (epilogue == FASTAV_EPI_SWIGLU ? 2.0 : 1.0), s);
-  bool ok = mfma_linear_supported(m, n, k, epilogue, dtype);
-  for (int i = 0; i < n_seg && ok; ++i) ok = mfma_linear_supported(m, seg_rows[i], k, epilogue, dtype);
-  if (ok) return launch_linear_mfma(a, w_seg, seg_rows, n_seg, w2, c, ldc, c_seg, ldc_seg, m, n, k, epilogue, scratch, scratch_bytes, s, rope, pend, rows);
-  if (dtype == FASTAV_F32 && rope == nullptr && f32_linear_supported(a, w_seg, seg_rows, n_seg, w2, m, k)) {
+  if (kernel == FASTAV_LINEAR_TILES) return launch_linear_mfma(a, w_seg, seg_rows, n_seg, w2, c, ldc, c_seg, ldc_seg, m, n, k, epilogue, scratch, scratch_bytes, s, rope, pend, rows);
+  if (kernel == FASTAV_LINEAR_F32 && rope == nullptr && f32_linear_aligned(a, w_seg, n_seg, w2)) {
     float* cs[3]; int64_t lds[3];
     int at = 0;
     for (int i = 0; i < n_seg; ++i) { cs[i] = c_seg ? (float*)c_seg[i] : (float*)c + at; lds[i] = c_seg ? ldc_seg[i] : ldc; at += seg_rows[i]; }
@@ -134,7 +145,7 @@ static fastav_status_t linear_segments(const void* a, const void* const* w_seg, 
 // The matrix-core kernels are the ones that can read their A rows through a list; a handful of bf16 rows go to the
 // skinny kernel.
 bool linear_takes_rows(int64_t m, int n, int k, int epilogue, int dtype, int64_t n_src) {
-  if (dtype == FASTAV_F32) return k % 4 == 0;           // the fp32 kernel (weights and workspace are 16-byte aligned)
+  if (dtype == FASTAV_F32) return linear_kernel(m, &n, 1, k, epilogue, dtype, n, false) == FASTAV_LINEAR_F32;   // weights and workspace are 16-byte aligned
   return m > FASTAV_MAX_DECODE_BATCH && mfma_linear_supported(m, n, k, epilogue, dtype) && mfma_linear_takes_rows(k, n_src);
 }
 
@@ -786,6 +797,15 @@ fastav_status_t fastav_linear(const void* a, const void* w, const void* w2, void
   if (epilogue < FASTAV_EPI_STORE || epilogue > FASTAV_EPI_SWIGLU) return fail(FASTAV_EINVAL, "bad epilogue");
   if (epilogue == FASTAV_EPI_SWIGLU && !w2) return fail(FASTAV_EINVAL, "w2 is NULL for the SwiGLU epilogue");
   return launch_linear(a, w, w2, c, m, n, k, epilogue, dtype, workspace, workspace ? workspace_bytes : 0, (hipStream_t)stream);
+}
+
+fastav_status_t fastav_linear_plan(int64_t m, int32_t n, int32_t k, int32_t epilogue, int32_t dtype, fastav_linear_plan_t* out) {
+  if (!out) return fail(FASTAV_EINVAL, "out is NULL");
+  if (m < 1 || n < 1 || k < 1 || (dtype != FASTAV_BF16 && dtype != FASTAV_F32)) return fail(FASTAV_EINVAL, "bad m/n/k/dtype");
+  if (epilogue < FASTAV_EPI_STORE || epilogue > FASTAV_EPI_SWIGLU) return fail(FASTAV_EINVAL, "bad epilogue");
+  *out = fastav_linear_plan_t{linear_kernel(m, &n, 1, k, epilogue, dtype, n, true), 0, 0, 0, linear_takes_rows(m, n, k, epilogue, dtype, m)};
+  if (out->kernel == FASTAV_LINEAR_TILES && ring_linear_plan(m, n, k, epilogue, out)) out->kernel = FASTAV_LINEAR_RING;
+  return FASTAV_OK;
 }
 
 fastav_status_t fastav_attention(const fastav_model_t* model, const void* q, int64_t q_row_stride, const void* k,

@@ -206,13 +206,16 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void k_gemm_f32(F32GemmArgs a) {
   }
 }
 
-bool f32_linear_supported(const void* x, const void* const* w, const int* seg_rows, int n_seg, const void* w2, int64_t m, int k) {
+// Sizes: 32-row tiles are counted by the grid's y, a tile lies in one segment.
+bool f32_linear_takes(int64_t m, const int* seg_rows, int n_seg, int k) {
+  for (int i = 0; i < n_seg; ++i)
+    if (n_seg > 1 && seg_rows[i] % 32) return false;
+  return k % 4 == 0 && m >= 1 && ceil_div(m, 32) <= 65535;
+}
+bool f32_linear_aligned(const void* x, const void* const* w, int n_seg, const void* w2) {
   uintptr_t all = (uintptr_t)x | (uintptr_t)w2;
-  for (int i = 0; i < n_seg; ++i) {
-    all |= (uintptr_t)w[i];
-    if (n_seg > 1 && seg_rows[i] % 32) return false;    // a tile lies in one segment
-  }
-  return k % 4 == 0 && all % 16 == 0 && m >= 1 && ceil_div(m, 32) <= 65535;
+  for (int i = 0; i < n_seg; ++i) all |= (uintptr_t)w[i];
+  return all % 16 == 0;
 }
 
 template <int EPI, bool NORM>
@@ -232,7 +235,7 @@ static void launch_f32_t(const F32GemmArgs& a, hipStream_t s) {
 fastav_status_t launch_linear_f32(const float* x, const int32_t* rows, const void* const* w_seg, const int* seg_rows, int n_seg,
                                   const void* w2, float* const* c, const int64_t* ldc, int64_t m, int k, int epilogue,
                                   const float* norm_g, float eps, const RopeFuse* rope, hipStream_t s) {
-  if (!f32_linear_supported(x, w_seg, seg_rows, n_seg, w2, m, k)) return fail(FASTAV_EUNSUPPORTED, "f32 linear: unsupported shape or alignment");
+  if (!f32_linear_takes(m, seg_rows, n_seg, k) || !f32_linear_aligned(x, w_seg, n_seg, w2)) return fail(FASTAV_EUNSUPPORTED, "f32 linear: unsupported shape or alignment");
   if (norm_g && (epilogue == FASTAV_EPI_RESADD || (uintptr_t)norm_g % 16)) return fail(FASTAV_EINVAL, "f32 linear: bad fused-norm arguments");
   F32GemmArgs a;
   a.x = x; a.rows = rows; a.w2 = (const float*)w2; a.M = (int)m; a.K = k; a.g = norm_g; a.eps = eps;

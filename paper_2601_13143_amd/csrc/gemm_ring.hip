@@ -308,6 +308,16 @@ bool ring_linear_takes(const GemmArgs& g, int n_seg, int epilogue) {
   return ring_plan(g.M, g.N, g.K, epilogue).bm != 0;
 }
 
+// The plan of a product with one weight matrix, for fastav_linear_plan.
+bool ring_linear_plan(int64_t m, int n, int k, int epilogue, fastav_linear_plan_t* out) {
+  GemmArgs g;
+  g.M = (int)m; g.N = n; g.K = k; g.seg_end[0] = n;
+  if (!ring_linear_takes(g, 1, epilogue)) return false;
+  const RingPlan p = ring_plan(g.M, n, k, epilogue);
+  out->tile_rows = p.bm; out->tile_cols = p.bn; out->splits = p.splits;
+  return true;
+}
+
 // Ring depths: all of LDS, or half of it where two workgroups share a CU (64 x 64 tiles).
 template <int EPI>
 static fastav_status_t launch_plan(const RingPlan& p, const GemmArgs& g, hipStream_t s) {

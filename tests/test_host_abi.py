@@ -68,6 +68,18 @@ def test_schedule_matches_oracle(cfg):
         assert tin[0] == 4096 and tin[14] == 2458 and tin[21] == 1721 and tin[27] == 1205 and tout[20] == 1721
 
 
+def test_fp32_products_take_a_keep_list_exactly_where_their_kernel_runs():
+    """Behind a FINE prune the prefill leaves the attention output uncompacted if the O projection can read it through the keep
+    list; only the fp32 matrix-core kernel can, and it counts its 32-row tiles in a grid dimension of 65535."""
+    for m in (1, 33, 4096, 65535 * 32 - 1, 65535 * 32, 65535 * 32 + 1, 4 << 20):
+        for n, k in ((64, 64), (66, 64), (64, 66), (100, 128)):
+            p = fa.fastav_linear_plan(m, n, k, fa.EPI_RESADD, fa.F32)
+            assert p.kernel in (fa.LINEAR_F32, fa.LINEAR_GENERIC)
+            assert bool(p.takes_rows) == (p.kernel == fa.LINEAR_F32), (m, n, k)
+            if m > 65535 * 32 or k % 4:
+                assert p.kernel == fa.LINEAR_GENERIC, (m, n, k)
+
+
 def test_schedule_n_last_counts_non_text_tail_once():
     # last 3 positions: one audio + two text -> protected = 4 text + 1 audio
     cu = [0, 20]
