@@ -1,6 +1,6 @@
 """The fp32 matrix-core kernels at the edges of their tiles: 32 x 32 tiles, 16-wide k chunks, the three workgroup
-forms of the products (8 and 4 waves on a tile, one wave per tile), 16-row / 16-key attention tiles; and a prefill
-whose sizes are multiples of none of them.  Tolerances: gpu_util's fp32 ones."""
+forms of the products (8 and 4 waves on a tile, waves of 64 x 64 from 2048 tiles on), 16-row / 16-key attention tiles;
+and a prefill whose sizes are multiples of none of them.  Tolerances: gpu_util's fp32 ones."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,8 @@ from oracle import fastav_oracle as orc
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,n,k", [(1, 16, 4), (33, 48, 20), (31, 33, 64), (128, 256, 688), (520, 1040, 36), (2050, 1060, 132)])
+@pytest.mark.parametrize("m,n,k", [(1, 16, 4), (33, 48, 20), (31, 33, 64), (128, 256, 688), (520, 1040, 36), (2050, 1060, 132),
+                                   (2017, 1041, 16), (4000, 530, 12), (1100, 2000, 48), (65, 32800, 64)])
 @pytest.mark.parametrize("epi", [fa.EPI_STORE, fa.EPI_RESADD, fa.EPI_SWIGLU])
 def test_linear(m, n, k, epi):
     rng = np.random.default_rng(m * 7 + n)
@@ -93,6 +94,7 @@ def test_attention_whose_last_row_sees_no_finite_logit():
 @pytest.mark.parametrize("hidden,hq,hkv,dh,mlp,samples", [
     (100, 3, 1, 64, 76, [[(fi.VIDEO, 40), (fi.AUDIO, 29), (fi.TEXT, 6)]]),
     (132, 2, 2, 128, 90, [[(fi.VIDEO, 33), (fi.TEXT, 1)], [(fi.AUDIO, 150), (fi.TEXT, 20)]]),
+    (128, 16, 2, 64, 530, [[(fi.VIDEO, 700), (fi.AUDIO, 390), (fi.TEXT, 21)], [(fi.AUDIO, 1080), (fi.TEXT, 20)]]),   # 64 x 64 per wave
     (66, 2, 1, 64, 70, [[(fi.VIDEO, 50), (fi.TEXT, 5)]]),          # hidden no multiple of 4: the separate launches
 ])
 def test_prefill(hidden, hq, hkv, dh, mlp, samples):
