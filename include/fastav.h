@@ -249,15 +249,16 @@ fastav_status_t fastav_linear(const void* a, const void* w, const void* w2, void
                               int32_t k, int32_t epilogue, int32_t dtype, void* workspace, size_t workspace_bytes,
                               void* stream);
 
-/* The kernel that fastav_linear runs for a shape (packed rows, 16-byte aligned operands, a full workspace): a host-side
- * query for tests and measurements, nothing is launched.  FEW_ROWS: the decode projections (at most 16 rows); TILES: bf16,
+/* The kernel that fastav_linear runs for a shape (packed rows, 16-byte aligned operands, a workspace of that many
+ * bytes): a host-side query for tests and measurements, nothing is launched.  FEW_ROWS: the decode projections (at most 16 rows); TILES: bf16,
  * 128- to 256-row tiles; RING: bf16, products of few rows, with the tile (rows x weight rows of W and W2 together) and the
  * shares of K; F32: fp32 matrix instructions; GENERIC: the vector ALUs.  takes_rows: whether the product can read its input
  * rows through a keep list (the O projection behind a FINE prune). */
 typedef enum { FASTAV_LINEAR_GENERIC = 0, FASTAV_LINEAR_FEW_ROWS = 1, FASTAV_LINEAR_TILES = 2, FASTAV_LINEAR_RING = 3,
                FASTAV_LINEAR_F32 = 4 } fastav_linear_kernel_t;
 typedef struct { int32_t kernel; int32_t tile_rows; int32_t tile_cols; int32_t splits; int32_t takes_rows; } fastav_linear_plan_t;
-fastav_status_t fastav_linear_plan(int64_t m, int32_t n, int32_t k, int32_t epilogue, int32_t dtype, fastav_linear_plan_t* out);
+fastav_status_t fastav_linear_plan(int64_t m, int32_t n, int32_t k, int32_t epilogue, int32_t dtype, size_t workspace_bytes,
+                                   fastav_linear_plan_t* out);
 
 /* Causal grouped-query attention over a packed batch: o = softmax(q k^T / sqrt(head_dim) + causal) v.
  * q,k,v,o are dev pointers in dtype with row strides in elements (q and o hold Hq heads, k and v Hkv).

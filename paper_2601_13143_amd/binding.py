@@ -113,7 +113,7 @@ _SIGS = {
     "fastav_linear_workspace_bytes": (C.c_size_t, []),
     "fastav_linear": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int32, C.c_int32,
                                 C.c_int32, C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]),
-    "fastav_linear_plan": (C.c_int, [C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(LinearPlan)]),
+    "fastav_linear_plan": (C.c_int, [C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_size_t, C.POINTER(LinearPlan)]),
     "fastav_attention": (C.c_int, [C.POINTER(Model), C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p,
                                    C.c_int64, C.c_void_p, C.c_int32, C.c_int64, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
     "fastav_profile_enable": (C.c_int, [C.c_uint32]),
@@ -480,10 +480,10 @@ def fastav_linear(a: torch.Tensor, w: torch.Tensor, epilogue: int = EPI_STORE, w
     return c
 
 
-def fastav_linear_plan(m: int, n: int, k: int, epilogue: int = EPI_STORE, dtype: int = BF16) -> LinearPlan:
-    """Host-side query: the kernel (LINEAR_*), tile and K shares fastav_linear takes for a shape."""
+def fastav_linear_plan(m: int, n: int, k: int, epilogue: int = EPI_STORE, dtype: int = BF16, workspace_bytes: Optional[int] = None) -> LinearPlan:
+    """Host-side query: the kernel (LINEAR_*), tile and K shares fastav_linear takes for a shape (default: its full workspace)."""
     out = LinearPlan()
-    _check(lib().fastav_linear_plan(m, n, k, epilogue, dtype, C.byref(out)))
+    _check(lib().fastav_linear_plan(m, n, k, epilogue, dtype, lib().fastav_linear_workspace_bytes() if workspace_bytes is None else workspace_bytes, C.byref(out)))
     return out
 
 

@@ -38,7 +38,7 @@ fastav_status_t launch_linear_mfma(const void* a, const void* const* w_seg, cons
                                    const void* w2, void* c, int64_t ldc, void* const* c_seg, const int64_t* ldc_seg,
                                    int64_t m, int n, int k, int epilogue, void* scratch, size_t scratch_bytes, hipStream_t s,
                                    const RopeFuse* rope = nullptr, SplitKPending* pend = nullptr, RowGather rows = RowGather());
-bool ring_linear_plan(int64_t m, int n, int k, int epilogue, fastav_linear_plan_t* out);
+bool ring_linear_plan(int64_t m, int n, int k, int epilogue, size_t room, fastav_linear_plan_t* out);
 bool mfma_linear_takes_rows(int k, int64_t n_src);
 bool mfma_linear_fuses_rope(int64_t m, const int* seg_rows, int n_seg, int rope_segs, int k, int dh, int dtype);
 size_t mfma_linear_scratch_bytes();
@@ -799,12 +799,13 @@ fastav_status_t fastav_linear(const void* a, const void* w, const void* w2, void
   return launch_linear(a, w, w2, c, m, n, k, epilogue, dtype, workspace, workspace ? workspace_bytes : 0, (hipStream_t)stream);
 }
 
-fastav_status_t fastav_linear_plan(int64_t m, int32_t n, int32_t k, int32_t epilogue, int32_t dtype, fastav_linear_plan_t* out) {
+fastav_status_t fastav_linear_plan(int64_t m, int32_t n, int32_t k, int32_t epilogue, int32_t dtype, size_t workspace_bytes,
+                                   fastav_linear_plan_t* out) {
   if (!out) return fail(FASTAV_EINVAL, "out is NULL");
   if (m < 1 || n < 1 || k < 1 || (dtype != FASTAV_BF16 && dtype != FASTAV_F32)) return fail(FASTAV_EINVAL, "bad m/n/k/dtype");
   if (epilogue < FASTAV_EPI_STORE || epilogue > FASTAV_EPI_SWIGLU) return fail(FASTAV_EINVAL, "bad epilogue");
   *out = fastav_linear_plan_t{linear_kernel(m, &n, 1, k, epilogue, dtype, n, true), 0, 0, 0, linear_takes_rows(m, n, k, epilogue, dtype, m)};
-  if (out->kernel == FASTAV_LINEAR_TILES && ring_linear_plan(m, n, k, epilogue, out)) out->kernel = FASTAV_LINEAR_RING;
+  if (out->kernel == FASTAV_LINEAR_TILES && ring_linear_plan(m, n, k, epilogue, workspace_bytes, out)) out->kernel = FASTAV_LINEAR_RING;
   return FASTAV_OK;
 }
 

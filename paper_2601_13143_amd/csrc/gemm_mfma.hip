@@ -651,7 +651,7 @@ fastav_status_t launch_linear_mfma(const void* a, const void* const* w_seg, cons
     }
   }
   if (((uintptr_t)a | (uintptr_t)w_seg[0]) % 16) return fail(FASTAV_EINVAL, "gemm: A and W must be 16-byte aligned");
-  if (ring_linear_takes(g, n_seg, epilogue)) return launch_linear_ring(g, epilogue, scratch, scratch_bytes, s, pend);
+  if (ring_linear_takes(g, n_seg, epilogue, scratch, scratch_bytes)) return launch_linear_ring(g, epilogue, scratch, scratch_bytes, s, pend);
   if (epilogue == FASTAV_EPI_STORE) return launch_epi<FASTAV_EPI_STORE>(g, big_ok, scratch, scratch_bytes, s, nullptr);
   if (epilogue == FASTAV_EPI_RESADD) return launch_epi<FASTAV_EPI_RESADD>(g, big_ok, scratch, scratch_bytes, s, pend);
   return launch_epi<FASTAV_EPI_SWIGLU>(g, big_ok, scratch, scratch_bytes, s, nullptr);

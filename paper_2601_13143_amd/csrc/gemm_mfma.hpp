@@ -65,7 +65,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 }
 
 // Products of few rows (gemm_ring.hip): whether this one runs there, and its launch.
-bool ring_linear_takes(const GemmArgs& g, int n_seg, int epilogue);
+bool ring_linear_takes(const GemmArgs& g, int n_seg, int epilogue, const void* scratch, size_t scratch_bytes);
 fastav_status_t launch_linear_ring(GemmArgs& g, int epilogue, void* scratch, size_t scratch_bytes, hipStream_t s, SplitKPending* pend);
 
 }  // namespace fastav

@@ -246,9 +246,8 @@ static fastav_status_t launch_ring(GemmArgs g, int splits, hipStream_t s) {
   return check_launch("gemm_ring");
 }
 
-// Weights of fewer elements stay with the large tiles, which sum K in one order whatever the rows (a batch of a small
-// model is then bit for bit its samples); there is little to gain: 1024 x 1024 and 1536 x 1024, 48 to 500 rows, 10-12 us
-// -> 8-12.  From the line on: 4096 -> 1024 columns 23-25 -> 11-18, 2048 x 2048 21-24 -> 9-19.
+// Weights of fewer elements stay with the large tiles: there is little to gain (1024 x 1024 and 1536 x 1024, 48 to 500 rows,
+// 10-12 us -> 8-12).  From the line on: 4096 -> 1024 columns 23-25 -> 11-18, 2048 x 2048 21-24 -> 9-19.
 constexpr int64_t kRingMinWeights = (int64_t)4 << 20;
 
 // Tile and split of a product.  bm = 0: not a product for this kernel.
@@ -258,16 +257,24 @@ struct RingPlan { int bm, bn, splits; };
 // a split product counts the sum of its partial tiles, which the next RMSNorm or the reduce launch does):
 // - 64-column tiles with the fewest rows that still make one round of 256 workgroups.  Q|K|V: 82 rows 33 -> 18 and
 //   38 -> 21, 232 rows 34 -> 26 and 39 -> 29, 331 rows 33 -> 23 and 38 -> 35; a second round loses (331 rows in 288
-//   tiles of 128: 38 -> 50).
+//   tiles of 128: 38 -> 50).  Of 192 rows: a single tile row (more than 128 columns of tiles) only up to 144 rows (9216
+//   columns, 129 / 144 / 160 / 192 rows: K = 5120 47 -> 48, 48 -> 50, 49 -> 53, 50 -> 56, K = 8192 71 -> 66, 72 -> 68,
+//   72 -> 69, 74 -> 75), and several tile rows only from 32 stages on (16 stages: 12 -> 13; 32: 21 -> 19).
 // - gate/up: one tile row of up to 256 rows, 128 or 160 columns, whichever gives one round.  82 rows 76 -> 57 and
 //   49 -> 44, 165 rows 98 -> 64 and 68 -> 56, 232 rows 98 -> 79 and 76 -> 66.  Up to 384 rows it pays only where the
-//   256 x 256 tiles need a second round (331 rows: 120 -> 101; in one round they win, 89 against 95), and not with half
-//   of the CUs idle (200 rows, 6144 gate/up columns in 96 tiles: 24 -> 34).
+//   256 x 256 tiles need a second round (257 / 300 / 331 / 384 rows of 18944 x 3584: 122 -> 101, 123 -> 99, 124 -> 101,
+//   128 -> 104; 16512 x 2048 77-79 -> 61-66, 20480 x 5120 178-189 -> 147-156; in one round they win, 89 against 95),
+//   and not with half of the CUs idle (200 rows, 6144 gate/up columns in 96 tiles: 24 -> 34).
 // - residual products, K shared out over one round of workgroups: 128 columns where a share then keeps 16 stages or
 //   more (down, 82 rows 49 + 4.7 -> 29 + 4.9 and 39 + 4.6 -> 26 + 4.8, 232 rows 54 + 6 -> 40 + 7 and 44 + 7 -> 35 + 7;
 //   beyond 256 rows both take 65), else 64 columns and fewer, longer shares (O, 116 rows 17 + 4.6 -> 11 + 4 and
-//   18 + 4.4 -> 13 + 4, 331 rows 19 + 7 -> 18 + 4 and 25 + 9 -> 20 + 5).
-static RingPlan ring_plan(int m, int n, int k, int epilogue) {
+//   18 + 4.4 -> 13 + 4, 331 rows 19 + 7 -> 18 + 4 and 25 + 9 -> 20 + 5).  Not: more than 48 tile columns of 128 and 193 rows
+//   or more (8192 x 12288, 224 rows: 72 -> 74) or long shares (8192 x 28672, 112 stages, 100 / 160 / 192 rows: 120 -> 113,
+//   126 -> 132, 132 -> 142); 193-256 rows whose 64-column tiles leave no second share (5120 x 5120: 33 -> 40).
+// - without room for the partial tiles, 64-row tiles and 128 x 64 win all the same (4096 x 14336, 64 rows: 122 -> 74;
+//   4096 x 4096, 100 rows 41 -> 29, 224 rows 41 -> 30), the others do not (160 rows 39 -> 36 and 49 -> 52; 128 columns:
+//   4096 x 14336, 224 rows 131 -> 193); those leave unless half of their shares find room.
+static RingPlan ring_plan(int m, int n, int k, int epilogue, size_t room) {
   const RingPlan no = {0, 0, 0};
   if (m > 576) return no;                               // three tiles of 192 rows
   const int rows[4] = {64, 128, 192, 256};
@@ -279,18 +286,32 @@ static RingPlan ring_plan(int m, int n, int k, int epilogue) {
     const int64_t t128 = tiles(one ? one : 256, n, 128);
     const bool long_k = t128 <= kNumCUs && (k / 64) / (kNumCUs / t128) >= 16;
     if (long_k && one == 0) return no;
-    if (long_k && one > 64) return {one, 128, kNumCUs / t128 < 16 ? (int)(kNumCUs / t128) : 16};
-    const int bm = m <= 64 ? 64 : m <= 128 ? 128 : m <= 192 ? 192 : m <= 256 ? 128 : 192;
-    const int64_t t64 = tiles(bm, n, 64);
-    if (t64 > kNumCUs) return no;
-    int splits = (int)(kNumCUs / t64);
-    if (splits > k / 64 / 8) splits = k / 64 / 8;       // a share is at least 8 stages
-    if (splits > 16) splits = 16;
-    return {bm, 64, splits < 1 ? 1 : splits};
+    RingPlan p;
+    if (long_k && one > 64) {
+      p = {one, 128, kNumCUs / t128 < 16 ? (int)(kNumCUs / t128) : 16};
+      if (t128 > 48 && (m > 192 || (m > 128 && (k / 64) / p.splits >= 64))) return no;
+    } else {
+      const int bm = m <= 64 ? 64 : m <= 128 ? 128 : m <= 192 ? 192 : m <= 256 ? 128 : 192;
+      const int64_t t64 = tiles(bm, n, 64);
+      if (t64 > kNumCUs || (m > 192 && m <= 256 && t64 > kNumCUs / 2)) return no;
+      int splits = (int)(kNumCUs / t64);
+      if (splits > k / 64 / 8) splits = k / 64 / 8;     // a share is at least 8 stages
+      if (splits > 16) splits = 16;
+      p = {bm, 64, splits < 1 ? 1 : splits};
+    }
+    const int64_t fits = (int64_t)(room / ((size_t)m * n * sizeof(float)));
+    if (p.splits > fits) {
+      if (!(p.bm == 64 || (p.bm == 128 && p.bn == 64)) && fits * 2 < p.splits) return no;
+      p.splits = fits < 1 ? 1 : (int)fits;
+    }
+    return p;
   }
   const int cols = epilogue == FASTAV_EPI_SWIGLU ? 2 * n : n;
-  for (int i = 0; i < 3; ++i)
-    if (tiles(rows[i], cols, 64) <= kNumCUs) return {rows[i], 64, 1};
+  for (int i = 0; i < 3; ++i) {
+    if (tiles(rows[i], cols, 64) > kNumCUs) continue;
+    if (rows[i] == 192 && (m <= 192 ? m > 144 : k < 32 * 64)) break;
+    return {rows[i], 64, 1};
+  }
   if (epilogue != FASTAV_EPI_SWIGLU) return no;
   if (tiles(256, cols, 128) < kNumCUs * 5 / 8) return no;
   if (one != 0 && tiles(one, cols, 128) <= kNumCUs) return {one, 128, 1};
@@ -299,21 +320,29 @@ static RingPlan ring_plan(int m, int n, int k, int epilogue) {
   return no;
 }
 
-bool ring_linear_takes(const GemmArgs& g, int n_seg, int epilogue) {
-  if ((int64_t)g.N * g.K < kRingMinWeights) return false;
+// Scratch for partial tiles, of which only whole, aligned rows of the residual can be completed.
+static size_t ring_room(const GemmArgs& g, const void* scratch, size_t scratch_bytes) {
+  return scratch == nullptr || (uintptr_t)scratch % 16 != 0 || g.ldc % 4 != 0 || (uintptr_t)g.C % 16 != 0 ? 0 : scratch_bytes;
+}
+
+static bool ring_sizes(int64_t m, int64_t n, int64_t k) {
+  if (n * k < kRingMinWeights) return false;
   // the copies address rows by 32-bit byte offsets from the start of a matrix
-  if ((int64_t)g.N * g.K * 2 >= ((int64_t)1 << 32) || (int64_t)g.M * g.K * 2 >= ((int64_t)1 << 32)) return false;
+  return n * k * 2 < ((int64_t)1 << 32) && m * k * 2 < ((int64_t)1 << 32);
+}
+
+bool ring_linear_takes(const GemmArgs& g, int n_seg, int epilogue, const void* scratch, size_t scratch_bytes) {
+  if (!ring_sizes(g.M, g.N, g.K)) return false;
   for (int i = 0, prev = 0; epilogue == FASTAV_EPI_STORE && i < n_seg; prev = g.seg_end[i++])
     if ((g.seg_end[i] - prev) % 128) return false;
-  return ring_plan(g.M, g.N, g.K, epilogue).bm != 0;
+  return ring_plan(g.M, g.N, g.K, epilogue, ring_room(g, scratch, scratch_bytes)).bm != 0;
 }
 
 // The plan of a product with one weight matrix, for fastav_linear_plan.
-bool ring_linear_plan(int64_t m, int n, int k, int epilogue, fastav_linear_plan_t* out) {
-  GemmArgs g;
-  g.M = (int)m; g.N = n; g.K = k; g.seg_end[0] = n;
-  if (!ring_linear_takes(g, 1, epilogue)) return false;
-  const RingPlan p = ring_plan(g.M, n, k, epilogue);
+bool ring_linear_plan(int64_t m, int n, int k, int epilogue, size_t room, fastav_linear_plan_t* out) {
+  if (m > 0x7FFFFFFF || !ring_sizes(m, n, k) || (epilogue == FASTAV_EPI_STORE && n % 128)) return false;
+  const RingPlan p = ring_plan((int)m, n, k, epilogue, room);
+  if (p.bm == 0) return false;
   out->tile_rows = p.bm; out->tile_cols = p.bn; out->splits = p.splits;
   return true;
 }
@@ -351,13 +380,10 @@ static fastav_status_t launch_plan(const RingPlan& p, const GemmArgs& g, hipStre
 }
 
 fastav_status_t launch_linear_ring(GemmArgs& g, int epilogue, void* scratch, size_t scratch_bytes, hipStream_t s, SplitKPending* pend) {
-  RingPlan p = ring_plan(g.M, g.N, g.K, epilogue);
+  const RingPlan p = ring_plan(g.M, g.N, g.K, epilogue, ring_room(g, scratch, scratch_bytes));
   if (epilogue == FASTAV_EPI_STORE) return launch_plan<FASTAV_EPI_STORE>(p, g, s);
   if (epilogue == FASTAV_EPI_SWIGLU) return launch_plan<FASTAV_EPI_SWIGLU>(p, g, s);
   // the partial tiles are added to the residual in split order
-  if (scratch == nullptr || (uintptr_t)scratch % 16 != 0 || g.ldc % 4 != 0 || (uintptr_t)g.C % 16 != 0 ||
-      (size_t)p.splits * g.M * g.N * sizeof(float) > scratch_bytes)
-    p.splits = 1;
   if (p.splits == 1) return launch_plan<FASTAV_EPI_RESADD>(p, g, s);
   GemmArgs gp = g;
   gp.partial = (float*)scratch;

@@ -80,6 +80,30 @@ def test_fp32_products_take_a_keep_list_exactly_where_their_kernel_runs():
                 assert p.kernel == fa.LINEAR_GENERIC, (m, n, k)
 
 
+def test_few_row_products_leave_the_ring_kernel_where_the_large_tiles_are_faster():
+    """The measured lines of ring_plan: the residual product's partial tiles have no room, or half of it; few K shares; one tile
+    row of 192 over more than half of the CUs; short K."""
+    def plan(m, n, k, epi, room=None):
+        p = fa.fastav_linear_plan(m, n, k, epi, fa.BF16, room)
+        return (p.tile_rows, p.tile_cols, p.splits) if p.kernel == fa.LINEAR_RING else p.kernel
+    tile = lambda m, n: 4 * m * n
+    assert plan(224, 4096, 14336, fa.EPI_RESADD) == (256, 128, 8)
+    assert plan(224, 4096, 14336, fa.EPI_RESADD, 0) == fa.LINEAR_TILES
+    assert plan(224, 4096, 14336, fa.EPI_RESADD, 3 * tile(224, 4096)) == fa.LINEAR_TILES
+    assert plan(224, 4096, 14336, fa.EPI_RESADD, 5 * tile(224, 4096) + 100) == (256, 128, 5)
+    assert plan(64, 4096, 14336, fa.EPI_RESADD) == (64, 64, 4)
+    assert plan(64, 4096, 14336, fa.EPI_RESADD, 0) == (64, 64, 1)
+    assert plan(64, 4096, 14336, fa.EPI_RESADD, 2 * tile(64, 4096)) == (64, 64, 2)
+    assert plan(100, 4096, 4096, fa.EPI_RESADD, 0) == (128, 64, 1) and plan(160, 4096, 4096, fa.EPI_RESADD, 0) == fa.LINEAR_TILES
+    assert plan(192, 5120, 5120, fa.EPI_RESADD) == (192, 64, 3) and plan(193, 5120, 5120, fa.EPI_RESADD) == fa.LINEAR_TILES
+    assert plan(192, 8192, 8192, fa.EPI_RESADD) == (192, 128, 4) and plan(193, 8192, 8192, fa.EPI_RESADD) == fa.LINEAR_TILES
+    assert plan(128, 8192, 28672, fa.EPI_RESADD) == (128, 128, 4) and plan(129, 8192, 28672, fa.EPI_RESADD) == fa.LINEAR_TILES
+    assert plan(144, 15360, 5120, fa.EPI_STORE) == (192, 64, 1) and plan(145, 15360, 5120, fa.EPI_STORE) == fa.LINEAR_TILES
+    assert plan(192, 6144, 4096, fa.EPI_STORE) == (128, 64, 1)
+    assert plan(300, 8192, 2048, fa.EPI_STORE) == (192, 64, 1) and plan(300, 8192, 1984, fa.EPI_STORE) == fa.LINEAR_TILES
+    assert plan(331, 18944, 3584, fa.EPI_SWIGLU) == (384, 160, 1) and plan(385, 18944, 3584, fa.EPI_SWIGLU) == fa.LINEAR_TILES
+
+
 def test_schedule_n_last_counts_non_text_tail_once():
     # last 3 positions: one audio + two text -> protected = 4 text + 1 audio
     cu = [0, 20]
