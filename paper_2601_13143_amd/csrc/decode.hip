@@ -169,6 +169,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t skinny_rsrc(const void* p, uin
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, bytes, 0x00020000);
 }
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+constexpr uint32_t kSkinnyOutside = 0x80000000u;            // a lane offset beyond every resource: such a load returns zero
 template <typename T>
 __device__ __forceinline__ T skinny_load(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t off) {
   return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0));
@@ -187,10 +188,16 @@ __device__ __forceinline__ f32x4v skinny_sum(const f32x4v (*red)[64], int lane) 
 // 1 / rms of every row from the sums of squares ss_in, into rs[16]; the caller's next barrier publishes it.  Thread =
 // (row, one of 32 column ranges), partial sums in range order.
 __device__ __forceinline__ void skinny_rms_part(const SkinnyArgs& a, int tid, float (*part)[16]) {
+  constexpr int R = 4 * kSkinnyWaves, U = 8;                  // U loads at a time: one after the other each waits for its own
   const int b = tid & 15, q = tid >> 4, n = a.K / 16;
   float t = 0.f;
-  if (b < a.B)
-    for (int i = q; i < n; i += 4 * kSkinnyWaves) t += a.ss_in[i * 16 + b];
+  for (int i = q; i < n; i += R * U) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i + R * u < n && b < a.B ? a.ss_in[(i + R * u) * 16 + b] : 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) t += v[u];
+  }
   part[q][b] = t;
 }
 __device__ __forceinline__ float skinny_rms(const SkinnyArgs& a, int b, const float (*part)[16]) {
@@ -292,82 +299,133 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArg
   }
 }
 
-// Any K, any epilogue, bf16 input: one item per workgroup; a wave walks its 64-k blocks four at a time with three such
-// chunks of weights and input operands in flight (192 KB of weights per workgroup; the input comes from L2).  This is
-// the O and down projections' kernel: their few items leave nothing to keep the batch resident for.
-// Before, batches of 16 loads with a serial remainder: down projection of 4096 x 14336 at 8 rows 30 us = 3.9 TB/s.
-template <int EPI>
+// Any K, any epilogue, bf16 input: P items per workgroup; a wave walks its 64-k blocks C at a time with three such chunks of
+// weights and input operands in flight (96 KB of weights per workgroup; the input comes from L2, once for all P items).
+// This is the O and down projections' kernel: their few items leave nothing to keep the batch resident for.  Eight rows:
+// down of 4096 x 14336 33 -> 27 us = 4.4 TB/s against batches of 16 loads with a serial remainder, O of 4096 x 4096 10.6 -> 9.9.
+// The stream carries nothing but what is needed, in order: loads past the end that repeat the last block cost down 5 us and
+// O of 1024 x 1024 7 of 11; a load behind a run-time test makes the compiler wait for its registers.
+template <int EPI, int P>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs a) {
-  constexpr int C = 4;
-  __shared__ f32x4v red[2][kSkinnyWaves][64];
+  constexpr int C = 2 / P, NG = 2 * P;                        // blocks per chunk, groups of 8 weight rows
+  __shared__ f32x4v red[NG][kSkinnyWaves][64];
   __shared__ float ss[EPI == FASTAV_EPI_RESADD ? 1 : 4 * kSkinnyWaves][16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kb = a.K / 64, item = blockIdx.x;
+  const int kb = a.K / 64, item0 = blockIdx.x * P;
   const int b = (lane & 15) < a.B ? (lane & 15) : a.B - 1;
   const int kq = (lane >> 4) * 8;
-  const bf16_t *p0, *p1;
-  skinny_rows<EPI>(a, item, p0, p1);
   const uint32_t woff = ((uint32_t)(lane & 7) * (uint32_t)a.K + ((lane >> 3) & 1) * 32 + kq) * 2, xoff = (uint32_t)(b * a.K + kq) * 2;
-  const __amdgpu_buffer_rsrc_t r0 = skinny_rsrc(p0, 16u * (uint32_t)a.K), r1 = skinny_rsrc(p1, 16u * (uint32_t)a.K);
+  __amdgpu_buffer_rsrc_t r[NG];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const bf16_t *p0, *p1;
+    skinny_rows<EPI>(a, item0 + p, p0, p1);
+    r[2 * p] = skinny_rsrc(p0, 16u * (uint32_t)a.K);
+    r[2 * p + 1] = skinny_rsrc(p1, 16u * (uint32_t)a.K);
+  }
   const __amdgpu_buffer_rsrc_t rx = skinny_rsrc(a.x, (uint32_t)(a.B * a.K) * 2u);
   f32x4v y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
+  static_assert(EPI != FASTAV_EPI_RESADD || P == 1, "the residual of one item is held");
   if (EPI == FASTAV_EPI_RESADD && wave == 0) {                // ahead of the stream: not waited for until the end
-    const float* y = (const float*)a.y + (int64_t)b * a.ldy + item * 16 + ((lane >> 4) & 1) * 4;
+    const float* y = (const float*)a.y + (int64_t)b * a.ldy + item0 * 16 + ((lane >> 4) & 1) * 4;
     y0 = *(const f32x4v*)y;
     y1 = *(const f32x4v*)(y + 8);
   }
-  bf16x8_t w0[2][C], w1[2][C], w2[2][C], x0[C][2], x1[C][2], x2[C][2];
-  auto load = [&](bf16x8_t (&w)[2][C], bf16x8_t (&x)[C][2], int ch) __attribute__((always_inline)) {
+  // as 32-bit words: vectors of 16-bit elements that meet behind a branch are rebuilt from halves, which waits for them
+  u32x4v w0[NG][C], w1[NG][C], w2[NG][C], x0[C][2], x1[C][2], x2[C][2];
+  // Blocks past the end exist in the last chunk only: their lane offset lies outside every resource, so they read as zero
+  // and touch no memory.
+  auto load = [&](u32x4v (&w)[NG][C], u32x4v (&x)[C][2], int ch, bool last) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < C; ++u) {
-      int blk = wave + kSkinnyWaves * (ch * C + u);
-      blk = blk < kb ? blk : kb - 1;                          // past the end: read again, not used
-      w[0][u] = skinny_load<bf16x8_t>(r0, woff, blk * 128);
-      w[1][u] = skinny_load<bf16x8_t>(r1, woff, blk * 128);
-      x[u][0] = skinny_load<bf16x8_t>(rx, xoff, blk * 128);
-      x[u][1] = skinny_load<bf16x8_t>(rx, xoff + 64, blk * 128);
+      const int blk = wave + kSkinnyWaves * (ch * C + u);
+      const bool in = !last || blk < kb;
+      const uint32_t off = in ? (uint32_t)blk * 128u : 0u, wl = in ? woff : kSkinnyOutside, xl = in ? xoff : kSkinnyOutside;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) w[g][u] = skinny_load<u32x4v>(r[g], wl, off);
+      x[u][0] = skinny_load<u32x4v>(rx, xl, off);
+      x[u][1] = skinny_load<u32x4v>(rx, xl + 64, off);
     }
+    __builtin_amdgcn_sched_barrier(0);                        // requested here, not next to their use
   };
-  f32x4v a00 = {0.f, 0.f, 0.f, 0.f}, a01 = a00, a10 = a00, a11 = a00;   // [group][half]
-  auto compute = [&](bf16x8_t (&w)[2][C], bf16x8_t (&x)[C][2], int ch) __attribute__((always_inline)) {
+  f32x4v acc[NG][2];                                          // [group][half]
+#pragma unroll
+  for (int g = 0; g < NG; ++g) acc[g][0] = acc[g][1] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](u32x4v (&w)[NG][C], u32x4v (&x)[C][2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < C; ++u)
-      if (wave + kSkinnyWaves * (ch * C + u) < kb) {          // uniform
-        a00 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[0][u], x[u][0], a00, 0, 0, 0);
-        a01 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[0][u], x[u][1], a01, 0, 0, 0);
-        a10 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[1][u], x[u][0], a10, 0, 0, 0);
-        a11 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[1][u], x[u][1], a11, 0, 0, 0);
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const bf16x8_t wv = __builtin_bit_cast(bf16x8_t, w[g][u]);
+        acc[g][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(bf16x8_t, x[u][0]), acc[g][0], 0, 0, 0);
+        acc[g][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(bf16x8_t, x[u][1]), acc[g][1], 0, 0, 0);
       }
+    __builtin_amdgcn_sched_barrier(0);
   };
+  // every end of the walk has a body of its own: a load behind a run-time test inside the stream costs it its depth
   const int nch = (kb + kSkinnyWaves * C - 1) / (kSkinnyWaves * C);
-  load(w0, x0, 0);
-  load(w1, x1, 1);
-  load(w2, x2, 2);
-  if (EPI != FASTAV_EPI_RESADD && a.ss_in != nullptr) skinny_rms_part(a, tid, ss);
-  int ch = 0;
-  for (; ch + 3 < nch; ch += 3) {
-    compute(w0, x0, ch);
-    load(w0, x0, ch + 3);
-    compute(w1, x1, ch + 1);
-    load(w1, x1, ch + 4);
-    compute(w2, x2, ch + 2);
-    load(w2, x2, ch + 5);
+  const bool scaled = EPI != FASTAV_EPI_RESADD && a.ss_in != nullptr;
+  if (nch >= 3) {
+    load(w0, x0, 0, false);
+    load(w1, x1, 1, false);
+    load(w2, x2, 2, true);
+    if (scaled) skinny_rms_part(a, tid, ss);
+    int ch = 3;
+    for (; ch + 2 < nch; ch += 3) {
+      compute(w0, x0);
+      load(w0, x0, ch, false);
+      compute(w1, x1);
+      load(w1, x1, ch + 1, false);
+      compute(w2, x2);
+      load(w2, x2, ch + 2, true);
+    }
+    if (ch == nch) {
+      compute(w0, x0);
+      compute(w1, x1);
+      compute(w2, x2);
+    } else if (ch + 1 == nch) {
+      compute(w0, x0);
+      load(w0, x0, ch, true);
+      compute(w1, x1);
+      compute(w2, x2);
+      compute(w0, x0);
+    } else {
+      compute(w0, x0);
+      load(w0, x0, ch, false);
+      compute(w1, x1);
+      load(w1, x1, ch + 1, true);
+      compute(w2, x2);
+      compute(w0, x0);
+      compute(w1, x1);
+    }
+  } else if (nch == 2) {
+    load(w0, x0, 0, false);
+    load(w1, x1, 1, true);
+    if (scaled) skinny_rms_part(a, tid, ss);
+    compute(w0, x0);
+    compute(w1, x1);
+  } else {
+    load(w0, x0, 0, true);
+    if (scaled) skinny_rms_part(a, tid, ss);
+    compute(w0, x0);
   }
-  compute(w0, x0, ch);
-  compute(w1, x1, ch + 1);
-  compute(w2, x2, ch + 2);
-  red[0][wave][lane] = lane < 32 ? a00 : a01;
-  red[1][wave][lane] = lane < 32 ? a10 : a11;
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    f32x4v t;                                                 // by element: a choice between two array elements goes through memory
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = lane < 32 ? acc[g][0][e] : acc[g][1][e];
+    red[g][wave][lane] = t;
+  }
   lds_barrier();
-  if (wave != 0) return;
-  f32x4v v0 = skinny_sum(red[0], lane), v1 = skinny_sum(red[1], lane);
-  if (EPI != FASTAV_EPI_RESADD && a.ss_in != nullptr) {
-    const float r = skinny_rms(a, lane & 15, ss);
-    v0 = v0 * r;
-    v1 = v1 * r;
+  if (wave >= P) return;                                      // wave p finishes item p
+  f32x4v v0 = skinny_sum(red[2 * wave], lane), v1 = skinny_sum(red[2 * wave + 1], lane);
+  if (scaled) {
+    const float f = skinny_rms(a, lane & 15, ss);
+    v0 = v0 * f;
+    v1 = v1 * f;
   }
-  skinny_finish<EPI>(a, item, lane, v0, v1, y0, y1);
+  skinny_finish<EPI>(a, item0 + wave, lane, v0, v1, y0, y1);
 }
 
 // ---------------------------------------------------------------------------------------- one-row GEMV
@@ -598,13 +656,20 @@ fastav_status_t launch_skinny_linear(const void* x, const void* const* w_seg, co
     return check_launch("gemv_rows");
   }
   // Items have 16 features (8 pairs for SwiGLU).  Up to 4096 columns the batch fits a workgroup's registers and 256
-  // workgroups (one per CU) walk the items; longer rows and the residual epilogue take the streaming kernel.
+  // workgroups (one per CU) walk the items; longer rows, the residual epilogue and products of one item per workgroup,
+  // which leave nothing to be resident for, take the streaming kernel (8 rows, resident against streaming: 256 items of
+  // 4096 columns 12.8 / 9.9 us, 192 of 2048 7.7 / 6.5, 288 of 3584 12.5 / 15.4).  Two gate/up items per workgroup share
+  // the input where that leaves a workgroup per CU (28672 x 8192, one against two: 4 rows 192 / 179 us, 8 rows 202 / 180,
+  // 16 rows 239 / 188; 2 rows of 8192 x 8192 56.6 / 58.2).
   const int items = epilogue == FASTAV_EPI_SWIGLU ? n / 8 : n / 16;
   const int nb = (k / 64 + kSkinnyWaves - 1) / kSkinnyWaves;
-  if (epilogue == FASTAV_EPI_RESADD || nb > 8) {
-    if (epilogue == FASTAV_EPI_RESADD) hipLaunchKernelGGL((k_skinny_stream<FASTAV_EPI_RESADD>), dim3((unsigned)items), dim3(64 * kSkinnyWaves), 0, s, a);
-    else if (epilogue == FASTAV_EPI_SWIGLU) hipLaunchKernelGGL((k_skinny_stream<FASTAV_EPI_SWIGLU>), dim3((unsigned)items), dim3(64 * kSkinnyWaves), 0, s, a);
-    else hipLaunchKernelGGL((k_skinny_stream<FASTAV_EPI_STORE>), dim3((unsigned)items), dim3(64 * kSkinnyWaves), 0, s, a);
+  if (epilogue == FASTAV_EPI_RESADD || nb > 8 || items <= 256) {
+#define FASTAV_STREAM(EPI, P) hipLaunchKernelGGL((k_skinny_stream<EPI, P>), dim3((unsigned)(items / P)), dim3(64 * kSkinnyWaves), 0, s, a)
+    if (epilogue == FASTAV_EPI_RESADD) FASTAV_STREAM(FASTAV_EPI_RESADD, 1);
+    else if (epilogue == FASTAV_EPI_STORE) FASTAV_STREAM(FASTAV_EPI_STORE, 1);
+    else if (B > 4 && items >= 512) FASTAV_STREAM(FASTAV_EPI_SWIGLU, 2);       // n is a multiple of 16: items are even
+    else FASTAV_STREAM(FASTAV_EPI_SWIGLU, 1);
+#undef FASTAV_STREAM
     return check_launch("skinny_stream");
   }
   const dim3 grid((unsigned)(items < 256 ? items : 256));
