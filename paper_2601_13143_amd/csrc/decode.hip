@@ -233,10 +233,10 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArg
     const __amdgpu_buffer_rsrc_t r0 = skinny_rsrc(p0, wbytes), r1 = skinny_rsrc(p1, wbytes);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      int blk = wave + kSkinnyWaves * j;
-      blk = blk < kb ? blk : kb - 1;                          // past the end: the input operand is zero
-      w[0][j] = skinny_load<bf16x8_t>(r0, woff, blk * 128);
-      w[1][j] = skinny_load<bf16x8_t>(r1, woff, blk * 128);
+      const int blk = wave + kSkinnyWaves * j;                // past the end both operands are zero: an infinite weight of
+      const uint32_t off = blk < kb ? woff : kSkinnyOutside;  // the last block must not meet a zero input
+      w[0][j] = skinny_load<bf16x8_t>(r0, off, blk < kb ? blk * 128 : 0);
+      w[1][j] = skinny_load<bf16x8_t>(r1, off, blk < kb ? blk * 128 : 0);
     }
   };
   bf16x8_t xf[NB][2], w0[2][NB], w1[2][NB];
@@ -244,11 +244,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArg
   for (int j = 0; j < NB; ++j) {
     const int blk = wave + kSkinnyWaves * j;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const bf16x8_t z = {0, 0, 0, 0, 0, 0, 0, 0};
-      const bf16x8_t v = skinny_load<bf16x8_t>(rx, xoff, (blk < kb ? blk : 0) * 128 + h * 64);
-      xf[j][h] = blk < kb ? v : z;
-    }
+    for (int h = 0; h < 2; ++h) xf[j][h] = skinny_load<bf16x8_t>(rx, blk < kb ? xoff + h * 64 : kSkinnyOutside, blk < kb ? blk * 128 : 0);
   }
   const int it0 = blockIdx.x;
   load(w0, it0);

@@ -64,6 +64,28 @@ def test_decode_linear_ends_of_the_streamed_rows(B, N, K, epi):
     assert_close(got, want, "bf16", what=f"skinny linear {B}x{N}x{K} epi {epi}")
 
 
+@pytest.mark.parametrize("epi", [fa.EPI_STORE, fa.EPI_SWIGLU])
+@pytest.mark.parametrize("N,K", [(4112, 640), (8208, 1920), (48, 2112)])
+def test_decode_linear_infinite_weight_in_the_last_block(N, K, epi):
+    """Waves whose blocks lie past the end of a row must not multiply the last one with zero: an infinite weight (up weight) gives
+    an infinite output of the input's sign, and no other output changes."""
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    a = torch.randn((3, K), device="cuda", generator=gen).bfloat16()
+    w, w2 = ((torch.randn((N, K), device="cuda", generator=gen) / K ** 0.5).bfloat16() for _ in range(2))
+    a[:, K - 1] = torch.tensor([1.0, -2.0, 0.5])
+    run = lambda: fa.fastav_linear(a, w, epi, w2 if epi == fa.EPI_SWIGLU else None)
+    plain = run()
+    at = [0, 7, 8, N - 1]
+    (w2 if epi == fa.EPI_SWIGLU else w)[at, K - 1] = float("inf")
+    got = run()
+    want = plain.clone()
+    sign = a[:, K - 1:].float().sign().expand(-1, len(at))
+    if epi == fa.EPI_SWIGLU:
+        sign = sign * (a.float() @ w[at].float().T).sign()                 # silu(gate) * inf
+    want[:, at] = (sign * float("inf")).bfloat16()
+    assert torch.equal(got, want)
+
+
 def _caches_from_oracle(w, weights, x):
     """Oracle pruned prefill -> per layer bf16-rounded (K, V) packed over the batch, rows per sample."""
     ref = orc.prefill(w, weights, x)
