@@ -253,16 +253,18 @@ __global__ __launch_bounds__(512) void k_score_logits_mfma(const bf16_t* __restr
 }
 
 // ml_in != nullptr: per-head (m, l) given as [batch, n_last, Hq, 2]; else merged here from partials.
-// V = positions per thread: 4 (16-byte loads) for long samples and batches; 1 where that would leave most CUs without a
-// workgroup - the time is then one thread's chain of exponentials, V per plane - or where planes are not 16-byte aligned.
-// 2048 tokens, 32 heads: 11.8 us with four, 9.0 with one.
+// V = positions per thread: 4 (16-byte loads) for long samples and batches; 1 where that would leave CUs without a
+// workgroup - the time is then one thread's chain of exponentials, V per plane.
+// Both kernels of a score, 32 heads, four against one: 2048 tokens 15.9 / 11.9 us, 16384 24.7 / 20.7, 98304 (97 workgroups
+// of four) 57.8 / 55.0, 131072 (129) 74.2 / 71.5, 8 x 16384 (136) 62.2 / 58.7; 196608 (193) 118 / 121, 262144 (257) 153 / 168 -
+// every workgroup of a sample merges all of its partials -, 200 x 1000 (200) and 16 x 16384 (272) equal.
 template <int V>
 __global__ __launch_bounds__(256) void k_score_finalize(const float* __restrict__ logits,
                                                         const float* __restrict__ ml_in,
                                                         const float* __restrict__ partials, int64_t n_chunk_slots,
                                                         const int32_t* __restrict__ cu, int Hq, int n_last,
                                                         int64_t T_total, float* __restrict__ scores) {
-  typedef float fV_t __attribute__((ext_vector_type(V)));
+  typedef float fV_t __attribute__((ext_vector_type(V), aligned(4)));   // planes start anywhere where T_total is odd
   constexpr int kKeys = 256 * V;
   constexpr int kFinalizeBatch = 32 / V;                   // planes in flight per thread
   extern __shared__ float mls[];                           // [n_rows*Hq][2] : (m, 1/l)
@@ -271,9 +273,10 @@ __global__ __launch_bounds__(256) void k_score_finalize(const float* __restrict_
   if ((int)(blockIdx.x * kKeys) >= n + V - 1) return;
   const int n_rows = n_last < n ? n_last : n;
   const int P = n_rows * Hq;
-  // a thread owns V consecutive positions of the packed token axis, aligned to 4 V bytes there (a sample may start
-  // anywhere, so four may hang over the sample's ends: those lanes of it are dropped).  The first kFinalizeBatch planes
-  // are requested before the (max, sum) merge below, which does not depend on them.
+  // a thread owns V consecutive positions of the packed token axis, a multiple of V there (a sample may start anywhere, so
+  // four may hang over the sample's ends: those are dropped; over the end of the last plane by up to three floats, where
+  // the partial sums or the (max, sum) pairs of the same workspace lie).  The first kFinalizeBatch planes are requested
+  // before the (max, sum) merge below, which does not depend on them.
   const int64_t q0 = (int64_t)(row0 & ~(V - 1)) + (int64_t)blockIdx.x * kKeys + threadIdx.x * V;
   const bool mine = q0 < row0 + n;
   fV_t L[kFinalizeBatch];
@@ -403,9 +406,10 @@ fastav_status_t launch_score_logits(const void* q, int64_t q_stride, const void*
   if (shmem > 64 * 1024) return fail(FASTAV_EUNSUPPORTED, "score: n_q_heads*(head_dim+128)*4 bytes must fit 64 KB of LDS");
   if (dtype == FASTAV_BF16 && G * n_last <= 64 && q_stride % 8 == 0 && k_stride % 8 == 0 &&
       (((uintptr_t)q | (uintptr_t)k) % 16) == 0) {
-    // waves (KV heads) per workgroup; one where eight would leave most CUs without work (a wave's heads are its own, so
-    // the waves do not care): 2048 tokens of 8 heads are 16 workgroups of eight, 11.9 us, or 128 of one, 5.6 us
-    const int wpg = (int64_t)grid.x * batch < 128 ? 1 : Hkv < 8 ? Hkv : 8;
+    // waves (KV heads) per workgroup; one where eight would leave CUs without work (a wave's heads are its own, so the
+    // waves do not care).  8 KV heads, both kernels of a score, eight against one: 16 chunks (2048 tokens) 18.4 / 11.9 us,
+    // 64 19.2 / 13.7, 128 20.7 / 17.1, 192 21.9 / 21.3, from 256 chunks on equal
+    const int wpg = (int64_t)grid.x * batch < 256 ? 1 : Hkv < 8 ? Hkv : 8;
     // one 128-key chunk per workgroup, chunks in launch order: neighbouring workgroups stream neighbouring
     // memory (letting a workgroup walk chunks a stride apart measured 10 % slower)
     const dim3 grid_m(grid.x, grid.y, (unsigned)((Hkv + wpg - 1) / wpg));
@@ -436,7 +440,7 @@ fastav_status_t launch_score_finalize(const float* logits, const float* ml, cons
   const size_t shmem = (size_t)n_last * Hq * 2 * sizeof(float);
   // + 3: a sample that starts off a 16-byte boundary needs up to three more positions
   const int64_t wg4 = ceil_div(max_seqlen + 3, 1024);
-  if (T % 4 == 0 && ((uintptr_t)logits & 15) == 0 && wg4 * batch >= 128)
+  if (wg4 * batch >= 160)
     hipLaunchKernelGGL(k_score_finalize<4>, dim3((unsigned)wg4, (unsigned)batch), dim3(256), shmem, s, logits, ml, partials,
                        chunk_slots(T, batch), cu, Hq, n_last, T, scores);
   else
