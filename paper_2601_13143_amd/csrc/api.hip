@@ -69,7 +69,6 @@ fastav_status_t launch_skinny_linear(const void* x, const void* const* w_seg, co
                                      hipStream_t s, const float* norm_x = nullptr, const void* norm_g = nullptr,
                                      float norm_eps = 0.f, const SkinnyRope* rope = nullptr, const SkinnyAppend* app = nullptr,
                                      const float* ss_in = nullptr, const SkinnyNext* next = nullptr);
-bool skinny_fuses_rope(int B, int n, int k, bool norm, int rope_rows, int dh);
 size_t decode_attn_workspace_bytes(int batch, int Hq, int dh, int max_splits);
 fastav_status_t launch_decode_attention(const void* q, const void* k_self, const void* v_self, int64_t q_stride,
                                         const void* k_prefix, const void* v_prefix, const int32_t* cu_prefix,
@@ -875,11 +874,15 @@ fastav_status_t fastav_decode_step(fastav_handle_t h, const fastav_decode_in_t* 
       !skinny_linear_supported(B, m.hidden, qd, m.dtype, m.hidden) || !skinny_linear_supported(B, m.mlp_dim, m.hidden, m.dtype, m.mlp_dim) ||
       !skinny_linear_supported(B, m.hidden, m.mlp_dim, m.dtype, m.hidden))
     return fail(FASTAV_EUNSUPPORTED, "decode step: hidden, heads*head_dim and mlp_dim must be multiples of 128");
+  if (m.n_q_heads / m.n_kv_heads > 8) return fail(FASTAV_EUNSUPPORTED, "decode step: at most 8 query heads per KV head");
+  // all of it before the first launch: the first product already appends to the generated-token caches
   for (int l = 0; l < m.n_layers; ++l) {
     if (!h->has_w[l]) return fail(FASTAV_EINVAL, "weights of layer %d were never set", l);
     if (!in->k_prefix[l] || !in->v_prefix[l] || !in->cu_prefix[l]) return fail(FASTAV_EINVAL, "a cache pointer of layer %d is NULL", l);
     if (in->max_prefix[l] < 0) return fail(FASTAV_EINVAL, "max_prefix[%d] is negative", l);
     if (in->k_gen && (!in->k_gen[l] || !in->v_gen[l])) return fail(FASTAV_EINVAL, "a generated-token cache pointer of layer %d is NULL", l);
+    if (((uintptr_t)in->k_prefix[l] | (uintptr_t)in->v_prefix[l] | (in->k_gen ? (uintptr_t)in->k_gen[l] | (uintptr_t)in->v_gen[l] : 0)) % 16)
+      return fail(FASTAV_EINVAL, "a cache pointer of layer %d is not 16-byte aligned", l);
   }
   char* base = (char*)workspace;
   float* x = (float*)(base + ws.x);
@@ -894,7 +897,6 @@ fastav_status_t fastav_decode_step(fastav_handle_t h, const fastav_decode_in_t* 
   // value to slot gen_len of the [B, gen_cap, kd] caches
   const bool fuse_norm = skinny_norm_supported(B, m.hidden), carry = B > 1;
   float* ss = carry ? (float*)(base + ws.ss) : nullptr;
-  const bool fuse_rope = skinny_fuses_rope(B, qkvd, m.hidden, fuse_norm, qd + kd, m.head_dim);
   FASTAV_TRY(launch_decode_begin(in->x_new, x, in->pos_new, base + ws.rope, B, m.hidden, m.head_dim, m.rope_base,
                                  SkinnyNext{h->w[0].g_attn, carry ? hn : nullptr, ss}, s));
   const SkinnyRope rope = {in->pos_new, base + ws.rope, qd + kd, m.head_dim, m.rope_base};
@@ -904,13 +906,9 @@ fastav_status_t fastav_decode_step(fastav_handle_t h, const fastav_decode_in_t* 
     const void* seg[3] = {W.wq, W.wk, W.wv};
     const int rows[3] = {qd, kd, kd};
     SkinnyAppend app = {nullptr, nullptr, (int64_t)in->gen_cap * kd};
-    const bool fuse_app = in->k_gen && fuse_rope && ((uintptr_t)in->k_gen[l] | (uintptr_t)in->v_gen[l]) % 16 == 0;
-    if (fuse_app) { app.k = (bf16_t*)in->k_gen[l] + (size_t)in->gen_len * kd; app.v = (bf16_t*)in->v_gen[l] + (size_t)in->gen_len * kd; }
+    if (in->k_gen) { app.k = (bf16_t*)in->k_gen[l] + (size_t)in->gen_len * kd; app.v = (bf16_t*)in->v_gen[l] + (size_t)in->gen_len * kd; }
     FASTAV_TRY(launch_skinny_linear(hn, seg, rows, 3, nullptr, qkv, qkvd, B, qkvd, m.hidden, FASTAV_EPI_STORE, s,
-                                    fuse_norm ? x : nullptr, W.g_attn, m.rms_eps, fuse_rope ? &rope : nullptr, fuse_app ? &app : nullptr, ss));
-    // the key heads follow the query heads in the row: one launch rotates both
-    if (!fuse_rope)
-      FASTAV_TRY(launch_rope(qkv, qkvd, in->pos_new, B, m.n_q_heads + m.n_kv_heads, m.head_dim, m.rope_base, m.dtype, s));
+                                    fuse_norm ? x : nullptr, W.g_attn, m.rms_eps, &rope, in->k_gen ? &app : nullptr, ss));
     const void* kg = in->k_gen ? in->k_gen[l] : nullptr;
     const void* vg = in->v_gen ? in->v_gen[l] : nullptr;
     // bytes the attention step has to move: the caches once (upper bound: the longest sample for all)
@@ -919,12 +917,6 @@ fastav_status_t fastav_decode_step(fastav_handle_t h, const fastav_decode_in_t* 
                                        in->v_prefix[l], in->cu_prefix[l], in->max_prefix[l], kg, vg, in->gen_len,
                                        in->gen_cap, B, m.n_q_heads, m.n_kv_heads, m.head_dim, (float*)(base + ws.part),
                                        ws.part_bytes, attn, qd, abytes, s));
-    if (in->k_gen && !fuse_app) {
-      FASTAV_TRY(launch_copy_rows(qkv + (size_t)qd * 2, (int64_t)qkvd * 2, (char*)in->k_gen[l] + (size_t)in->gen_len * kd * 2,
-                                  (int64_t)kd * 2, B, nullptr, s, (int64_t)in->gen_cap * kd * 2));
-      FASTAV_TRY(launch_copy_rows(qkv + (size_t)(qd + kd) * 2, (int64_t)qkvd * 2, (char*)in->v_gen[l] + (size_t)in->gen_len * kd * 2,
-                                  (int64_t)kd * 2, B, nullptr, s, (int64_t)in->gen_cap * kd * 2));
-    }
     const void* so[1] = {W.wo};
     const int ro[1] = {m.hidden};
     const SkinnyNext mlp = {W.g_mlp, hn, ss}, attn_next = {l + 1 < m.n_layers ? h->w[l + 1].g_attn : nullptr, hn, ss};

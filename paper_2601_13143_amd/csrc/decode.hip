@@ -585,7 +585,7 @@ bool skinny_norm_supported(int B, int k) { return gemv_rows_supported(B, 16, k, 
 
 // Whether the store epilogue rotates the leading rope_rows features (whole heads); n must be whole heads too.  The
 // one-row GEMV evaluates the angles itself, the matrix-core kernels read a table of the batch (SkinnyRope::table).
-bool skinny_fuses_rope(int B, int n, int k, bool norm, int rope_rows, int dh) {
+static bool skinny_fuses_rope(int B, int n, int k, bool norm, int rope_rows, int dh) {
   if (gemv_rows_supported(B, n, k, norm)) return gemv_rows_fuses_rope(B, n, k, norm, rope_rows, dh);
   return (dh == 64 || dh == 128) && rope_rows % dh == 0 && n % dh == 0 && rope_rows <= n;
 }

@@ -290,3 +290,21 @@ def test_probes_and_options_reject_bad_arguments():
     for opt in (B.OPT_FUSED_SCORE_SELECT, B.OPT_FUSED_ROPE, B.OPT_FUSED_SPLITK_NORM, B.OPT_FUSED_GATHER_OPROJ):
         assert lib.fastav_set_option(opt, 0) == B.OK and lib.fastav_set_option(opt, 1) == B.OK
 
+
+@pytest.mark.parametrize("heads,off,status,word", [((9, 1), 0, B.EUNSUPPORTED, b"8 query heads"), ((8, 2), 2, B.EINVAL, b"aligned")])
+def test_decode_step_refuses_caches_and_head_groups_before_any_launch(heads, off, status, word):
+    """The step's first product writes the new key and value to the generated-token caches, so what attention would refuse is
+    refused first."""
+    lib = fa.lib()
+    h, fake = C.c_void_p(), 1 << 20
+    m = fa.make_model(1, 128, heads[0], heads[1], 128, 128)
+    assert lib.fastav_create(C.byref(m), C.byref(h)) == B.OK
+    assert lib.fastav_set_weights(h, 0, C.byref(B.LayerWeights(*[fake] * 9))) == B.OK
+    ptrs = lambda v: (C.c_void_p * 1)(v)
+    need = C.c_size_t()
+    assert lib.fastav_decode_workspace_bytes(h, 2, C.byref(need)) == B.OK
+    for kp, kg in ((off, 0), (0, off)):
+        di = B.DecodeIn(2, fake, fake, ptrs(fake + kp), ptrs(fake), ptrs(fake), (C.c_int32 * 1)(4), ptrs(fake), ptrs(fake + kg), 0, 4)
+        assert lib.fastav_decode_step(h, C.byref(di), fake, fake, need.value, None) == status
+        assert word in lib.fastav_last_error()
+    lib.fastav_destroy(h)
