@@ -276,6 +276,57 @@ def test_decode_step_head_layouts(hq, hkv, dh, batch):
     assert_close(host(r["x_out"]), want, "bf16", scale=float(np.sqrt(np.mean(want ** 2))), what=f"decode Hq{hq} Hkv{hkv} dh{dh} B{batch}")
 
 
+def _steps_with_generated_cache(m, batch, n_prefix, steps, seed, gen_cap=4):
+    """Consecutive decode steps on random caches of ragged lengths, with the generated-token caches, against the oracle: hidden
+    states, and the appended keys and values of all layers and steps."""
+    rng = np.random.default_rng(seed)
+    weights = [{k: v.astype(np.float64) for k, v in fi.layer_weights(m, l, seed).items()} for l in range(m.n_layers)]
+    lens = rng.integers(1, n_prefix, size=(m.n_layers, batch)).astype(np.int32)
+    draw = lambda *s: fi.round_bf16(rng.standard_normal(s).astype(np.float32))
+    kv = [tuple(draw(int(lens[l].sum()), m.n_kv_heads, m.head_dim) for _ in range(2)) for l in range(m.n_layers)]
+    x_steps = [draw(batch, m.hidden) for _ in range(steps)]
+    pos0 = rng.integers(n_prefix, 4 * n_prefix, batch).astype(np.int32)
+    dec = make_decoder(m, [{k: v.astype(np.float32) for k, v in W.items()} for W in weights])
+    kv_dev = [(dev(K, "bf16"), dev(V, "bf16")) for K, V in kv]
+    gen = [tuple(torch.full((batch, gen_cap, m.n_kv_heads, m.head_dim), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+           for _ in range(m.n_layers)]
+    cu = np.concatenate([np.zeros((m.n_layers, 1), np.int64), np.cumsum(lens, axis=1)], axis=1)
+    caches = [[tuple(t[cu[l, b]:cu[l, b + 1]].astype(np.float64) for t in kv[l]) for l in range(m.n_layers)] for b in range(batch)]
+    state = None
+    for t in range(steps):
+        r = dec.fastav_decode_step(dev(x_steps[t], "bf16"), torch.from_numpy(pos0 + t).cuda(), kv_dev, lens, gen=gen, gen_len=t, state=state)
+        state = r["state"]
+        torch.cuda.synchronize()
+        for b in range(batch):
+            ref = orc.decode_step(m, weights, x_steps[t][b].astype(np.float64), int(pos0[b]) + t, caches[b])
+            scale = float(np.sqrt(np.mean(ref["x_out"] ** 2)))
+            assert_close(host(r["x_out"])[b], ref["x_out"], "bf16", scale=scale, what=f"step {t} sample {b}")
+            for l in range(m.n_layers):
+                for i, what in ((0, "K"), (1, "V")):
+                    got, want = host(gen[l][i][b, t]), ref["kv"][l][i]
+                    assert_close(got, want, "bf16", scale=max(1.0, float(np.sqrt(np.mean(want ** 2)))), what=f"appended {what} {l} step {t} sample {b}")
+                # both sides read the keys and values that were appended
+                caches[b][l] = tuple(np.concatenate([c, host(gen[l][i][b, t])[None]]) for i, c in enumerate(caches[b][l]))
+    for l in range(m.n_layers):
+        for i in range(2):
+            assert bool((gen[l][i][:, steps:] == 7.0).all())                   # slots behind the last step are untouched
+
+
+@pytest.mark.parametrize("hq,hkv,dh,hidden", [(8, 2, 128, 512), (8, 8, 64, 1024), (7, 1, 128, 1536), (16, 4, 64, 640)])
+def test_one_sample_appends_to_its_generated_cache(hq, hkv, dh, hidden):
+    """One sample: the one-row projections (hidden a multiple of 512) or the matrix-core ones write the token's own key (a rotated
+    pair per wave) and value to the caches."""
+    _steps_with_generated_cache(fi.Model(2, hidden, hq, hkv, dh, 1024, 1.0e4, 1e-6, "bf16"), 1, 90, 3, 11)
+
+
+@pytest.mark.parametrize("batch", [2, 5, 16])
+@pytest.mark.parametrize("hq,hkv,dh", [(16, 2, 128), (18, 6, 64)])
+def test_decode_step_hidden_above_the_resident_limit(batch, hq, hkv, dh):
+    """hidden 4224: Q|K|V and gate/up stream their rows (one and two gate/up items per workgroup) and scale by the sums of squares
+    that the residual projections left, with rotation and cache append in their epilogue."""
+    _steps_with_generated_cache(fi.Model(2, 4224, hq, hkv, dh, 4096, 1.0e4, 1e-6, "bf16"), batch, 70, 2, 5)
+
+
 def test_decode_step_rejects_bad_arguments():
     w, weights, x = _small()
     m = w.model
