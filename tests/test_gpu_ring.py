@@ -141,6 +141,30 @@ def test_prefill_against_the_oracle_and_the_separate_launches(dh):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("hidden,mlp,rows,shares", [(1024, 8192, 60, 16), (2048, 8192, 100, 8), (1536, 5120, 60, 10), (4224, 2048, 100, 3), (5120, 2048, 120, 3), (8192, 1024, 60, 2)])
+def test_prefill_partial_tiles_left_to_the_rmsnorm(hidden, mlp, rows, shares):
+    """Up to 16 partial tiles per residual row, rows of one to eight registers per thread in the RMSNorm that adds them (it reads two
+    or four partial rows at a time): the bits of the separate reduction."""
+    assert _plan(fa.EPI_RESADD, rows, hidden, mlp)[2] == shares
+    m = fi.Model(3, hidden, 8, 2, 128, mlp, 1.0e4, 1e-6, "bf16")
+    w = fi.Workload("partial", m, [[(fi.VIDEO, rows - 20), (fi.TEXT, 20)]], [], seed=5)
+    d = make_decoder(m, [fi.layer_weights(m, l, 37) for l in range(m.n_layers)])
+    spans, offs = fi.span_table(w)
+    xd = dev(fi.embeddings(w), "bf16")
+    res = []
+    try:
+        for fused in (1, 0):
+            fa.fastav_set_option(fa.OPT_FUSED_SPLITK_NORM, fused)
+            o = d.fastav_prefill(xd, fi.cu_seqlens(w), spans, offs, [], 1, want_kv=True)
+            torch.cuda.synchronize()
+            res.append([o["x_out"].clone()] + [t.clone() for p in o["kv"] for t in p])
+    finally:
+        fa.fastav_set_option(fa.OPT_FUSED_SPLITK_NORM, 1)
+    assert all(torch.isfinite(t.float()).all() for t in res[0])
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+@pytest.mark.gpu
 def test_prefill_of_a_batch_agrees_with_its_samples_to_rounding():
     """Tiles and K shares follow the number of rows, and with them the order of the fp32 sums: a batch and its samples alone
     agree to bf16 rounding (every layer's rounding of the hidden state differs in the last place here and there)."""
