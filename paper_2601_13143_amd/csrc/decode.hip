@@ -429,7 +429,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs 
 // With one row there is nothing for the matrix cores to reuse, so the kernel is laid out purely for the weight
 // stream: a wave owns two consecutive weight rows and reads them as whole 1 KB runs (lane = 16-byte chunk), eight
 // to sixteen loads in flight per lane; a workgroup's eight waves cover 16 rows = one contiguous slab.  The input
-// row sits in LDS as bf16 (normalised there when NORM, exactly as k_skinny_linear does it), each 16-byte chunk of
+// row sits in LDS as bf16 (normalised there when NORM, rounded as k_rmsnorm rounds it), each 16-byte chunk of
 // it is read once per pair of rows and multiplied with v_dot2_f32_bf16 into fp32 sums, which the wave reduces at
 // the end.  K % 512 == 0.
 __device__ __forceinline__ float dot8(bf16x8_t w, bf16x8_t x, float acc) {

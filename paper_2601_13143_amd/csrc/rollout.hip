@@ -5,11 +5,12 @@
 //
 // The head-mean map is formed without ever holding a per-head n x n map: a first pass computes every query
 // row's softmax (max, sum) per head by streaming K through the matrix cores (S^T = K Q^T tiles, running
-// max / sum per lane, like the prefill attention but with no values), a second pass recomputes each 128 x 64
+// max / sum per lane, like the prefill attention but with no values), a second pass recomputes each 32 x 64
 // tile of logits for every head, turns it into probabilities with those (max, sum) and accumulates the mean
 // in registers, so A is written exactly once (bf16, the operand type of the GEMM that consumes it).  Both
 // passes read Q and K straight from global memory in MFMA operand layout (they are served by L2: a tile of
-// one head is a few KB and is reused by the neighbouring workgroups); no LDS, no barriers.
+// one head is a few KB and is reused by the neighbouring workgroups); LDS holds only what the eight waves of a
+// workgroup, which share out the keys or the heads, sum at the end.
 //
 // The rollout is kept transposed, RT = (R^l)^T, because the library's GEMM multiplies by a row-major [out, in]
 // matrix: RT_new = RT (alpha A + (1 - alpha) I)^T = alpha (RT A^T) + (1 - alpha) RT, and C[i][j] =
