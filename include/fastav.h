@@ -176,7 +176,9 @@ fastav_status_t fastav_workspace_bytes(fastav_handle_t h, int64_t max_total_toke
 
 /* Pruned prefill (Fig. 3): runs every layer on the packed batch and applies the prune schedule.
  * n_last >= 1 is the number of last query rows Eq. 4 averages (the paper uses 1).  With no prunes, or
- * keep_ratio 1.0 everywhere, the result is the plain prefill.  All weights must have been set. */
+ * keep_ratio 1.0 everywhere, the result is the plain prefill.  All weights must have been set.
+ * The kernels' tiles, and with them the order of their fp32 sums, follow the number of packed rows: a batch agrees with
+ * its samples run one by one to rounding, not bit for bit. */
 fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, const fastav_prune_t* prunes,
                                int32_t n_prunes, int32_t n_last, void* workspace, size_t workspace_bytes,
                                const fastav_prefill_out_t* out, void* stream);

@@ -211,8 +211,8 @@ __device__ __forceinline__ float skinny_rms(const SkinnyArgs& a, int b, const fl
 // (NB 64-k blocks per wave, read once) and walks the items blockIdx, + gridDim, ... with two items' weights in flight
 // (128 KB each for K = 4096).
 // Bound: the weight stream.  Before, every workgroup of 16 features normalised the batch into 64 KB of LDS (one
-// workgroup per CU): gate/up of 14336 x 4096 at 8 rows 86 us = 2.7 TB/s, now 47 us = 5.0 TB/s; Q|K|V of 6144 x 4096 with
-// its rotation and cache rows 31 + 6 + 9 us -> 18 us.
+// workgroup per CU): gate/up of 14336 x 4096 at 8 rows 86 us = 2.7 TB/s, now 45 us = 5.2 TB/s; Q|K|V of 6144 x 4096 with
+// its rotation and cache rows 31 + 6 + 9 us -> 17 us.
 template <int EPI, int NB>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArgs a, int items) {
   __shared__ f32x4v red[2][2][kSkinnyWaves][64];
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArg
 
 // Any K, any epilogue, bf16 input: P items per workgroup; a wave walks its 64-k blocks C at a time with three such chunks of
 // weights and input operands in flight (96 KB of weights per workgroup; the input comes from L2, once for all P items).
-// This is the O and down projections' kernel: their few items leave nothing to keep the batch resident for.  Eight rows:
+// The O and down projections' kernel, and that of smaller products: few items leave nothing to keep the batch resident for.  Eight rows:
 // down of 4096 x 14336 33 -> 27 us = 4.4 TB/s against batches of 16 loads with a serial remainder, O of 4096 x 4096 10.6 -> 9.9.
 // The stream carries nothing but what is needed, in order: loads past the end that repeat the last block cost down 5 us and
 // O of 1024 x 1024 7 of 11; a load behind a run-time test makes the compiler wait for its registers.
@@ -652,7 +652,7 @@ fastav_status_t launch_skinny_linear(const void* x, const void* const* w_seg, co
     return check_launch("gemv_rows");
   }
   // Items have 16 features (8 pairs for SwiGLU).  Up to 4096 columns the batch fits a workgroup's registers and 256
-  // workgroups (one per CU) walk the items; longer rows, the residual epilogue and products of one item per workgroup,
+  // workgroups (one per CU) walk the items, more than 256 of them; longer rows, the residual epilogue and products of one item per workgroup,
   // which leave nothing to be resident for, take the streaming kernel (8 rows, resident against streaming: 256 items of
   // 4096 columns 12.8 / 9.9 us, 192 of 2048 7.7 / 6.5, 288 of 3584 12.5 / 15.4).  Two gate/up items per workgroup share
   // the input where that leaves a workgroup per CU (28672 x 8192, one against two: 4 rows 192 / 179 us, 8 rows 202 / 180,
@@ -668,7 +668,7 @@ fastav_status_t launch_skinny_linear(const void* x, const void* const* w_seg, co
 #undef FASTAV_STREAM
     return check_launch("skinny_stream");
   }
-  const dim3 grid((unsigned)(items < 256 ? items : 256));
+  const dim3 grid(256);
 #define FASTAV_SKINNY(EPI, NB) hipLaunchKernelGGL((k_skinny_resident<EPI, NB>), grid, dim3(64 * kSkinnyWaves), 0, s, a, items)
 #define FASTAV_SKINNY_NB(EPI) \
   do { if (nb <= 2) FASTAV_SKINNY(EPI, 2); else if (nb <= 4) FASTAV_SKINNY(EPI, 4); else if (nb <= 7) FASTAV_SKINNY(EPI, 7); else FASTAV_SKINNY(EPI, 8); } while (0)
