@@ -77,9 +77,10 @@ __device__ __forceinline__ bf16_t* skinny_append_row(const SkinnyArgs& a, int b,
 // partial sums meet in LDS in wave order.
 constexpr int kSkinnyWaves = 8;
 
+template <bool PLAIN>
 __device__ __forceinline__ void skinny_item(const SkinnyArgs& a, int epi, int item, int& n0, int& dn) {
   if (epi == FASTAV_EPI_SWIGLU) { n0 = item * 8; dn = 0; return; }
-  if (a.rope_rows > 0) {
+  if (!PLAIN && a.rope_rows > 0) {
     const int per_head = a.dh / 16;
     n0 = (item / per_head) * a.dh + (item % per_head) * 8;
     dn = a.dh / 2;
@@ -89,26 +90,33 @@ __device__ __forceinline__ void skinny_item(const SkinnyArgs& a, int epi, int it
   }
 }
 
-// First weight elements of the item's two groups (both lie in one segment).
-template <int EPI>
+// First weight elements of the item's two groups (both lie in one segment).  The segments' pointers are made values before
+// one is chosen: left to the compiler the chosen one is loaded behind the comparisons, those behind the choice of rotated
+// heads, and the first weight load waits for three trips to the constant cache (8 rows, 1024 x 1024 4.19 -> 3.95 us, 4096 x
+// 4096 9.4 -> 9.1).  PLAIN: no segment has rotated heads.
+template <int EPI, bool PLAIN = false>
 __device__ __forceinline__ void skinny_rows(const SkinnyArgs& a, int item, const bf16_t*& p0, const bf16_t*& p1) {
+  const bf16_t *w0 = a.w[0], *w1 = EPI == FASTAV_EPI_SWIGLU ? a.w2 : a.w[1], *w2 = a.w[2];
+  int end0 = a.seg_end[0], end1 = a.seg_end[1];
+  asm volatile("" : "+s"(w0), "+s"(w1) : "s"(a.x), "s"(a.y), "s"(a.B), "s"(a.K));
+  if (EPI != FASTAV_EPI_SWIGLU) asm volatile("" : "+s"(w2), "+s"(end0), "+s"(end1) : "s"(a.rope_rows), "s"(a.dh));
   int n0, dn;
-  skinny_item(a, EPI, item, n0, dn);
-  const bf16_t* wbase = a.w[0];
+  skinny_item<PLAIN>(a, EPI, item, n0, dn);
   int seg0 = 0;
+  p0 = w0;
   if (EPI != FASTAV_EPI_SWIGLU) {
-    if (n0 >= a.seg_end[0]) { wbase = a.w[1]; seg0 = a.seg_end[0]; }
-    if (n0 >= a.seg_end[1]) { wbase = a.w[2]; seg0 = a.seg_end[1]; }
+    if (n0 >= end0) { p0 = w1; seg0 = end0; }
+    if (n0 >= end1) { p0 = w2; seg0 = end1; }
   }
-  p0 = wbase + (int64_t)(n0 - seg0) * a.K;
-  p1 = EPI == FASTAV_EPI_SWIGLU ? a.w2 + (int64_t)n0 * a.K : p0 + (int64_t)dn * a.K;
+  p0 += (int64_t)(n0 - seg0) * a.K;
+  p1 = EPI == FASTAV_EPI_SWIGLU ? w1 + (int64_t)n0 * a.K : p0 + (int64_t)dn * a.K;
 }
 
 // The sums of one item: v0, v1 = features n + f4 .. + 3 of the two groups, batch row b (lanes 0-31; the others hold copies).
-template <int EPI>
+template <int EPI, bool PLAIN = false>
 __device__ __forceinline__ void skinny_finish(const SkinnyArgs& a, int item, int lane, f32x4v v0, f32x4v v1, f32x4v y0, f32x4v y1) {
   int n0, dn;
-  skinny_item(a, EPI, item, n0, dn);
+  skinny_item<PLAIN>(a, EPI, item, n0, dn);
   const int b = lane & 15, f4 = ((lane >> 4) & 1) * 4;
   if (lane >= 32 || b >= a.B) return;
   const int n = n0 + f4;
@@ -118,7 +126,7 @@ __device__ __forceinline__ void skinny_finish(const SkinnyArgs& a, int item, int
     y1 = y1 + v1;
     *(f32x4v*)y = y0;
     *(f32x4v*)(y + dn) = y1;
-    if (a.xg_out == nullptr) return;
+    if (PLAIN || a.xg_out == nullptr) return;
     const bf16x4_t g0 = *(const bf16x4_t*)(a.g_out + n), g1 = *(const bf16x4_t*)(a.g_out + n + dn);
     bf16x4_t o0, o1;
     float ss = 0.f;
@@ -142,7 +150,7 @@ __device__ __forceinline__ void skinny_finish(const SkinnyArgs& a, int item, int
     *(bf16x4_t*)y = o0;
     return;
   }
-  if (n0 < a.rope_rows) {
+  if (!PLAIN && n0 < a.rope_rows) {
     const f32x4v* t = (const f32x4v*)(a.rope_tab + b * (a.dh / 2) + n0 % a.dh + f4);
     const f32x4v t0 = t[0], t1 = t[1];
     const float cs[4] = {t0[0], t0[2], t1[0], t1[2]}, sn[4] = {t0[1], t0[3], t1[1], t1[3]};
@@ -157,6 +165,7 @@ __device__ __forceinline__ void skinny_finish(const SkinnyArgs& a, int item, int
   for (int r = 0; r < 4; ++r) { o0[r] = (bf16_t)v0[r]; o1[r] = (bf16_t)v1[r]; }
   *(bf16x4_t*)y = o0;
   *(bf16x4_t*)(y + dn) = o1;
+  if (PLAIN) return;
   if (bf16_t* p = skinny_append_row(a, b, n)) {              // both groups lie in one segment
     *(bf16x4_t*)p = o0;
     *(bf16x4_t*)(p + dn) = o1;
@@ -176,13 +185,36 @@ __device__ __forceinline__ T skinny_load(__amdgpu_buffer_rsrc_t r, uint32_t lane
 }
 
 // Sum of the waves' partials of one group, in wave order: lanes 0-31 add the first halves, 32-63 the second.
+__device__ __forceinline__ f32x4v skinny_halves(f32x4v s) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) s[r] += __shfl_xor(s[r], 32, kWave);
+  return s;
+}
 __device__ __forceinline__ f32x4v skinny_sum(const f32x4v (*red)[64], int lane) {
   f32x4v s = red[0][lane];
 #pragma unroll
   for (int w = 1; w < kSkinnyWaves; ++w) s = s + red[w][lane];
+  return skinny_halves(s);
+}
+// Two groups, all reads asked for before the first addition: where a workgroup ends with its sum, two or three reads in
+// flight make that a chain of LDS latencies (8 rows, 512 x 512 2.99 -> 2.89 us, 4096 x 4096 9.12 -> 9.02).
+__device__ __forceinline__ void skinny_last_sums(const f32x4v (*red)[kSkinnyWaves][64], int lane, f32x4v& v0, f32x4v& v1) {
+  f32x4v p[2][kSkinnyWaves];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) s[r] += __shfl_xor(s[r], 32, kWave);
-  return s;
+  for (int w = 0; w < kSkinnyWaves; ++w) {
+    p[0][w] = red[0][w][lane];
+    p[1][w] = red[1][w][lane];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  v0 = p[0][0];
+  v1 = p[1][0];
+#pragma unroll
+  for (int w = 1; w < kSkinnyWaves; ++w) {
+    v0 = v0 + p[0][w];
+    v1 = v1 + p[1][w];
+  }
+  v0 = skinny_halves(v0);
+  v1 = skinny_halves(v1);
 }
 
 // 1 / rms of every row from the sums of squares ss_in, into rs[16]; the caller's next barrier publishes it.  Thread =
@@ -200,10 +232,14 @@ __device__ __forceinline__ void skinny_rms_part(const SkinnyArgs& a, int tid, fl
   }
   part[q][b] = t;
 }
+template <bool AHEAD>
 __device__ __forceinline__ float skinny_rms(const SkinnyArgs& a, int b, const float (*part)[16]) {
-  float t = 0.f;
+  float p[4 * kSkinnyWaves], t = 0.f;
 #pragma unroll
-  for (int q = 0; q < 4 * kSkinnyWaves; ++q) t += part[q][b];
+  for (int q = 0; q < 4 * kSkinnyWaves; ++q) p[q] = part[q][b];
+  if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 4 * kSkinnyWaves; ++q) t += p[q];
   return 1.0f / sqrtf(t / (float)a.K + a.eps);
 }
 
@@ -268,7 +304,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArg
     if (wave == (n_done & (kSkinnyWaves - 1))) {
       f32x4v v0 = skinny_sum(red[buf][0], lane), v1 = skinny_sum(red[buf][1], lane);
       if (a.ss_in != nullptr) {
-        const float r = skinny_rms(a, lane & 15, ss);
+        const float r = skinny_rms<false>(a, lane & 15, ss);
         v0 = v0 * r;
         v1 = v1 * r;
       }
@@ -301,7 +337,9 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArg
 // down of 4096 x 14336 33 -> 27 us = 4.4 TB/s against batches of 16 loads with a serial remainder, O of 4096 x 4096 10.6 -> 9.9.
 // The stream carries nothing but what is needed, in order: loads past the end that repeat the last block cost down 5 us and
 // O of 1024 x 1024 7 of 11; a load behind a run-time test makes the compiler wait for its registers.
-template <int EPI, int P>
+// BRIEF: K <= 2048 and nothing folded in.  Such a product ends in 2-6 us, and code that is only jumped over and blocks that
+// are only requested to read as zero show: 8 rows of 512 x 512 2.89 -> 2.61 us, of 768 x 1152 3.58 -> 3.44.
+template <int EPI, int P, bool BRIEF>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs a) {
   constexpr int C = 2 / P, NG = 2 * P;                        // blocks per chunk, groups of 8 weight rows
   __shared__ f32x4v red[NG][kSkinnyWaves][64];
@@ -316,7 +354,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs 
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const bf16_t *p0, *p1;
-    skinny_rows<EPI>(a, item0 + p, p0, p1);
+    skinny_rows<EPI, BRIEF>(a, item0 + p, p0, p1);
     r[2 * p] = skinny_rsrc(p0, 16u * (uint32_t)a.K);
     r[2 * p + 1] = skinny_rsrc(p1, 16u * (uint32_t)a.K);
   }
@@ -330,11 +368,11 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs 
   }
   // as 32-bit words: vectors of 16-bit elements that meet behind a branch are rebuilt from halves, which waits for them
   u32x4v w0[NG][C], w1[NG][C], w2[NG][C], x0[C][2], x1[C][2], x2[C][2];
-  // Blocks past the end exist in the last chunk only: their lane offset lies outside every resource, so they read as zero
-  // and touch no memory.
-  auto load = [&](u32x4v (&w)[NG][C], u32x4v (&x)[C][2], int ch, bool last) __attribute__((always_inline)) {
+  // n of a chunk's blocks, a number known at compile time.  Blocks past the end exist in the last chunk only: their lane
+  // offset lies outside every resource, so they read as zero and touch no memory.
+  auto load = [&](u32x4v (&w)[NG][C], u32x4v (&x)[C][2], int ch, bool last, int n = 2 / P) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < C; ++u) {
+    for (int u = 0; u < C && u < n; ++u) {
       const int blk = wave + kSkinnyWaves * (ch * C + u);
       const bool in = !last || blk < kb;
       const uint32_t off = in ? (uint32_t)blk * 128u : 0u, wl = in ? woff : kSkinnyOutside, xl = in ? xoff : kSkinnyOutside;
@@ -348,9 +386,9 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs 
   f32x4v acc[NG][2];                                          // [group][half]
 #pragma unroll
   for (int g = 0; g < NG; ++g) acc[g][0] = acc[g][1] = f32x4v{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](u32x4v (&w)[NG][C], u32x4v (&x)[C][2]) __attribute__((always_inline)) {
+  auto compute = [&](u32x4v (&w)[NG][C], u32x4v (&x)[C][2], int n = 2 / P) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < C; ++u)
+    for (int u = 0; u < C && u < n; ++u)
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         const bf16x8_t wv = __builtin_bit_cast(bf16x8_t, w[g][u]);
@@ -361,8 +399,8 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs 
   };
   // every end of the walk has a body of its own: a load behind a run-time test inside the stream costs it its depth
   const int nch = (kb + kSkinnyWaves * C - 1) / (kSkinnyWaves * C);
-  const bool scaled = EPI != FASTAV_EPI_RESADD && a.ss_in != nullptr;
-  if (nch >= 3) {
+  const bool scaled = !BRIEF && EPI != FASTAV_EPI_RESADD && a.ss_in != nullptr;
+  if (!BRIEF && nch >= 3) {
     load(w0, x0, 0, false);
     load(w1, x1, 1, false);
     load(w2, x2, 2, true);
@@ -395,6 +433,9 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs 
       compute(w0, x0);
       compute(w1, x1);
     }
+  } else if (BRIEF && kb <= kSkinnyWaves) {
+    load(w0, x0, 0, true, 1);
+    compute(w0, x0, 1);
   } else if (nch == 2) {
     load(w0, x0, 0, false);
     load(w1, x1, 1, true);
@@ -415,13 +456,14 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_stream(SkinnyArgs 
   }
   lds_barrier();
   if (wave >= P) return;                                      // wave p finishes item p
-  f32x4v v0 = skinny_sum(red[2 * wave], lane), v1 = skinny_sum(red[2 * wave + 1], lane);
+  f32x4v v0, v1;
+  skinny_last_sums(red + 2 * wave, lane, v0, v1);
   if (scaled) {
-    const float f = skinny_rms(a, lane & 15, ss);
+    const float f = skinny_rms<true>(a, lane & 15, ss);
     v0 = v0 * f;
     v1 = v1 * f;
   }
-  skinny_finish<EPI>(a, item0 + wave, lane, v0, v1, y0, y1);
+  skinny_finish<EPI, BRIEF>(a, item0 + wave, lane, v0, v1, y0, y1);
 }
 
 // ---------------------------------------------------------------------------------------- one-row GEMV
@@ -660,11 +702,13 @@ fastav_status_t launch_skinny_linear(const void* x, const void* const* w_seg, co
   const int items = epilogue == FASTAV_EPI_SWIGLU ? n / 8 : n / 16;
   const int nb = (k / 64 + kSkinnyWaves - 1) / kSkinnyWaves;
   if (epilogue == FASTAV_EPI_RESADD || nb > 8 || items <= 256) {
-#define FASTAV_STREAM(EPI, P) hipLaunchKernelGGL((k_skinny_stream<EPI, P>), dim3((unsigned)(items / P)), dim3(64 * kSkinnyWaves), 0, s, a)
-    if (epilogue == FASTAV_EPI_RESADD) FASTAV_STREAM(FASTAV_EPI_RESADD, 1);
-    else if (epilogue == FASTAV_EPI_STORE) FASTAV_STREAM(FASTAV_EPI_STORE, 1);
-    else if (B > 4 && items >= 512) FASTAV_STREAM(FASTAV_EPI_SWIGLU, 2);       // n is a multiple of 16: items are even
-    else FASTAV_STREAM(FASTAV_EPI_SWIGLU, 1);
+    const bool brief = k <= 64 * kSkinnyWaves * 4 && !ss_in && !rope && !app && !next;
+#define FASTAV_STREAM(EPI, P, BRIEF) hipLaunchKernelGGL((k_skinny_stream<EPI, P, BRIEF>), dim3((unsigned)(items / P)), dim3(64 * kSkinnyWaves), 0, s, a)
+    if (epilogue == FASTAV_EPI_RESADD) { if (brief) FASTAV_STREAM(FASTAV_EPI_RESADD, 1, true); else FASTAV_STREAM(FASTAV_EPI_RESADD, 1, false); }
+    else if (epilogue == FASTAV_EPI_STORE) { if (brief) FASTAV_STREAM(FASTAV_EPI_STORE, 1, true); else FASTAV_STREAM(FASTAV_EPI_STORE, 1, false); }
+    else if (B > 4 && items >= 512) FASTAV_STREAM(FASTAV_EPI_SWIGLU, 2, false);       // n is a multiple of 16: items are even
+    else if (brief) FASTAV_STREAM(FASTAV_EPI_SWIGLU, 1, true);
+    else FASTAV_STREAM(FASTAV_EPI_SWIGLU, 1, false);
 #undef FASTAV_STREAM
     return check_launch("skinny_stream");
   }

@@ -55,10 +55,10 @@ def test_decode_linear_ragged_blocks(B, N, K, epi):
 
 
 @pytest.mark.parametrize("epi", [fa.EPI_STORE, fa.EPI_RESADD, fa.EPI_SWIGLU])
-@pytest.mark.parametrize("B,N,K", [(2, 32, 1024), (3, 48, 1088), (16, 64, 2048), (7, 32, 2112), (2, 4096, 3072), (9, 64, 5312),
+@pytest.mark.parametrize("B,N,K", [(2, 32, 512), (5, 48, 576), (2, 32, 1024), (3, 48, 1088), (16, 64, 2048), (7, 32, 2112), (2, 4096, 3072), (9, 64, 5312),
                                    (4, 4096, 4224), (5, 4096, 4224), (16, 4112, 6272), (6, 4128, 4608), (13, 48, 16512)])
 def test_decode_linear_ends_of_the_streamed_rows(B, N, K, epi):
-    """The streaming kernel's ends: 1, 2, 3, ... whole or partial chunks of 16 blocks of 64 columns (two gate/up items per
+    """The streaming kernel's ends: half of one, 1, 2, 3, ... whole or partial chunks of 16 blocks of 64 columns (two gate/up items per
     workgroup from five rows and 4096 features on: chunks of 8), 256 items (the last size that streams up to 4096 columns)."""
     got, want = _skinny_case(B, N, K, epi, B + N + K + epi)
     assert_close(got, want, "bf16", what=f"skinny linear {B}x{N}x{K} epi {epi}")
