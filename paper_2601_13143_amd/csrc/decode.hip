@@ -247,8 +247,8 @@ __device__ __forceinline__ float skinny_rms(const SkinnyArgs& a, int b, const fl
 // (NB 64-k blocks per wave, read once) and walks the items blockIdx, + gridDim, ... with two items' weights in flight
 // (128 KB each for K = 4096).
 // Bound: the weight stream.  Before, every workgroup of 16 features normalised the batch into 64 KB of LDS (one
-// workgroup per CU): gate/up of 14336 x 4096 at 8 rows 86 us = 2.7 TB/s, now 45 us = 5.2 TB/s; Q|K|V of 6144 x 4096 with
-// its rotation and cache rows 31 + 6 + 9 us -> 17 us.
+// workgroup per CU): gate/up of 14336 x 4096 at 8 rows 86 us = 2.7 TB/s, now 44 us = 5.3 TB/s; Q|K|V of 6144 x 4096 with
+// its rotation and cache rows 31 + 6 + 9 us -> 16 us.
 template <int EPI, int NB>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArgs a, int items) {
   __shared__ f32x4v red[2][2][kSkinnyWaves][64];
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_skinny_resident(SkinnyArg
 // Any K, any epilogue, bf16 input: P items per workgroup; a wave walks its 64-k blocks C at a time with three such chunks of
 // weights and input operands in flight (96 KB of weights per workgroup; the input comes from L2, once for all P items).
 // The O and down projections' kernel, and that of smaller products: few items leave nothing to keep the batch resident for.  Eight rows:
-// down of 4096 x 14336 33 -> 27 us = 4.4 TB/s against batches of 16 loads with a serial remainder, O of 4096 x 4096 10.6 -> 9.9.
+// down of 4096 x 14336 33 -> 27 us = 4.4 TB/s against batches of 16 loads with a serial remainder, O of 4096 x 4096 10.2 -> 9.0.
 // The stream carries nothing but what is needed, in order: loads past the end that repeat the last block cost down 5 us and
 // O of 1024 x 1024 7 of 11; a load behind a run-time test makes the compiler wait for its registers.
 // BRIEF: K <= 2048 and nothing folded in.  Such a product ends in 2-6 us, and code that is only jumped over and blocks that
