@@ -1,7 +1,8 @@
 // Causal grouped-query flash attention for prefill on the CDNA4 matrix cores (bf16 in, fp32 accumulate),
 // with the last-query logits of Eq. 4 as a side output.
 //
-// One workgroup = 128 query rows of one head of one sample; each of its 4 waves owns 32 rows.  K/V tiles
+// One workgroup = 128 query rows of one head of one sample; each of its 4 waves owns 32 rows (or, with the keys
+// split, two waves share a row block: one takes the even key tiles, one the odd ones).  K/V tiles
 // of 64 keys are copied HBM/L2 -> LDS asynchronously (global_load_lds_dwordx4) one tile ahead of the math
 // into one of two LDS stages, both row-major [key][d] and XOR-swizzled so that the operand reads spread over all 64
 // LDS banks (K: 32 keys x one 16-byte chunk per MFMA operand; V: 4 keys x 32 bytes per 16 lanes of the
@@ -17,9 +18,9 @@
 // The lane whose query is the last row of a sample also writes that row's scaled logits for every key
 // and its final (max, sum): the fine-prune score is finalised from those without a second pass over K.
 //
-// A workgroup processes query tiles i and last - i one after the other, which gives every workgroup of a
-// sample the same number of key tiles.  Workgroup ids are re-dealt so that the query heads that share a KV
-// head run on one XCD and share its L2.
+// Three forms, chosen by the launcher (AttnForm): a query tile per workgroup, the longest first; tiles i and last - i by
+// one workgroup; a query tile per workgroup of eight waves with the keys split over two groups of four.  Workgroup ids
+// are re-dealt so that the query heads that share a KV head run on one XCD and share its L2.
 #include "common.hpp"
 
 namespace fastav {
@@ -35,6 +36,7 @@ struct AttnArgs {
 };
 
 typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
+typedef f32x4_t f32x4_dword_t __attribute__((aligned(4)));   // a 16-byte store at a 4-byte address
 
 // Asynchronous 16-byte global -> LDS copies (no VGPR staging, no ds_write); lane l's data lands at
 // lds_byte_addr + 16 l.  Completion is tracked by vmcnt.  First form: per-lane 64-bit address.  Second form:
@@ -56,8 +58,8 @@ __device__ __forceinline__ void attn_dma16_sbase(const void* base, uint32_t voff
 // can: one fma + one exp2 per logit, one packed conversion and one packed dot product (the row sum) per two,
 // one three-way max per two, and a rescale of the accumulators only when a row's max has moved by more than
 // 2^8 since the last rescale (probabilities then stay below 256, exact in fp32 and harmless in bf16).
-template <int DH>
-__global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
+template <int DH, int KG, bool PAIRED, bool EMIT>
+__global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
   constexpr int BQ = 128, BKV = 64;
   constexpr int DCH = DH / 8;                       // 16-byte chunks per row
   constexpr int NS = DH / 16;                       // MFMA k-steps over the head dimension
@@ -69,13 +71,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
   //      eight pieces fall in eight distinct 32-byte slots.
   auto kswz = [](int key, int c) { return DH == 128 ? (c ^ (key & 15)) : (c ^ ((key >> 1) & 7)); };
   auto vswz = [](int key, int c) { return DH == 128 ? (c ^ ((key & 3) << 2)) : (c ^ ((key & 2) << 1)); };
-  extern __shared__ bf16x8_t attn_lds[];            // K stages then V stages: [2][BKV*DCH] each
+  extern __shared__ bf16x8_t attn_lds[];            // K stages then V stages: [2][KG][BKV*DCH] each
   constexpr int TILE = BKV * DCH;                   // 16-byte chunks per tile
+  constexpr int STAGE = KG * TILE;
 
-  // Work item = one (sample, head) pair x one PAIR of query tiles (i, last - i): under the causal mask tile i
-  // sees i + 1 tiles' worth of keys, so every item of a sample carries the same amount of work and a launch
-  // has no long tail.  When the KV groups divide evenly over the 8 XCDs (block id % 8 is the XCD), the query
-  // heads of one KV head are placed on one XCD and share its L2.
+  // Work item = one (sample, head) pair x one query tile, or a pair of them (i, last - i).  When the KV groups divide
+  // evenly over the 8 XCDs (block id % 8 is the XCD), the query heads of one KV head are placed on one XCD and share its L2.
   const int v = blockIdx.x;
   int pair, item;
   const int G = a.Hq / a.Hkv, n_groups = a.n_pairs / G;
@@ -95,10 +96,11 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
   const int row0 = __builtin_amdgcn_readfirstlane(a.cu[b]);      // wave-uniform by construction: keep them in SGPRs
   const int n = __builtin_amdgcn_readfirstlane(a.cu[b + 1]) - row0;
   const int nq = (n + BQ - 1) / BQ;                               // this sample's query tiles
-  if (item >= (nq + 1) / 2) return;
+  if (PAIRED ? item >= (nq + 1) / 2 : a.n_qtiles - 1 - item >= nq) return;
   const int g = h / G;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, so control flow stays scalar
+  const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, so control flow stays scalar
+  const int wave = wave_wg & 3, grp = wave_wg >> 2;               // 32-row block of the query tile, key group
   const int l32 = lane & 31, hf = lane >> 5;
   // first K / V row of this sample and KV head; rows are then addressed with 32-bit byte offsets (the
   // launcher checks that a sample's K/V rows span less than 2 GB)
@@ -113,8 +115,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
   // swizzles only look at key bits that the group index does not touch.
   constexpr int RPI = 64 / DCH;                      // rows per copy instruction
   constexpr int NCP = BKV / RPI / 4;                 // copy instructions per wave, per tile, for K and for V each
-  const uint32_t k_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)attn_lds;
-  const uint32_t v_lds = k_lds + 2u * TILE * 16u;
+  const uint32_t k_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)attn_lds + (uint32_t)(grp * TILE) * 16u;
+  const uint32_t v_lds = k_lds + 2u * STAGE * 16u;
   const int cp_row = lane / DCH, cp_pos = lane % DCH;
   const uint32_t k_voff = (uint32_t)cp_row * row_bytes + (uint32_t)kswz(wave * RPI + cp_row, cp_pos) * 16u;
   const uint32_t v_voff = (uint32_t)cp_row * row_bytes + (uint32_t)vswz(cp_row, cp_pos) * 16u;
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < NCP; ++i) {
       const int r0 = (i * 4 + wave) * RPI;
-      const uint32_t dst = (uint32_t)(st * TILE + r0 * DCH) * 16u;
+      const uint32_t dst = (uint32_t)(st * STAGE + r0 * DCH) * 16u;
       if (t * BKV + BKV <= n) {
         const uint32_t off = (uint32_t)(t * BKV + r0) * row_bytes;
         attn_dma16_sbase(kbase + off, k_voff, k_lds + dst);
@@ -137,7 +139,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
       }
     }
   };
-  auto fetch_wait = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); };
+  // vmcnt(0) through the builtin, which the compiler's own wait counts take into account: behind an asm wait it went on
+  // waiting for the Q rows inside the tile loop (vmcnt 7 .. 0 between the QK^T products), and with them for the next
+  // tile's copies
+  auto fetch_wait = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); asm volatile("" : : : "memory"); };
 
   // this lane's part of a transposing V read: 16 lanes cover 4 keys x 16 dims (two chunks)
   const int tr_krow = (lane & 15) >> 2;                          // which of the 4 keys this lane addresses
@@ -150,12 +155,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
   // K operand of S^T = K Q^T: the 32 keys of half kb of the tile in stage st, k-step sI over the head dimension
   auto k_frag = [&](int st, int kb, int sI) __attribute__((always_inline)) -> bf16x8_t {
     const int key = kb * 32 + l32;
-    return attn_lds[st * TILE + key * DCH + kswz(key, 2 * sI + hf)];
+    return attn_lds[grp * TILE + st * STAGE + key * DCH + kswz(key, 2 * sI + hf)];
   };
   // V^T operand of O^T += V^T P^T for 16 keys (half kb, quarter sp) and 32 dims (block d):
   // slot e holds key 32kb + 16sp + (e/4)*8 + hf*4 + e%4
   auto v_frag = [&](int st, int kb, int sp, int d) __attribute__((always_inline)) -> bf16x8_t {
-    const bf16_t* vtile = (const bf16_t*)(attn_lds + (2 + st) * TILE);
+    const bf16_t* vtile = (const bf16_t*)(attn_lds + grp * TILE + (2 + st) * STAGE);
     bf16x8_t vf;
 #pragma unroll
     for (int r2 = 0; r2 < 2; ++r2) {
@@ -168,8 +173,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
   };
 
 #pragma nounroll
-  for (int part = 0; part < 2; ++part) {
-  const int qt = part == 0 ? nq - 1 - item : item;                // the long tile first
+  for (int part = 0; part < (PAIRED ? 2 : 1); ++part) {
+  const int qt = !PAIRED ? a.n_qtiles - 1 - item : part == 0 ? nq - 1 - item : item;   // the long tiles first
   if (part == 1 && qt == nq - 1 - item) break;                    // odd count: the middle tile stands alone
   const int q0 = qt * BQ;
   const int qw0 = q0 + 32 * wave;
@@ -188,8 +193,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
   for (int d = 0; d < NDB; ++d) o[d] = zero16;
   // m: running max (log2 domain); m_ref: the value the stored probabilities and sums are relative to
   float m = -INFINITY, m_ref = -INFINITY, l = 0.f;
-  const bool emit = (a.last_logits != nullptr) && (qi == n - 1);
-  const bool emit_wave = __ballot(emit) != 0;                    // wave-uniform: some lane owns the sample's last row
+  const bool emit = EMIT && a.last_logits != nullptr && qi == n - 1;
+  const bool emit_wave = EMIT && __ballot(emit) != 0;                    // wave-uniform: some lane owns the sample's last row
 
   const int kv_end = (q0 + BQ < n) ? q0 + BQ : n;                // keys this workgroup can see
   const int n_tiles = (kv_end + BKV - 1) / BKV;
@@ -226,9 +231,13 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = j0 + kb * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
-          if (emit && key <= qi) a.last_logits[(int64_t)h * a.T + row0 + key] = s[kb][r] * a.scale;
+        for (int r = 0; r < 16; r += 4) {
+          const int key = j0 + kb * 32 + (r >> 2) * 8 + hf * 4;
+          float* lp = a.last_logits + (int64_t)h * a.T + row0 + key;
+          if (emit && key + 3 <= qi) *(f32x4_dword_t*)lp = f32x4_t{s[kb][r], s[kb][r + 1], s[kb][r + 2], s[kb][r + 3]} * a.scale;
+          else
+#pragma unroll
+            for (int e = 0; e < 3; ++e) if (emit && key + e <= qi) lp[e] = s[kb][r + e] * a.scale;
         }
     }
     if ((j0 + BKV - 1 > qw0) || (j0 + BKV > n)) {                 // diagonal or ragged tile: mask (wave-uniform test)
@@ -261,7 +270,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
     m = fmaxf(m, mx * a.scale_log2);
     if (__ballot(m > m_ref + kRescaleStep) != 0) {                 // also taken on the first tile (m_ref = -inf)
       const float m_to = (m > m_ref + kRescaleStep) ? m : m_ref;
-      const float alpha = __builtin_amdgcn_exp2f(m_ref - m_to);    // 1 for the rows that stay
+      const float alpha = KG > 1 && m_to == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_to);   // 1 for the rows that stay
       m_ref = m_to;
       l *= alpha;
 #pragma unroll
@@ -269,14 +278,16 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
     }
+    // a row that has seen nothing but -inf keeps weights of 0 in this group; the other group may hold its finite keys
+    const float ref = KG > 1 && m_ref == -INFINITY ? 0.f : m_ref;
     bf16x8_t pb[2][2];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int r = 0; r < 16; r += 2) {
         bf16x2_t pr;                                               // exp2(-inf) = 0 for masked keys
-        pr[0] = (bf16_t)__builtin_amdgcn_exp2f(fmaf(s[kb][r], a.scale_log2, -m_ref));
-        pr[1] = (bf16_t)__builtin_amdgcn_exp2f(fmaf(s[kb][r + 1], a.scale_log2, -m_ref));
+        pr[0] = (bf16_t)__builtin_amdgcn_exp2f(fmaf(s[kb][r], a.scale_log2, -ref));
+        pr[1] = (bf16_t)__builtin_amdgcn_exp2f(fmaf(s[kb][r + 1], a.scale_log2, -ref));
         l = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, l, false);  // row sum of the rounded probabilities
         pb[kb][r >> 3][r & 7] = pr[0];
         pb[kb][r >> 3][(r & 7) + 1] = pr[1];
@@ -292,19 +303,50 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto tile_step = [&](int t, int st) __attribute__((always_inline)) {
-    if (t + 1 < n_tiles) fetch(t + 1, st ^ 1);                   // stage st^1 was last read before the previous barrier
-    if (t < my_tiles) tile_math(t, st);
+  // Step i: group `grp` works on key tile i * kg + grp.  A sample of one or two query tiles leaves all tiles to group 0, so
+  // that it gives the same bits whichever form the longest sample of its batch asks for.
+  const int kg = KG > 1 && nq >= 3 ? KG : 1;
+  auto tile_step = [&](int i, int st) __attribute__((always_inline)) {
+    const int t = i * kg + grp;
+    if (grp < kg && t + kg < n_tiles) fetch(t + kg, st ^ 1);     // stage st^1 was last read before the previous barrier
+    if (grp < kg && t < my_tiles) tile_math(t, st);
     fetch_wait();
     __syncthreads();
   };
 
-  fetch(0, 0);
+  const int n_steps = (n_tiles + kg - 1) / kg;
+  if (grp < kg && grp < n_tiles) fetch(grp, 0);
   fetch_wait();
   __syncthreads();
-  for (int t = 0; t < n_tiles; t += 2) {
-    tile_step(t, 0);
-    if (t + 1 < n_tiles) tile_step(t + 1, 1);
+  for (int i = 0; i < n_steps; i += 2) {
+    tile_step(i, 0);
+    if (i + 1 < n_steps) tile_step(i + 1, 1);
+  }
+
+  if constexpr (KG == 2) {
+    // group 1 hands its (reference, max, sum, O^T) over through LDS, which is free after the last step's barrier: 4-byte
+    // words [wave][value][lane].  A row of group 1 without any key has m_ref = -inf and a weight of 0; group 0 always
+    // holds key 0.
+    float* xch = (float*)attn_lds + (wave * (16 * NDB + 3)) * 64 + lane;
+    if (grp == 1) {
+      xch[0] = m_ref; xch[64] = m; xch[128] = l;
+#pragma unroll
+      for (int d = 0; d < NDB; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) xch[(3 + 16 * d + r) * 64] = o[d][r];
+    }
+    __syncthreads();
+    if (grp == 1) return;
+    const float ref1 = xch[0], to = fmaxf(m_ref, ref1), l1 = xch[128];
+    m = fmaxf(m, xch[64]);
+    const float safe = to == -INFINITY ? 0.f : to;
+    const float w0 = __builtin_amdgcn_exp2f(m_ref - safe), w1 = __builtin_amdgcn_exp2f(ref1 - safe);
+    m_ref = to;
+    l = l * w0 + l1 * w1;
+#pragma unroll
+    for (int d = 0; d < NDB; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[d][r] = o[d][r] * w0 + xch[(3 + 16 * d + r) * 64] * w1;
   }
 
   // ---- normalise and store.  o[d][r] is (dim 32d + (r/4)*8 + hf*4 + r%4, query qi).
@@ -322,20 +364,64 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(AttnArgs a) {
         for (int e = 0; e < 4; ++e) w[e] = (bf16_t)(o[d][4 * r4 + e] * inv);
         *(bf16x4_t*)(op + d * 32 + r4 * 8) = w;
       }
-    if (emit && hf == 0 && a.last_ml) {
+    if (emit && hf == 0) {
       // (max, sum of exp relative to the max), back from the log2 domain
       a.last_ml[((int64_t)b * a.Hq + h) * 2] = m * 0.6931471805599453f;
       a.last_ml[((int64_t)b * a.Hq + h) * 2 + 1] = l_tot * __builtin_amdgcn_exp2f(m_ref - m);
     }
   }
-  __syncthreads();                                               // the next part's first copy reuses stage 0
+  if constexpr (PAIRED) __syncthreads();                        // the next part's first copy reuses stage 0
   }  // part
+}
+
+// Which workgroups a launch is cut into.  Under the causal mask query tile i sees i + 1 tiles' worth of keys.
+//   kAttnTiles   a workgroup per query tile, the longest tiles of the launch first: a CU that is done takes the next one.
+//   kAttnPaired  a workgroup per pair (i, last - i), all of equal work: nothing to balance, but a launch is whole rounds of
+//                two workgroups per CU, and one of 320 pairs ends with 192 CUs half empty.
+//   kAttnSplit   kAttnTiles with eight waves: two groups of four waves take the even and the odd key tiles of the same
+//                rows and group 0 merges them through LDS.  One workgroup per CU, but two waves per SIMD (a wave alone
+//                needs 1.5 us a key tile, two sharing a SIMD about 2.1 for a tile each) and half the chain.
+// Microseconds (32 / 8 heads of 128, one sample; before = pairs always):
+//   tokens      166   331  1024  1205  2048  2248  2458  3072  4096  5000  9000  16384
+//   before     14.5  19.3  34.2  37.9  53.4  70.4  77.8  96.3 139.7   262   719   1959
+//   tiles       8.6  12.3  25.9  28.9  50.6  56.3  61.9  86.3 147.7   208   623   1964
+//   pairs      13.9  18.6  32.1  35.8  50.4  73.9  81.3   100 139.7   248   695   2015
+//   split       9.6  11.6  23.1  24.8  46.0  60.9  70.4  94.3 151.8   226   654   2074
+// The split form wins while its workgroups find a CU each (256), and beyond that as long as the items are long against
+// their start and merge (ten tiles or more) and there are no more than two for a CU; heads of 64 cost half as much per
+// key, so the line lies at twice that.  Three prompts of 331 (288 items): split 19.5, tiles 14.4; two of 1024 (512 items)
+// 33.2 against 31.4.  Pairs win where they fill one round of 512 (4096 tokens, 32 heads; 4600 tokens, 28 heads 156 against 163).
+enum AttnForm { kAttnTiles, kAttnPaired, kAttnSplit };
+static AttnForm attn_form(int n_qtiles, int n_pairs, int dh, bool emit, bool even) {
+  const int64_t items = (int64_t)n_qtiles * n_pairs, pairs = (int64_t)((n_qtiles + 1) / 2) * n_pairs;
+  if (n_qtiles >= 3 && (items <= 256 || (n_qtiles >= 10 && items <= (dh == 64 ? 1024 : 512)))) return kAttnSplit;
+  return !emit && even && pairs >= 480 && pairs <= 512 ? kAttnPaired : kAttnTiles;
 }
 
 bool mfma_attention_supported(int dh, int dtype, int64_t q_stride, int64_t kv_stride, int64_t o_stride, int max_seqlen) {
   // the tile copies address a sample's K / V rows with 32-bit byte offsets
   return dtype == FASTAV_BF16 && (dh == 64 || dh == 128) && q_stride % 8 == 0 && kv_stride % 8 == 0 && o_stride % 4 == 0 &&
          ((int64_t)max_seqlen + 64) * kv_stride * 2 < ((int64_t)1 << 31);
+}
+
+template <int DH, int KG, bool PAIRED, bool EMIT>
+static fastav_status_t launch_attn(const AttnArgs& a, int64_t blocks, hipStream_t s) {
+  constexpr int shmem = 4 * KG * 64 * DH * 2;                     // two stages of KG 64-key K tiles and V tiles
+  if constexpr (shmem > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)k_attn_mfma<DH, KG, PAIRED, EMIT>, hipFuncAttributeMaxDynamicSharedMemorySize, shmem);
+    if (e != hipSuccess) return fail(FASTAV_EHIP, "attention: hipFuncSetAttribute: %s", hipGetErrorString(e));
+  }
+  hipLaunchKernelGGL((k_attn_mfma<DH, KG, PAIRED, EMIT>), dim3((unsigned)blocks), dim3(256 * KG), shmem, s, a);
+  return check_launch("attention_mfma");
+}
+template <int DH>
+static fastav_status_t launch_attn(const AttnArgs& a, AttnForm form, int64_t blocks, hipStream_t s) {
+  const bool emit = a.last_logits != nullptr;
+  // pairs come without the side output, but in the build that has its branch: that one keeps the tile loop's schedule
+  // (4096 tokens 139.7 us, 142.0 without the branch)
+  if (form == kAttnPaired) return launch_attn<DH, 1, true, true>(a, blocks, s);
+  if (form == kAttnSplit) return emit ? launch_attn<DH, 2, false, true>(a, blocks, s) : launch_attn<DH, 2, false, false>(a, blocks, s);
+  return emit ? launch_attn<DH, 1, false, true>(a, blocks, s) : launch_attn<DH, 1, false, false>(a, blocks, s);
 }
 
 fastav_status_t launch_attention_mfma(const void* q, int64_t q_stride, const void* k, const void* v,
@@ -350,15 +436,14 @@ fastav_status_t launch_attention_mfma(const void* q, int64_t q_stride, const voi
   a.qs = q_stride; a.kvs = kv_stride; a.os = o_stride; a.cu = cu; a.Hq = Hq; a.Hkv = Hkv;
   a.n_qtiles = (max_seqlen + 127) / 128;
   a.n_pairs = Hq * batch;
-  const int64_t blocks = (int64_t)((a.n_qtiles + 1) / 2) * a.n_pairs;       // balanced pairs of query tiles
+  // even: the samples' lengths lie within a sixteenth of the longest on average
+  const AttnForm form = attn_form(a.n_qtiles, a.n_pairs, dh, last_logits != nullptr, 16 * T >= (int64_t)15 * batch * max_seqlen);
+  const int64_t blocks = (int64_t)(form == kAttnPaired ? (a.n_qtiles + 1) / 2 : a.n_qtiles) * a.n_pairs;
   if (blocks > 0x7FFFFFFF) return fail(FASTAV_EUNSUPPORTED, "attention: too many workgroups");
   a.scale = 1.0f / sqrtf((float)dh);
   a.scale_log2 = a.scale * 1.4426950408889634f;
   a.T = T; a.last_logits = last_logits; a.last_ml = last_ml;
-  // two stages of a 64-key K tile and V tile
-  if (dh == 128) hipLaunchKernelGGL(k_attn_mfma<128>, dim3((unsigned)blocks), dim3(256), 4 * 64 * 128 * 2, s, a);
-  else hipLaunchKernelGGL(k_attn_mfma<64>, dim3((unsigned)blocks), dim3(256), 4 * 64 * 64 * 2, s, a);
-  return check_launch("attention_mfma");
+  return dh == 128 ? launch_attn<128>(a, form, blocks, s) : launch_attn<64>(a, form, blocks, s);
 }
 
 }  // namespace fastav
