@@ -60,7 +60,7 @@ bool mfma_attention_supported(int dh, int dtype, int64_t q_stride, int64_t kv_st
 fastav_status_t launch_attention_mfma(const void* q, int64_t q_stride, const void* k, const void* v,
                                       int64_t kv_stride, void* o, int64_t o_stride, const int32_t* cu, int batch,
                                       int64_t T, int max_seqlen, int Hq, int Hkv, int dh, float* last_logits,
-                                      float* last_ml, hipStream_t s);
+                                      float* last_ml, float2* row_stats, hipStream_t s);
 
 bool skinny_linear_supported(int64_t m, int n, int k, int dtype, int64_t ldy);
 bool skinny_norm_supported(int B, int k);
@@ -79,13 +79,13 @@ fastav_status_t launch_decode_attention(const void* q, const void* k_self, const
 
 size_t attention_map_stats_bytes(int n, int Hq);
 fastav_status_t launch_attention_map(const void* q, int64_t q_stride, const void* k, int64_t k_stride, int n, int Hq,
-                                     int Hkv, int dh, float* stats, void* a_out, hipStream_t s);
+                                     int Hkv, int dh, float2* stats, bool have_stats, void* a_out, int64_t ld, bool lower, hipStream_t s);
 fastav_status_t launch_iota(int32_t* p, int n, hipStream_t s);
 fastav_status_t launch_rollout_init(float* rt, void* rt16, int n, hipStream_t s);
 fastav_status_t launch_rollout_cutoff(const float* rt, int n, const uint8_t* prot, float threshold, float* influence,
                                       int32_t* cutoff, hipStream_t s);
-fastav_status_t launch_rollout_step(float* rt, void* rt16, const void* a16, float* c, int n, float alpha,
-                                    void* linear_ws, size_t linear_ws_bytes, hipStream_t s);
+int64_t rollout_pitch(int64_t n);
+fastav_status_t launch_rollout_step(float* rt, const void* rt16, const void* a16, void* rt16_next, int n, float alpha, hipStream_t s);
 
 // The kernel that a product's sizes ask for; the decode kernels also want packed rows in and out (few_ok).
 static fastav_linear_kernel_t linear_kernel(int64_t m, const int* seg_rows, int n_seg, int k, int epilogue, int dtype, int64_t ldc, bool few_ok) {
@@ -159,11 +159,11 @@ fastav_status_t launch_linear(const void* a, const void* w, const void* w2, void
 fastav_status_t launch_attention(const void* q, int64_t q_stride, const void* k, const void* v, int64_t kv_stride,
                                  void* o, int64_t o_stride, const int32_t* cu, int batch, int64_t T, int max_seqlen,
                                  int Hq, int Hkv, int dh, float* last_logits, float* last_ml, int dtype,
-                                 double flops_hint, hipStream_t s) {
+                                 double flops_hint, hipStream_t s, float2* row_stats) {
   ProfScope prof(FASTAV_PROF_ATTENTION, flops_hint, s);
   if (mfma_attention_supported(dh, dtype, q_stride, kv_stride, o_stride, max_seqlen))
     return launch_attention_mfma(q, q_stride, k, v, kv_stride, o, o_stride, cu, batch, T, max_seqlen, Hq, Hkv, dh,
-                                 last_logits, last_ml, s);
+                                 last_logits, last_ml, row_stats, s);
   if (dtype == FASTAV_F32 && f32_attention_supported(q, q_stride, k, v, kv_stride, o, o_stride, batch, Hq, dh))
     return launch_attention_f32(q, q_stride, k, v, kv_stride, o, o_stride, cu, batch, T, max_seqlen, Hq, Hkv, dh, last_logits,
                                 last_ml, s);
@@ -953,10 +953,10 @@ fastav_status_t fastav_attention_map(const fastav_model_t* model, const void* q,
   if (q_row_stride < (int64_t)model->n_q_heads * model->head_dim || k_row_stride < (int64_t)model->n_kv_heads * model->head_dim)
     return fail(FASTAV_EINVAL, "row strides are smaller than a row");
   return launch_attention_map(q, q_row_stride, k, k_row_stride, n, model->n_q_heads, model->n_kv_heads, model->head_dim,
-                              (float*)workspace, a_out, (hipStream_t)stream);
+                              (float2*)workspace, false, a_out, n, false, (hipStream_t)stream);
 }
 
-struct RolloutWs { size_t resid, hn, qkv, attn, hmlp, pos, cu, stats, a16, c, rt16, gemm, gemm_bytes, total; };
+struct RolloutWs { size_t resid, hn, qkv, attn, hmlp, pos, cu, stats, a16, rt16[2], rope_table, gemm, gemm_bytes, total; };
 
 static RolloutWs carve_rollout(const fastav_model_t& m, int64_t n) {
   RolloutWs w;
@@ -971,9 +971,11 @@ static RolloutWs carve_rollout(const fastav_model_t& m, int64_t n) {
   w.pos = take((size_t)n * 4);
   w.cu = take(256);
   w.stats = take(attention_map_stats_bytes((int)n, m.n_q_heads));
-  w.a16 = take((size_t)n * n * 2);
-  w.c = take((size_t)n * n * 4);
-  w.rt16 = take((size_t)n * n * 2);
+  const size_t square = (size_t)rollout_pitch(n) * (size_t)rollout_pitch(n) * 2;
+  w.a16 = take(square);
+  w.rt16[0] = take(square);
+  w.rt16[1] = take(square);
+  w.rope_table = take(rope_table_bytes((int)n, m.head_dim));
   w.gemm_bytes = mfma_linear_scratch_bytes();
   w.gemm = take(w.gemm_bytes);
   w.total = at;
@@ -1015,7 +1017,13 @@ fastav_status_t fastav_rollout(fastav_handle_t h, const void* x, int32_t n, floa
   FASTAV_TRY(upload_small(cu, cu_host, sizeof(cu_host), s));
   FASTAV_TRY(launch_iota(pos, n, s));
   FASTAV_TRY(launch_to_f32(x, resid, (int64_t)n * m.hidden, m.dtype, s));
-  FASTAV_TRY(launch_rollout_init(rt_out, base + ws.rt16, n, s));
+  FASTAV_TRY(launch_rollout_init(rt_out, base + ws.rt16[0], n, s));
+  // RoPE as in the prefill: in the projection's epilogue where the matrix-core kernel runs, from one table
+  void* rope_tab = base + ws.rope_table;
+  FASTAV_TRY(launch_rope_table(rope_tab, n, m.head_dim, m.rope_base, s));
+  const int qkv_rows[3] = {qd, kd, kd};
+  const bool rope_fused = g_options[FASTAV_OPT_FUSED_ROPE] && n > FASTAV_MAX_DECODE_BATCH &&
+                          mfma_linear_fuses_rope(n, qkv_rows, 3, 2, m.hidden, m.head_dim, m.dtype);
   // the RMSNorm behind a residual product adds its partial sums; it runs before the scratch they lie in is used again
   SplitKPending pend_o, pend_down;
   for (int l = 0; l < upto_layers; ++l) {
@@ -1023,16 +1031,23 @@ fastav_status_t fastav_rollout(fastav_handle_t h, const void* x, int32_t n, floa
     FASTAV_TRY(launch_rmsnorm(resid, W.g_attn, hn, n, m.hidden, m.rms_eps, m.dtype, s, &pend_down));
     const void* seg[3] = {W.wq, W.wk, W.wv};
     const int rows[3] = {qd, kd, kd};
-    FASTAV_TRY(linear_segments(hn, seg, rows, 3, nullptr, qkv, qkvd, n, m.hidden, FASTAV_EPI_STORE, m.dtype, nullptr, 0, s));
-    FASTAV_TRY(launch_rope(qkv, qkvd, pos, n, m.n_q_heads + m.n_kv_heads, m.head_dim, m.rope_base, m.dtype, s));
+    const RopeFuse rf = {pos, rope_tab, m.head_dim, 2};
+    FASTAV_TRY(linear_segments(hn, seg, rows, 3, nullptr, qkv, qkvd, n, m.hidden, FASTAV_EPI_STORE, m.dtype, nullptr, 0, s, nullptr, nullptr,
+                               rope_fused ? &rf : nullptr));
+    if (!rope_fused) FASTAV_TRY(launch_rope(qkv, qkvd, pos, n, m.n_q_heads + m.n_kv_heads, m.head_dim, m.rope_base, m.dtype, s, rope_tab));
+    // The layer's attention leaves every row's softmax statistics, which the map needs.  The hidden state past the last
+    // requested layer is not needed: there the map's own pass makes them.
+    const bool last = l + 1 == upto_layers;
+    const bool attn_stats = !last && mfma_attention_supported(m.head_dim, m.dtype, qkvd, qkvd, qd, n);
+    float2* const stats = (float2*)(base + ws.stats);
+    if (!last)
+      FASTAV_TRY(launch_attention(qkv, qkvd, qkv + (size_t)qd * 2, qkv + (size_t)(qd + kd) * 2, qkvd, attn, qd, cu, 1, n, n,
+                                  m.n_q_heads, m.n_kv_heads, m.head_dim, nullptr, nullptr, m.dtype,
+                                  2.0 * m.n_q_heads * m.head_dim * (double)n * ((double)n + 1.0), s, attn_stats ? stats : nullptr));
     FASTAV_TRY(launch_attention_map(qkv, qkvd, qkv + (size_t)qd * 2, qkvd, n, m.n_q_heads, m.n_kv_heads, m.head_dim,
-                                    (float*)(base + ws.stats), base + ws.a16, s));
-    FASTAV_TRY(launch_rollout_step(rt_out, base + ws.rt16, base + ws.a16, (float*)(base + ws.c), n, alpha,
-                                   base + ws.gemm, ws.gemm_bytes, s));
-    if (l + 1 == upto_layers) break;                   // the hidden state past the last requested layer is not needed
-    FASTAV_TRY(launch_attention(qkv, qkvd, qkv + (size_t)qd * 2, qkv + (size_t)(qd + kd) * 2, qkvd, attn, qd, cu, 1, n, n,
-                                m.n_q_heads, m.n_kv_heads, m.head_dim, nullptr, nullptr, m.dtype,
-                                2.0 * m.n_q_heads * m.head_dim * (double)n * ((double)n + 1.0), s));
+                                    stats, attn_stats, base + ws.a16, rollout_pitch(n), true, s));
+    FASTAV_TRY(launch_rollout_step(rt_out, base + ws.rt16[l & 1], base + ws.a16, base + ws.rt16[(l & 1) ^ 1], n, alpha, s));
+    if (last) break;
     FASTAV_TRY(launch_linear(attn, W.wo, nullptr, resid, n, m.hidden, qd, FASTAV_EPI_RESADD, m.dtype, base + ws.gemm, ws.gemm_bytes, s, &pend_o));
     FASTAV_TRY(launch_rmsnorm(resid, W.g_mlp, hn, n, m.hidden, m.rms_eps, m.dtype, s, &pend_o));
     FASTAV_TRY(launch_linear(hn, W.w_gate, W.w_up, hmlp, n, m.mlp_dim, m.hidden, FASTAV_EPI_SWIGLU, m.dtype, nullptr, 0, s));

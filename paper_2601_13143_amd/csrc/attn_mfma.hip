@@ -33,32 +33,22 @@ struct AttnArgs {
   float scale, scale_log2;             // 1/sqrt(dh) and the same times log2(e)
   int64_t T;
   float* last_logits; float* last_ml;
+  float2* row_stats;                   // kSideRows: [Hq][T], a row's (max in the log2 domain, 1 / sum of exp2)
 };
+
+// What a launch leaves besides O: nothing, the last row's logits with their (max, sum), or every row's (max, 1 / sum) of
+// each head.  The rows' sums are those of the probabilities before they are rounded for the product with V.
+enum AttnSide { kSideNone, kSideLast, kSideRows };
 
 typedef __attribute__((address_space(3))) bf16x4_t* lds_bf16x4_ptr;
 typedef f32x4_t f32x4_dword_t __attribute__((aligned(4)));   // a 16-byte store at a 4-byte address
-
-// Asynchronous 16-byte global -> LDS copies (no VGPR staging, no ds_write); lane l's data lands at
-// lds_byte_addr + 16 l.  Completion is tracked by vmcnt.  First form: per-lane 64-bit address.  Second form:
-// wave-uniform base in SGPRs plus a per-lane 32-bit byte offset, which keeps the address arithmetic of a
-// streaming copy on the scalar unit.
-__device__ __forceinline__ void attn_dma16(const void* gptr, uint32_t lds_byte_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gptr), "s"(lds_byte_addr) : "memory");
-}
-__device__ __forceinline__ void attn_dma16_sbase(const void* base, uint32_t voff, uint32_t lds_byte_addr) {
-  // the base is wave-uniform by contract; say so, or the register allocator may leave it in VGPRs
-  const uint64_t u = (uint64_t)(uintptr_t)base;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-  const void* sbase = (const void*)(uintptr_t)(((uint64_t)hi << 32) | lo);
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase), "s"(lds_byte_addr) : "memory");
-}
 
 // The vector ALU's issue port is what this kernel runs out of first (it also issues the matrix
 // instructions), so the softmax recurrence is written to spend as few vector instructions per logit as it
 // can: one fma + one exp2 per logit, one packed conversion and one packed dot product (the row sum) per two,
 // one three-way max per two, and a rescale of the accumulators only when a row's max has moved by more than
 // 2^8 since the last rescale (probabilities then stay below 256, exact in fp32 and harmless in bf16).
-template <int DH, int KG, bool PAIRED, bool EMIT>
+template <int DH, int KG, bool PAIRED, int SIDE>
 __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
   constexpr int BQ = 128, BKV = 64;
   constexpr int DCH = DH / 8;                       // 16-byte chunks per row
@@ -129,13 +119,13 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
       const uint32_t dst = (uint32_t)(st * STAGE + r0 * DCH) * 16u;
       if (t * BKV + BKV <= n) {
         const uint32_t off = (uint32_t)(t * BKV + r0) * row_bytes;
-        attn_dma16_sbase(kbase + off, k_voff, k_lds + dst);
-        attn_dma16_sbase(vbase + off, v_voff, v_lds + dst);
+        lds_copy16(kbase + off, k_voff, k_lds + dst);
+        lds_copy16(vbase + off, v_voff, v_lds + dst);
       } else {
         const int key = r0 + cp_row;
         const int jr = (t * BKV + key < n) ? t * BKV + key : n - 1;
-        attn_dma16(kbase + (uint32_t)jr * row_bytes + kswz(key, cp_pos) * 16, k_lds + dst);
-        attn_dma16(vbase + (uint32_t)jr * row_bytes + vswz(key, cp_pos) * 16, v_lds + dst);
+        lds_copy16(kbase + (uint32_t)jr * row_bytes + kswz(key, cp_pos) * 16, k_lds + dst);
+        lds_copy16(vbase + (uint32_t)jr * row_bytes + vswz(key, cp_pos) * 16, v_lds + dst);
       }
     }
   };
@@ -192,9 +182,9 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
 #pragma unroll
   for (int d = 0; d < NDB; ++d) o[d] = zero16;
   // m: running max (log2 domain); m_ref: the value the stored probabilities and sums are relative to
-  float m = -INFINITY, m_ref = -INFINITY, l = 0.f;
-  const bool emit = EMIT && a.last_logits != nullptr && qi == n - 1;
-  const bool emit_wave = EMIT && __ballot(emit) != 0;                    // wave-uniform: some lane owns the sample's last row
+  float m = -INFINITY, m_ref = -INFINITY, l = 0.f, lx[2] = {0.f, 0.f};   // lx: the sum before rounding (kSideRows)
+  const bool emit = SIDE == kSideLast && a.last_logits != nullptr && qi == n - 1;
+  const bool emit_wave = SIDE == kSideLast && __ballot(emit) != 0;                    // wave-uniform: some lane owns the sample's last row
 
   const int kv_end = (q0 + BQ < n) ? q0 + BQ : n;                // keys this workgroup can see
   const int n_tiles = (kv_end + BKV - 1) / BKV;
@@ -273,6 +263,7 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
       const float alpha = KG > 1 && m_to == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_to);   // 1 for the rows that stay
       m_ref = m_to;
       l *= alpha;
+      if (SIDE == kSideRows) { lx[0] *= alpha; lx[1] *= alpha; }
 #pragma unroll
       for (int d = 0; d < NDB; ++d)
 #pragma unroll
@@ -286,8 +277,11 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r += 2) {
         bf16x2_t pr;                                               // exp2(-inf) = 0 for masked keys
-        pr[0] = (bf16_t)__builtin_amdgcn_exp2f(fmaf(s[kb][r], a.scale_log2, -ref));
-        pr[1] = (bf16_t)__builtin_amdgcn_exp2f(fmaf(s[kb][r + 1], a.scale_log2, -ref));
+        const float e0 = __builtin_amdgcn_exp2f(fmaf(s[kb][r], a.scale_log2, -ref));
+        const float e1 = __builtin_amdgcn_exp2f(fmaf(s[kb][r + 1], a.scale_log2, -ref));
+        pr[0] = (bf16_t)e0;
+        pr[1] = (bf16_t)e1;
+        if (SIDE == kSideRows) { lx[0] += e0; lx[1] += e1; }
         l = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, l, false);  // row sum of the rounded probabilities
         pb[kb][r >> 3][r & 7] = pr[0];
         pb[kb][r >> 3][(r & 7) + 1] = pr[1];
@@ -327,13 +321,13 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
     // group 1 hands its (reference, max, sum, O^T) over through LDS, which is free after the last step's barrier: 4-byte
     // words [wave][value][lane].  A row of group 1 without any key has m_ref = -inf and a weight of 0; group 0 always
     // holds key 0.
-    float* xch = (float*)attn_lds + (wave * (16 * NDB + 3)) * 64 + lane;
+    float* xch = (float*)attn_lds + (wave * (16 * NDB + 4)) * 64 + lane;
     if (grp == 1) {
-      xch[0] = m_ref; xch[64] = m; xch[128] = l;
+      xch[0] = m_ref; xch[64] = m; xch[128] = l; xch[192] = lx[0] + lx[1];
 #pragma unroll
       for (int d = 0; d < NDB; ++d)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) xch[(3 + 16 * d + r) * 64] = o[d][r];
+        for (int r = 0; r < 16; ++r) xch[(4 + 16 * d + r) * 64] = o[d][r];
     }
     __syncthreads();
     if (grp == 1) return;
@@ -343,10 +337,11 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
     const float w0 = __builtin_amdgcn_exp2f(m_ref - safe), w1 = __builtin_amdgcn_exp2f(ref1 - safe);
     m_ref = to;
     l = l * w0 + l1 * w1;
+    if (SIDE == kSideRows) { lx[0] = (lx[0] + lx[1]) * w0 + xch[192] * w1; lx[1] = 0.f; }
 #pragma unroll
     for (int d = 0; d < NDB; ++d)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[d][r] = o[d][r] * w0 + xch[(3 + 16 * d + r) * 64] * w1;
+      for (int r = 0; r < 16; ++r) o[d][r] = o[d][r] * w0 + xch[(4 + 16 * d + r) * 64] * w1;
   }
 
   // ---- normalise and store.  o[d][r] is (dim 32d + (r/4)*8 + hf*4 + r%4, query qi).
@@ -368,6 +363,12 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
       // (max, sum of exp relative to the max), back from the log2 domain
       a.last_ml[((int64_t)b * a.Hq + h) * 2] = m * 0.6931471805599453f;
       a.last_ml[((int64_t)b * a.Hq + h) * 2 + 1] = l_tot * __builtin_amdgcn_exp2f(m_ref - m);
+    }
+    if (SIDE == kSideRows) {
+      const float lh = lx[0] + lx[1];
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lh), __float_as_uint(lh), false, false);
+      const float sum = (__uint_as_float(sw[0]) + __uint_as_float(sw[1])) * __builtin_amdgcn_exp2f(m_ref - m);
+      if (hf == 0) a.row_stats[(int64_t)h * a.T + row0 + qi] = make_float2(m, 1.0f / sum);
     }
   }
   if constexpr (PAIRED) __syncthreads();                        // the next part's first copy reuses stage 0
@@ -392,10 +393,10 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
 // key, so the line lies at twice that.  Three prompts of 331 (288 items): split 19.5, tiles 14.4; two of 1024 (512 items)
 // 33.2 against 31.4.  Pairs win where they fill one round of 512 (4096 tokens, 32 heads; 4600 tokens, 28 heads 156 against 163).
 enum AttnForm { kAttnTiles, kAttnPaired, kAttnSplit };
-static AttnForm attn_form(int n_qtiles, int n_pairs, int dh, bool emit, bool even) {
+static AttnForm attn_form(int n_qtiles, int n_pairs, int dh, bool side, bool even) {
   const int64_t items = (int64_t)n_qtiles * n_pairs, pairs = (int64_t)((n_qtiles + 1) / 2) * n_pairs;
   if (n_qtiles >= 3 && (items <= 256 || (n_qtiles >= 10 && items <= (dh == 64 ? 1024 : 512)))) return kAttnSplit;
-  return !emit && even && pairs >= 480 && pairs <= 512 ? kAttnPaired : kAttnTiles;
+  return !side && even && pairs >= 480 && pairs <= 512 ? kAttnPaired : kAttnTiles;
 }
 
 bool mfma_attention_supported(int dh, int dtype, int64_t q_stride, int64_t kv_stride, int64_t o_stride, int max_seqlen) {
@@ -404,30 +405,33 @@ bool mfma_attention_supported(int dh, int dtype, int64_t q_stride, int64_t kv_st
          ((int64_t)max_seqlen + 64) * kv_stride * 2 < ((int64_t)1 << 31);
 }
 
-template <int DH, int KG, bool PAIRED, bool EMIT>
+template <int DH, int KG, bool PAIRED, int SIDE>
 static fastav_status_t launch_attn(const AttnArgs& a, int64_t blocks, hipStream_t s) {
   constexpr int shmem = 4 * KG * 64 * DH * 2;                     // two stages of KG 64-key K tiles and V tiles
   if constexpr (shmem > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_attn_mfma<DH, KG, PAIRED, EMIT>, hipFuncAttributeMaxDynamicSharedMemorySize, shmem);
+    hipError_t e = hipFuncSetAttribute((const void*)k_attn_mfma<DH, KG, PAIRED, SIDE>, hipFuncAttributeMaxDynamicSharedMemorySize, shmem);
     if (e != hipSuccess) return fail(FASTAV_EHIP, "attention: hipFuncSetAttribute: %s", hipGetErrorString(e));
   }
-  hipLaunchKernelGGL((k_attn_mfma<DH, KG, PAIRED, EMIT>), dim3((unsigned)blocks), dim3(256 * KG), shmem, s, a);
+  hipLaunchKernelGGL((k_attn_mfma<DH, KG, PAIRED, SIDE>), dim3((unsigned)blocks), dim3(256 * KG), shmem, s, a);
   return check_launch("attention_mfma");
+}
+template <int DH, int SIDE>
+static fastav_status_t launch_attn(const AttnArgs& a, AttnForm form, int64_t blocks, hipStream_t s) {
+  return form == kAttnSplit ? launch_attn<DH, 2, false, SIDE>(a, blocks, s) : launch_attn<DH, 1, false, SIDE>(a, blocks, s);
 }
 template <int DH>
 static fastav_status_t launch_attn(const AttnArgs& a, AttnForm form, int64_t blocks, hipStream_t s) {
-  const bool emit = a.last_logits != nullptr;
   // pairs come without the side output, but in the build that has its branch: that one keeps the tile loop's schedule
   // (4096 tokens 139.7 us, 142.0 without the branch)
-  if (form == kAttnPaired) return launch_attn<DH, 1, true, true>(a, blocks, s);
-  if (form == kAttnSplit) return emit ? launch_attn<DH, 2, false, true>(a, blocks, s) : launch_attn<DH, 2, false, false>(a, blocks, s);
-  return emit ? launch_attn<DH, 1, false, true>(a, blocks, s) : launch_attn<DH, 1, false, false>(a, blocks, s);
+  if (form == kAttnPaired) return launch_attn<DH, 1, true, kSideLast>(a, blocks, s);
+  if (a.row_stats != nullptr) return launch_attn<DH, kSideRows>(a, form, blocks, s);
+  return a.last_logits != nullptr ? launch_attn<DH, kSideLast>(a, form, blocks, s) : launch_attn<DH, kSideNone>(a, form, blocks, s);
 }
 
 fastav_status_t launch_attention_mfma(const void* q, int64_t q_stride, const void* k, const void* v,
                                       int64_t kv_stride, void* o, int64_t o_stride, const int32_t* cu, int batch,
                                       int64_t T, int max_seqlen, int Hq, int Hkv, int dh, float* last_logits,
-                                      float* last_ml, hipStream_t s) {
+                                      float* last_ml, float2* row_stats, hipStream_t s) {
   if (batch == 0 || max_seqlen == 0) return FASTAV_OK;
   if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) % 16 || ((uintptr_t)o % 8))
     return fail(FASTAV_EINVAL, "attention: q, k, v must be 16-byte aligned and o 8-byte aligned");
@@ -437,12 +441,12 @@ fastav_status_t launch_attention_mfma(const void* q, int64_t q_stride, const voi
   a.n_qtiles = (max_seqlen + 127) / 128;
   a.n_pairs = Hq * batch;
   // even: the samples' lengths lie within a sixteenth of the longest on average
-  const AttnForm form = attn_form(a.n_qtiles, a.n_pairs, dh, last_logits != nullptr, 16 * T >= (int64_t)15 * batch * max_seqlen);
+  const AttnForm form = attn_form(a.n_qtiles, a.n_pairs, dh, last_logits != nullptr || row_stats != nullptr, 16 * T >= (int64_t)15 * batch * max_seqlen);
   const int64_t blocks = (int64_t)(form == kAttnPaired ? (a.n_qtiles + 1) / 2 : a.n_qtiles) * a.n_pairs;
   if (blocks > 0x7FFFFFFF) return fail(FASTAV_EUNSUPPORTED, "attention: too many workgroups");
   a.scale = 1.0f / sqrtf((float)dh);
   a.scale_log2 = a.scale * 1.4426950408889634f;
-  a.T = T; a.last_logits = last_logits; a.last_ml = last_ml;
+  a.T = T; a.last_logits = last_logits; a.last_ml = last_ml; a.row_stats = row_stats;
   return dh == 128 ? launch_attn<128>(a, form, blocks, s) : launch_attn<64>(a, form, blocks, s);
 }
 

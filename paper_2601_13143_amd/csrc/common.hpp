@@ -36,6 +36,21 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Asynchronous 16-byte global -> LDS copies (no VGPR staging, no ds_write); lane l's data lands at
+// lds_byte_addr + 16 l.  Completion is tracked by vmcnt.  First form: per-lane 64-bit address.  Second form:
+// wave-uniform base in SGPRs plus a per-lane 32-bit byte offset, which keeps the address arithmetic of a
+// streaming copy on the scalar unit.
+__device__ __forceinline__ void lds_copy16(const void* gptr, uint32_t lds_byte_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gptr), "s"(lds_byte_addr) : "memory");
+}
+__device__ __forceinline__ void lds_copy16(const void* base, uint32_t voff, uint32_t lds_byte_addr) {
+  // the base is wave-uniform by contract; say so, or the register allocator may leave it in VGPRs
+  const uint64_t u = (uint64_t)(uintptr_t)base;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  const void* sbase = (const void*)(uintptr_t)(((uint64_t)hi << 32) | lo);
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase), "s"(lds_byte_addr) : "memory");
+}
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
 
@@ -96,10 +111,12 @@ bool linear_takes_rows(int64_t m, int n, int k, int epilogue, int dtype, int64_t
 fastav_status_t launch_linear(const void* a, const void* w, const void* w2, void* c, int64_t m, int n, int k,
                               int epilogue, int dtype, void* scratch, size_t scratch_bytes, hipStream_t s,
                               SplitKPending* pend = nullptr, RowGather rows = RowGather());
+// row_stats (optional; the bf16 matrix-core kernel only, without last_logits): [Hq][T] = (max in the log2 domain, 1 / sum of
+// exp2) of every row, what the attention map is made from
 fastav_status_t launch_attention(const void* q, int64_t q_stride, const void* k, const void* v, int64_t kv_stride,
                                  void* o, int64_t o_stride, const int32_t* cu, int batch, int64_t T, int max_seqlen,
                                  int Hq, int Hkv, int dh, float* last_logits, float* last_ml, int dtype,
-                                 double flops_hint, hipStream_t s);
+                                 double flops_hint, hipStream_t s, float2* row_stats = nullptr);
 
 // RoPE folded into the plain-store epilogue of a projection: rows are rotated by pos[row] with the (cos, sin) table
 // launch_rope_table wrote; the first n_segs weight segments (whole heads of head_dim columns) are rotated.

@@ -126,3 +126,27 @@ def test_attention_map_heads_and_keys_dealt_over_waves(Hq, Hkv, dh, n):
     """Head counts that are no multiple of a workgroup's eight waves (or fewer), and key counts below, at and just beyond
     the blocks that the waves take in turn."""
     test_attention_map_matches_oracle(Hq, Hkv, dh, n)
+
+
+@pytest.mark.parametrize("n", [8, 64, 68, 128, 196, 388])
+def test_rollout_at_the_edges_of_its_tiles(n):
+    """One to seven 64 x 64 tiles a side, whole and ragged, and more K slices than a workgroup has waves."""
+    m = fi.Model(3, 512, 8, 2, 128, 1024, 1.0e4, 1e-6, "bf16")
+    w = fi.Workload("roll", m, [[(fi.TEXT, 4), (fi.VIDEO, n - 4)]], [], seed=n)
+    weights = [fi.layer_weights(m, l, 17) for l in range(m.n_layers)]
+    for W in weights:
+        W["wq"] = fi.round_bf16((W["wq"] * 6.0).astype(np.float32))
+        W["wk"] = fi.round_bf16((W["wk"] * 6.0).astype(np.float32))
+    x = fi.embeddings(w)
+    dec = make_decoder(m, weights)
+    want = orc.attention_rollout(m, weights, x, 0.6)
+    for upto in (1, 3):                                # the statistics of the map's own pass, and those of the attention
+        got = host(dec.fastav_rollout(dev(x, "bf16"), 0.6, upto))
+        assert rel_l2(got, want[upto - 1]) <= 1e-2, (n, upto, rel_l2(got, want[upto - 1]))   # the bound of the rollout above
+        assert np.all(np.triu(got, 1) == 0.0)
+
+
+@pytest.mark.parametrize("Hq,Hkv,dh,n", [(3, 1, 128, 1412), (5, 5, 64, 1476), (1, 1, 64, 68)])
+def test_attention_map_with_more_tiles_than_cus(Hq, Hkv, dh, n):
+    """Beyond 256 tiles the heads are dealt over two waves a block instead of four; head counts that no share divides."""
+    test_attention_map_matches_oracle(Hq, Hkv, dh, n)
