@@ -974,13 +974,19 @@ size_t decode_attn_workspace_bytes(int batch, int Hq, int dh, int max_splits) {
   return align_up((size_t)batch * Hq * max_splits * (dh + 2) * sizeof(float), 256);
 }
 
-int decode_attn_splits(int batch, int Hkv, int max_keys) {
-  int chunks = (max_keys + 63) / 64;
-  int want = (1024 + batch * Hkv - 1) / (batch * Hkv);          // about four workgroups per CU
-  int s = want < chunks ? want : chunks;
-  if (s < 1) s = 1;
-  if (s > 64) s = 64;
-  return s;
+// Keys per split.  A workgroup's four waves take 64 keys each, so shares of 256 keys keep all of them at work; the sums of the
+// waves meet in LDS, those of the splits in the merge.  Where that makes fewer than 192 workgroups the keys are
+// cut finer instead, one wave at work in each: the loads in flight count then.  A step's time per layer in us, finest
+// shares (about four workgroups per CU, whatever is left of them for a wave) against 256 keys: 8 prompts of 5000 (the ragged
+// batch) 125.2 / 121.4, 4 of 3000 112.8 / 110.0, 7 of 6000 with 4 KV heads 135.9 / 131.0, 2 of 6000 (192 workgroups) 114.7 / 113.9;
+// one of 4096 (136) 94.8 / 95.3, one of 512 (16) 94.0 / 95.4.
+static int decode_attn_chunk(int batch, int Hkv, int max_keys) {
+  const int64_t groups = (int64_t)batch * Hkv;
+  if (ceil_div(max_keys, 256) * groups >= 192) return (int)(ceil_div(ceil_div(max_keys, 64), 256) * 256);
+  const int64_t want = (1024 + groups - 1) / groups, chunks = ceil_div(max_keys, 64);
+  int64_t splits = want < chunks ? want : chunks;
+  if (splits > 64) splits = 64;
+  return (int)(ceil_div(ceil_div(max_keys, splits), 64) * 64);
 }
 
 fastav_status_t launch_decode_attention(const void* q, const void* k_self, const void* v_self, int64_t q_stride,
@@ -1002,8 +1008,8 @@ fastav_status_t launch_decode_attention(const void* q, const void* k_self, const
   a.k_gen = (const bf16_t*)k_gen; a.v_gen = (const bf16_t*)v_gen; a.gen_len = gen_len; a.gen_cap = gen_cap;
   a.Hq = Hq; a.Hkv = Hkv;
   const int max_keys = max_prefix + gen_len + 1;
-  a.splits = decode_attn_splits(batch, Hkv, max_keys);
-  a.chunk = (int)(ceil_div(ceil_div(max_keys, a.splits), 64) * 64);
+  a.chunk = decode_attn_chunk(batch, Hkv, max_keys);
+  a.splits = (int)ceil_div(max_keys, a.chunk);          // at most 64
   a.scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
   a.part = part;
   if ((size_t)batch * Hq * a.splits * (dh + 2) * sizeof(float) > part_bytes)

@@ -327,6 +327,12 @@ def test_decode_step_hidden_above_the_resident_limit(batch, hq, hkv, dh):
     _steps_with_generated_cache(fi.Model(2, 4224, hq, hkv, dh, 4096, 1.0e4, 1e-6, "bf16"), batch, 70, 2, 5)
 
 
+@pytest.mark.parametrize("batch,hq,hkv,dh,n_prefix", [(16, 16, 8, 64, 260), (16, 8, 4, 128, 770), (6, 16, 8, 64, 1030), (3, 32, 32, 64, 520), (1, 8, 8, 64, 16600)])
+def test_decode_attention_in_shares_of_256_keys(batch, hq, hkv, dh, n_prefix):
+    """192 workgroups or more: shares of 256 keys (512 beyond 64 of them), samples that end at, before and inside a share."""
+    _steps_with_generated_cache(fi.Model(1, 512, hq, hkv, dh, 512, 1.0e4, 1e-6, "bf16"), batch, n_prefix, 2, 23)
+
+
 def test_decode_step_rejects_bad_arguments():
     w, weights, x = _small()
     m = w.model
