@@ -479,16 +479,29 @@ fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, cons
   fastav_span_t* spans_dev = (fastav_span_t*)(base + ws.spans);
   void* gscr = ws.gemm_scratch_bytes ? (void*)(base + ws.gemm_scratch) : nullptr;
 
-  FASTAV_TRY(upload_small(cu_dev, cu_host.data(), cu_host.size() * 4, s));
-  FASTAV_TRY(upload_small(span_off_dev, in->span_offsets, (size_t)(B + 1) * 4, s));
-  FASTAV_TRY(upload_small(spans_dev, in->spans, (size_t)in->span_offsets[B] * sizeof(fastav_span_t), s));
-  FASTAV_TRY(launch_init_tokens(cu_dev, span_off_dev, spans_dev, B, T0, max_len0, n_last, pos[0], prot[0], s));
-  FASTAV_TRY(launch_to_f32(in->x, resid[0], T0 * m.hidden, m.dtype, s));
+  // The residual stream and the positions of the last stage live in the caller's outputs: the last prune compacts into them
+  // (without a prune the set-up writes them), and nothing is left to copy at the end.  Where x_out lies over x, or the positions
+  // at odd addresses, they stay in the workspace and are copied as the last step.
+  const char *x0 = (const char*)in->x, *x1 = x0 + (size_t)T0 * m.hidden * (m.dtype == FASTAV_BF16 ? 2 : 4);
+  const char *y0 = (const char*)out->x_out, *y1 = y0 + (size_t)T_stage[n_stages - 1] * m.hidden * 4;
+  const bool outputs_direct = (y1 <= x0 || x1 <= y0) && (uintptr_t)out->kept_pos_out % 4 == 0 && (uintptr_t)out->cu_seqlens_out % 4 == 0;
+  if (n_prunes == 0 && outputs_direct) { resid[0] = out->x_out; pos[0] = out->kept_pos_out; }
   // rotary (cos, sin) of every original position, once: tokens keep their positions through every prune
   // fp32 models: RMSNorm and RoPE ride in the projections (16-byte loads of the rows and gains)
   const bool f32_fused = m.dtype == FASTAV_F32 && m.hidden % 4 == 0 && ceil_div(T0, 32) <= 65535;
   void* rope_tab = m.dtype == FASTAV_BF16 || f32_fused ? (void*)(base + ws.rope_table) : nullptr;
-  if (rope_tab) FASTAV_TRY(launch_rope_table(rope_tab, max_len0, m.head_dim, m.rope_base, s));
+  const bool one_setup = outputs_direct && prefill_begin_fits(n_stages, B, in->span_offsets[B]);
+  if (one_setup) {
+    FASTAV_TRY(launch_prefill_begin(PrefillSetup{cu_host.data(), n_stages, in->span_offsets, in->spans, B, n_last, m.hidden, m.dtype, T0, in->x, resid[0],
+                                                 cu_dev, out->cu_seqlens_out, pos[0], prot[0], rope_tab, max_len0, m.head_dim, m.rope_base}, s));
+  } else {
+    FASTAV_TRY(upload_small(cu_dev, cu_host.data(), cu_host.size() * 4, s));
+    FASTAV_TRY(upload_small(span_off_dev, in->span_offsets, (size_t)(B + 1) * 4, s));
+    FASTAV_TRY(upload_small(spans_dev, in->spans, (size_t)in->span_offsets[B] * sizeof(fastav_span_t), s));
+    FASTAV_TRY(launch_init_tokens(cu_dev, span_off_dev, spans_dev, B, T0, max_len0, n_last, pos[0], prot[0], s));
+    FASTAV_TRY(launch_to_f32(in->x, resid[0], T0 * m.hidden, m.dtype, s));
+    if (rope_tab) FASTAV_TRY(launch_rope_table(rope_tab, max_len0, m.head_dim, m.rope_base, s));
+  }
 
   const size_t es = m.dtype == FASTAV_BF16 ? 2 : 4;
   const int qd = m.n_q_heads * m.head_dim, kd = m.n_kv_heads * m.head_dim;
@@ -508,6 +521,7 @@ fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, cons
                                                                         : SelectRule{kSelEarliest, 0, nullptr};
       FASTAV_TRY(launch_select(nullptr, prot[cur], cu_in, cu_nx, B, maxlen_stage[stage], kidx,
                                (rule.order == kSelRandom ? 5.0 : 1.0) * T_stage[stage] + 4.0 * T_stage[stage + 1], s, rule));
+      if (outputs_direct && pi + 1 == n_prunes) { resid[cur ^ 1] = out->x_out; pos[cur ^ 1] = out->kept_pos_out; }
       GatherTensor g[3] = {{resid[cur], resid[cur ^ 1], (int64_t)m.hidden * 4, 0},
                            {pos[cur], pos[cur ^ 1], 4, 0},
                            {prot[cur], prot[cur ^ 1], 1, 0}};
@@ -595,6 +609,7 @@ fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, cons
       if (g_options[FASTAV_OPT_FUSED_GATHER_OPROJ] && linear_takes_rows(T_stage[stage + 1], m.hidden, qd, FASTAV_EPI_RESADD, m.dtype, Tl)) {
         o_rows.idx = kidx; o_rows.n_src = Tl;
       }
+      if (outputs_direct && pi + 1 == n_prunes) { resid[cur ^ 1] = out->x_out; pos[cur ^ 1] = out->kept_pos_out; }
       GatherTensor g[6] = {{resid[cur], resid[cur ^ 1], (int64_t)m.hidden * 4, 0},
                            {pos[cur], pos[cur ^ 1], 4, 0},
                            {prot[cur], prot[cur ^ 1], 1, 0},
@@ -639,9 +654,11 @@ fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, cons
       FASTAV_TRY(launch_copy_rows(resid[cur], (int64_t)m.hidden * 4, out->layer_x_out[l], (int64_t)m.hidden * 4, To, nullptr, s));
   }
   const int64_t Tf = T_stage[stage];
-  FASTAV_TRY(launch_copy_rows(resid[cur], (int64_t)m.hidden * 4, out->x_out, (int64_t)m.hidden * 4, Tf, nullptr, s));
-  FASTAV_TRY(launch_copy_rows(pos[cur], 4, out->kept_pos_out, 4, Tf, nullptr, s));
-  FASTAV_TRY(launch_copy_rows(cu_dev + (size_t)stage * (B + 1), 4, out->cu_seqlens_out, 4, B + 1, nullptr, s));
+  if (!outputs_direct) {
+    FASTAV_TRY(launch_copy_rows(resid[cur], (int64_t)m.hidden * 4, out->x_out, (int64_t)m.hidden * 4, Tf, nullptr, s));
+    FASTAV_TRY(launch_copy_rows(pos[cur], 4, out->kept_pos_out, 4, Tf, nullptr, s));
+  }
+  if (!one_setup) FASTAV_TRY(launch_copy_rows(cu_dev + (size_t)stage * (B + 1), 4, out->cu_seqlens_out, 4, B + 1, nullptr, s));
   return FASTAV_OK;
 }
 

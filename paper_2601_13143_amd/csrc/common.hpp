@@ -79,6 +79,20 @@ fastav_status_t upload_small(void* dst_dev, const void* host_src, size_t bytes, 
 fastav_status_t launch_init_tokens(const int32_t* cu, const int32_t* span_offsets, const fastav_span_t* spans,
                                    int batch, int64_t T, int max_seqlen, int n_last, int32_t* pos, uint8_t* prot,
                                    hipStream_t s);
+// A prefill's set-up in one launch, where schedule and spans fit the kernel arguments: prefix sums of all stages to cu (the last
+// stage's also to cu_out), positions, protected rows, the embeddings as fp32, and (table != nullptr) the rotary table.
+struct PrefillSetup {
+  const int32_t* host_cu; int n_stages;             // [n_stages][batch + 1]
+  const int32_t* host_span_offsets; const fastav_span_t* host_spans;
+  int batch, n_last, hidden, dtype;
+  int64_t T;
+  const void* x; float* resid;
+  int32_t *cu, *cu_out, *pos;
+  uint8_t* prot;
+  void* table; int n_pos, head_dim; float base;
+};
+bool prefill_begin_fits(int n_stages, int batch, int n_spans);
+fastav_status_t launch_prefill_begin(const PrefillSetup& c, hipStream_t s);
 fastav_status_t launch_to_f32(const void* x, float* y, int64_t n, int dtype, hipStream_t s);
 // dst_row_bytes_stride == 0: destination rows are packed
 fastav_status_t launch_copy_rows(const void* src, int64_t src_row_bytes_stride, void* dst, int64_t row_bytes,

@@ -1,0 +1,60 @@
+"""The prefill's first launch (schedule, positions, protected rows, fp32 embeddings, rotary table) and outputs that are written in place."""
+import numpy as np
+import pytest
+import torch
+
+import fastav_inputs as fi
+import paper_2601_13143_amd as fa
+from gpu_util import dev, host, make_decoder, prune_tuples
+from oracle import fastav_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(samples, prunes, dtype, hidden=192, seed=5):
+    m = fi.Model(2, hidden, 4, 2, 64, 256, 1.0e4, 1e-6, dtype)
+    w = fi.Workload("setup", m, samples, prunes, seed=seed)
+    weights = [fi.layer_weights(m, l, 3) for l in range(m.n_layers)]
+    return w, weights, fi.embeddings(w)
+
+
+def _run(dec, w, x, **kw):
+    spans, offs = fi.span_table(w)
+    o = dec.fastav_prefill(x, fi.cu_seqlens(w), spans, offs, prune_tuples(w), 1, **kw)
+    torch.cuda.synchronize()
+    return o
+
+
+def _check(w, weights, x, o, tol):
+    ref = orc.prefill(w, weights, x, keep_kv=False)
+    cu = o["cu_seqlens_out"].cpu().numpy()
+    assert cu.tolist() == np.concatenate([[0], np.cumsum([len(r["kept_pos"]) for r in ref])]).tolist()
+    for b, r in enumerate(ref):
+        assert np.array_equal(o["kept_pos"].cpu().numpy()[cu[b]:cu[b + 1]], r["kept_pos"])
+        g = host(o["x_out"])[cu[b]:cu[b + 1]]
+        assert np.linalg.norm(g - r["x_out"]) <= tol * np.linalg.norm(r["x_out"]), b
+
+
+@pytest.mark.parametrize("dtype,tol", [("f32", 2e-5), ("bf16", 1e-2)])
+@pytest.mark.parametrize("prunes", [[], [fi.Prune(1, fi.GLOBAL, 0.5)]])
+@pytest.mark.parametrize("batch", [1, 3, 200])
+def test_setup_and_outputs(batch, prunes, dtype, tol):
+    """One sample to 200 (whose schedule and spans do not fit the kernel arguments: separate launches), with the last stage's
+    rows written to the outputs by the set-up (no prune) or by the last compaction; spans that start mid-sample, rows that
+    end inside a workgroup."""
+    samples = [[(fi.TEXT, 1 + b % 3), (fi.VIDEO, 4 + b % 5), (fi.AUDIO, 3), (fi.TEXT, 2)] for b in range(batch)]
+    if batch == 3:
+        samples[1] = [(fi.VIDEO, 300), (fi.TEXT, 7), (fi.AUDIO, 211)]
+    w, weights, x = _case(samples, prunes, dtype, hidden=200 if dtype == "f32" else 192)
+    _check(w, weights, x, _run(make_decoder(w.model, weights), w, dev(x, dtype)), tol)
+
+
+def test_output_over_the_input():
+    """x_out in the memory of x (an fp32 model without a prune): the residual stream then stays in the workspace."""
+    w, weights, x = _case([[(fi.VIDEO, 40), (fi.TEXT, 9)]], [], "f32")
+    dec, xd = make_decoder(w.model, weights), dev(x, "f32")
+    want = _run(dec, w, xd.clone())
+    outputs = {k: torch.empty_like(want[k]) for k in ("cu_seqlens_out", "kept_pos")}
+    got = _run(dec, w, xd, outputs={"x_out": xd, **outputs})
+    assert got["x_out"].data_ptr() == xd.data_ptr()
+    assert torch.equal(got["x_out"], want["x_out"]) and torch.equal(got["kept_pos"], want["kept_pos"]) and torch.equal(got["cu_seqlens_out"], want["cu_seqlens_out"])
