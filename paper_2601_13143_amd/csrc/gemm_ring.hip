@@ -1,14 +1,14 @@
 // bf16 linear layers of few rows (a short prompt, or the layers behind the prunes): C = A W^T with A [M, K], W [N, K].
 //
-// Bound: the weights' way from HBM, until about 200 rows; beyond, the wait for a stage's copies (331 rows of 18944 x 3584
-// gate/up, tiles of 384 x 160 with one stage behind the present one: matrix pipes busy 0.43 of the time, LDS 0.19, the
-// waves waiting 0.40).  So a workgroup keeps a deep ring of stages (64 of K) in flight instead of the two of the large
+// Bound: the weights' way from HBM, until about 200 rows; beyond, LDS and the stage's barrier (331 rows of 18944 x 3584
+// gate/up, tiles of 384 x 160: 13 operand reads to 30 matrix instructions; a third slot for the weights' stages changes
+// nothing, so it is not their latency).  So a workgroup keeps a deep ring of stages (64 of K) in flight instead of the two of the large
 // tiles, its rows are cut to a multiple of 64 close to M, and its columns or its share of K are cut so that one round of
 // workgroups covers the chip.
 //
 // A stage's operands travel to LDS with asynchronous 16-byte-per-lane copies, 8 rows x 128 contiguous bytes each, into
 // slot (stage mod NS); the one barrier of a stage publishes stage t and frees the slot of stage t-1, which takes the
-// copies of stage t + NS - 1.  A wave owns TM blocks of 16 rows and all BN columns of the tile; with KS = 2 the two k-steps of a stage
+// copies of stage t + NS - 1 (t + NS where the next k-step's operands are read ahead).  A wave owns TM blocks of 16 rows and all BN columns of the tile; with KS = 2 the two k-steps of a stage
 // go to two waves (the second wave of a SIMD covers the first one's LDS reads), whose sums meet in LDS at the end.
 // A wave that spans all columns holds every pair the epilogues need in one lane: gate and up (the tile's weight rows
 // alternate 16 gate, 16 up) and the two halves of a rotated head.
@@ -54,6 +54,11 @@ __global__ __launch_bounds__(BM / (16 * TM) * KS * 64) void k_gemm_ring(GemmArgs
   const int kt0 = (int)((int64_t)kt_all * split / g.splits);
   const int KT = (int)((int64_t)kt_all * (split + 1) / g.splits) - kt0;
 
+  // Gate and up rows at a pitch of whole 4 KB, every workgroup at the same k: the rows then meet in a few memory channels, so
+  // each workgroup starts its walk of K elsewhere (weights of 28672 x 4096, 48 / 82 / 117 / 166 rows: 52 / 53 / 55 / 62 ->
+  // 46 / 48 / 51 / 59 us; rows of other pitches, the other products and the large tiles gain nothing).
+  const int rot = EPI == FASTAV_EPI_SWIGLU && K % 2048 == 0 ? pid * 5 % KT : 0;
+
   const bf16_t* wbase = g.W[0];
   int seg_start = 0, seg = 0;
   if (EPI == FASTAV_EPI_STORE) {
@@ -97,7 +102,9 @@ __global__ __launch_bounds__(BM / (16 * TM) * KS * 64) void k_gemm_ring(GemmArgs
     vo[c] = ((uint32_t)src * (uint32_t)K + (uint32_t)(dpos ^ ((row >> 1) & 7)) * 8u) * 2u;
   }
   auto copies = [&](int t, int slot) __attribute__((always_inline)) {   // past the last stage: the last one again, unread
-    const uint32_t so = (uint32_t)((t < KT ? t : KT - 1) * 128);
+    int at = (t < KT ? t : KT - 1) + rot;
+    if (EPI == FASTAV_EPI_SWIGLU && at >= KT) at -= KT;
+    const uint32_t so = (uint32_t)(at * 128);
     const uint32_t dst = lds0 + (uint32_t)slot * SLOT + (uint32_t)wave * 1024u;
 #pragma unroll
     for (int c = 0; c < D; ++c)
@@ -111,32 +118,93 @@ __global__ __launch_bounds__(BM / (16 * TM) * KS * 64) void k_gemm_ring(GemmArgs
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int frow = lane & 15, fch = lane >> 4;
 
-#pragma unroll
-  for (int t = 0; t < NS - 1; ++t) copies(t, t);
-  int slot = 0, fill = NS - 1;
-#pragma unroll 1
-  for (int t = 0; t < KT; ++t) {
-    // stage t has landed when only the copies of the NS - 2 stages behind it are in flight
-    if (FULL == NW || nd == D) dma_wait_keep<(NS - 2) * D>(); else dma_wait_keep<(NS - 2) * (D - 1)>();
-    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");           // and stage t - 1 has been read
-    __syncthreads();
-    copies(t + NS - 1, fill);
+  auto read_step = [&](int slot, int ks, bf16x8_t (&af)[TM], bf16x8_t (&bf)[TN]) __attribute__((always_inline)) {
     const bf16x8_t* sl = lds + slot * (SLOT / 16);
 #pragma unroll
-    for (int s = 0; s < 2 / KS; ++s) {
-      const int ks = KS == 2 ? wk : s;
-      bf16x8_t af[TM], bf[TN];
+    for (int i = 0; i < TM; ++i) af[i] = sl[swz8(wm * 16 * TM + frow, ks * 4 + fch) + i * 128];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[i] = sl[swz8(wm * 16 * TM + frow, ks * 4 + fch) + i * 128];
+    for (int j = 0; j < TN; ++j) bf[j] = sl[BM * 8 + swz8(frow, ks * 4 + fch) + j * 128];
+  };
+  auto multiply = [&](const bf16x8_t (&af)[TM], const bf16x8_t (&bf)[TN]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) bf[j] = sl[BM * 8 + swz8(frow, ks * 4 + fch) + j * 128];
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);
+  };
+  // PIPED: the operands of a k-step are read while the one before it is multiplied, a read behind every few matrix instructions;
+  // stage t's barrier publishes stage t + 1 and, every wave having read stage t, frees its slot for stage t + NS.  With a wave per
+  // SIMD and two k-steps a stage the reads stood alone at the head of each: gate/up of 200 rows 83 -> 71 (3584 x 37888) and
+  // 75 -> 65 us, 331 rows 106 -> 102, down of 200 rows 48 -> 46 and 44 -> 42.  Projections of up to 128-row tiles gain where
+  // the weights' stream leaves room (82 rows, Q|K|V 20.5 -> 18.2 and 23.0 -> 20.2); the other tiles of two k-steps to two waves
+  // have no registers for a second set of operands (192 x 160 spills: 66 -> 180 us) or lose a percent.
+  constexpr bool PIPED = KS == 1 || (EPI == FASTAV_EPI_STORE && TN == 4 && BM <= 128);
+  auto interleave = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);
+    for (int u = 0; u < TM + TN; ++u) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, TM * TN / (TM + TN), 0);
     }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(TM * TN >= TM + TN, "at least one matrix instruction to a read");
+  int slot = 0;
+  auto next_stage = [&](int t) __attribute__((always_inline)) {
+    // stage t + 1 has landed when only the copies of the NS - 2 stages behind it are in flight
+    if (FULL == NW || nd == D) dma_wait_keep<(NS - 2) * D>(); else dma_wait_keep<(NS - 2) * (D - 1)>();
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+    __syncthreads();
+    copies(t + NS, slot);
     slot = slot + 1 == NS ? 0 : slot + 1;
-    fill = fill + 1 == NS ? 0 : fill + 1;
+  };
+  bf16x8_t a0[TM], b0[TN], a1[TM], b1[TN];
+  if constexpr (PIPED) {
+#pragma unroll
+    for (int t = 0; t < NS; ++t) copies(t, t);
+    if (FULL == NW || nd == D) dma_wait_keep<(NS - 1) * D>(); else dma_wait_keep<(NS - 1) * (D - 1)>();
+    __syncthreads();
+    read_step(0, wk, a0, b0);
+  }
+  if constexpr (KS == 1) {
+#pragma unroll 1
+    for (int t = 0; t < KT; ++t) {
+      read_step(slot, 1, a1, b1);
+      multiply(a0, b0);
+      interleave();
+      next_stage(t);
+      read_step(slot, 0, a0, b0);                                  // behind the last stage: a repeated one, not multiplied
+      multiply(a1, b1);
+      interleave();
+    }
+  } else if constexpr (PIPED) {
+    int t = 0;
+#pragma unroll 1
+    for (; t + 1 < KT; t += 2) {
+      next_stage(t);
+      read_step(slot, wk, a1, b1);
+      multiply(a0, b0);
+      interleave();
+      next_stage(t + 1);
+      read_step(slot, wk, a0, b0);
+      multiply(a1, b1);
+      interleave();
+    }
+    if (t < KT) multiply(a0, b0);
+  } else {
+#pragma unroll
+    for (int t = 0; t < NS - 1; ++t) copies(t, t);
+    int fill = NS - 1;
+#pragma unroll 1
+    for (int t = 0; t < KT; ++t) {
+      // stage t has landed when only the copies of the NS - 2 stages behind it are in flight
+      if (FULL == NW || nd == D) dma_wait_keep<(NS - 2) * D>(); else dma_wait_keep<(NS - 2) * (D - 1)>();
+      asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");         // and stage t - 1 has been read
+      __syncthreads();
+      copies(t + NS - 1, fill);
+      read_step(slot, wk, a0, b0);
+      multiply(a0, b0);
+      slot = slot + 1 == NS ? 0 : slot + 1;
+      fill = fill + 1 == NS ? 0 : fill + 1;
+    }
   }
 
   if constexpr (KS == 2) {

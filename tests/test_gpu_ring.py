@@ -30,6 +30,9 @@ CASES = [         # epilogue, rows, columns, K, (tile rows, tile columns, K shar
     (fa.EPI_SWIGLU, 129, 14336, 384, (192, 128, 1)), (fa.EPI_SWIGLU, 256, 14336, 320, (256, 128, 1)), (fa.EPI_SWIGLU, 64, 18944, 256, (64, 160, 1)),
     (fa.EPI_SWIGLU, 128, 18944, 320, (128, 160, 1)), (fa.EPI_SWIGLU, 191, 18944, 256, (192, 160, 1)), (fa.EPI_SWIGLU, 193, 18880, 256, (256, 160, 1)),
     (fa.EPI_SWIGLU, 257, 18944, 256, (384, 160, 1)), (fa.EPI_SWIGLU, 331, 18944, 320, (384, 160, 1)), (fa.EPI_SWIGLU, 384, 16448, 256, (384, 160, 1)),
+    (fa.EPI_SWIGLU, 300, 18944, 448, (384, 160, 1)),
+    (fa.EPI_STORE, 100, 4096, 1152, (64, 64, 1)), (fa.EPI_STORE, 200, 8192, 576, (128, 64, 1)),       # odd numbers of stages
+    (fa.EPI_SWIGLU, 100, 14336, 2048, (128, 128, 1)), (fa.EPI_SWIGLU, 250, 14336, 4096, (256, 128, 1)),   # K walked from another place
     (fa.EPI_SWIGLU, 385, 18944, 256, TILES), (fa.EPI_SWIGLU, 145, 8192, 512, TILES),
 ]
 
