@@ -105,7 +105,7 @@ _SIGS = {
     "fastav_score_static": (C.c_int, [C.POINTER(Model), C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int32,
                                       C.c_int64, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]),
     "fastav_select_workspace_bytes": (C.c_size_t, [C.c_int32]),
-    "fastav_select_gather": (C.c_int, [C.c_void_p, C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.c_int32,
+    "fastav_select_gather": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32,
                                        C.c_int32, C.POINTER(C.c_void_p), C.POINTER(C.c_void_p), C.POINTER(C.c_int64),
                                        C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "fastav_rmsnorm": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int32, C.c_float, C.c_int32, C.c_void_p]),
@@ -147,8 +147,16 @@ def _check(st: int) -> None:
         raise FastavError(st, lib().fastav_last_error().decode())
 
 
+try:                                                     # the stream's address without a Stream object around it: 2.8 -> 0.3 us
+    from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
+except ImportError:
+    _cuda_getCurrentRawStream = None
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _cuda_getCurrentRawStream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _cuda_getCurrentRawStream(_cuda_getDevice())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -429,19 +437,20 @@ def fastav_select_gather(scores: Optional[torch.Tensor], protected_mask: torch.T
     kc = _i32(keep_counts)
     B = len(cu) - 1
     dev = protected_mask.device
-    total_keep = int(kc.sum())
-    keep_idx = torch.empty(max(total_keep, 1), dtype=torch.int32, device=dev)
+    total_keep = sum(kc.tolist())
+    need = lib().fastav_select_workspace_bytes(B)
+    # the rows' list and, behind it, the call's scratch
+    keep_idx = torch.empty(max(total_keep, 0) + (need + 3) // 4, dtype=torch.int32, device=dev)
     cu_out = torch.empty(B + 1, dtype=torch.int32, device=dev)
-    dsts = [torch.empty((total_keep,) + tuple(t.shape[1:]), dtype=t.dtype, device=dev) for t in tensors]
+    dsts = [torch.empty((total_keep, *t.shape[1:]), dtype=t.dtype, device=dev) for t in tensors]
     nt = len(tensors)
     src = (C.c_void_p * max(1, nt))(*[t.data_ptr() for t in tensors])
     dst = (C.c_void_p * max(1, nt))(*[t.data_ptr() if t.numel() else None for t in dsts])
     rb = (C.c_int64 * max(1, nt))(*[t.stride(0) * t.element_size() if t.dim() > 1 else t.element_size() for t in tensors])
-    need = lib().fastav_select_workspace_bytes(B)
-    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    _check(lib().fastav_select_gather(_ptr(scores), protected_mask.data_ptr(), cu.ctypes.data_as(C.POINTER(C.c_int32)),
-                                      kc.ctypes.data_as(C.POINTER(C.c_int32)), B, nt, src, dst, rb, keep_idx.data_ptr(),
-                                      cu_out.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
+    at = keep_idx.data_ptr()
+    _check(lib().fastav_select_gather(_ptr(scores), protected_mask.data_ptr(), cu.__array_interface__["data"][0],
+                                      kc.__array_interface__["data"][0], B, nt, src, dst, rb, at, cu_out.data_ptr(),
+                                      at + 4 * max(total_keep, 0), need, _stream()))
     return keep_idx[:total_keep], cu_out, dsts
 
 

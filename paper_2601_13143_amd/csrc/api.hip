@@ -778,11 +778,19 @@ fastav_status_t fastav_select_gather(const float* scores, const uint8_t* protect
   }
   hipStream_t s = (hipStream_t)stream;
   int32_t* cu_dev = (int32_t*)workspace;
-  FASTAV_TRY(upload_small(cu_dev, cu_seqlens, (size_t)(batch + 1) * 4, s));
-  FASTAV_TRY(upload_small(cu_seqlens_out, cu_out.data(), (size_t)(batch + 1) * 4, s));
+  SelectBounds bounds;
+  if (batch <= kSelMaxBounds) {
+    bounds.batch = batch;
+    bounds.cu_out_dev = cu_seqlens_out;
+    std::memcpy(bounds.cu, cu_seqlens, (size_t)(batch + 1) * 4);
+    std::memcpy(bounds.cu_out, cu_out.data(), (size_t)(batch + 1) * 4);
+  } else {
+    FASTAV_TRY(upload_small(cu_dev, cu_seqlens, (size_t)(batch + 1) * 4, s));
+    FASTAV_TRY(upload_small(cu_seqlens_out, cu_out.data(), (size_t)(batch + 1) * 4, s));
+  }
   FASTAV_TRY(launch_select(scores, protected_mask, cu_dev, cu_seqlens_out, batch, max_len, keep_idx_out,
                            (scores ? 5.0 : 1.0) * cu_seqlens[batch] + 4.0 * cu_out[batch], s,
-                           SelectRule{scores ? kSelHighScore : kSelEarliest, 0, nullptr}));
+                           SelectRule{scores ? kSelHighScore : kSelEarliest, 0, nullptr}, bounds));
   return launch_gather(g, n_tensors, keep_idx_out, cu_out[batch], s);
 }
 

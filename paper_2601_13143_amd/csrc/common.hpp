@@ -184,10 +184,18 @@ struct SelectRule {
 bool select_fuses_score(int max_seqlen, int n_heads);   // limits of the fused path
 uint32_t select_random_key(uint32_t seed, int layer);
 
+// Prefix sums of the rows and of the kept rows by value (batch > 0) for calls that hold them on the host; the kernel writes
+// the kept rows' to cu_out_dev.  Two upload launches of a prune step less, 9 us of its host time.
+constexpr int kSelMaxBounds = 32;
+struct SelectBounds {
+  int batch = 0;
+  int32_t* cu_out_dev = nullptr;
+  int32_t cu[kSelMaxBounds + 1], cu_out[kSelMaxBounds + 1];
+};
 // Selection + compaction.  keep_idx/cu_out as in fastav_select_gather; scores are read by the two score orders only.
 fastav_status_t launch_select(const float* scores, const uint8_t* prot, const int32_t* cu, const int32_t* cu_out,
                               int batch, int max_seqlen, int32_t* keep_idx, double bytes_hint, hipStream_t s,
-                              SelectRule rule);
+                              SelectRule rule, const SelectBounds& bounds = SelectBounds());
 // src_stride_bytes == 0 means rows are packed (stride = row_bytes); row_bytes == 0 skips the tensor.
 struct GatherTensor { const void* src; void* dst; int64_t row_bytes; int64_t src_stride_bytes; };
 fastav_status_t launch_gather(const GatherTensor* t, int n_tensors, const int32_t* keep_idx, int64_t n_rows,

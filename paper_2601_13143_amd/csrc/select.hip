@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
                                                         const uint8_t* __restrict__ prot,
                                                         const int32_t* __restrict__ cu,
                                                         const int32_t* __restrict__ cu_out,
-                                                        int32_t* __restrict__ keep_idx, SelectRule rule) {
+                                                        int32_t* __restrict__ keep_idx, SelectRule rule, SelectBounds bounds) {
   extern __shared__ __align__(16) uint32_t keys[];                      // [n] when KEYS_IN_LDS; key 0 = protected (never a candidate)
   __shared__ int hist[kSelWaves][256];
   __shared__ int wave_tot[kSelWaves];
@@ -96,9 +96,12 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
   __shared__ int sh_need;
 
   const int b = blockIdx.x;
-  const int row0 = cu[b], n = cu[b + 1] - row0;
-  const int out0 = cu_out[b], k_keep = cu_out[b + 1] - out0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool given = bounds.batch > 0;                    // prefix sums in the kernel arguments
+  if (given && b == 0)
+    for (int i = tid; i <= bounds.batch; i += kSelThreads) bounds.cu_out_dev[i] = bounds.cu_out[i];
+  const int row0 = given ? bounds.cu[b] : cu[b], n = (given ? bounds.cu[b + 1] : cu[b + 1]) - row0;
+  const int out0 = given ? bounds.cu_out[b] : cu_out[b], k_keep = (given ? bounds.cu_out[b + 1] : cu_out[b + 1]) - out0;
   if (n <= 0) return;
   const uint32_t sample_key = mix32(rule.key + kGolden * (uint32_t)(b + 1));
 
@@ -323,8 +326,8 @@ bool select_fuses_score(int max_seqlen, int n_heads) { return max_seqlen <= kSel
 
 fastav_status_t launch_select(const float* scores, const uint8_t* prot, const int32_t* cu, const int32_t* cu_out,
                               int batch, int max_seqlen, int32_t* keep_idx, double bytes_hint, hipStream_t s,
-                              SelectRule rule) {
-  if (batch == 0 || max_seqlen == 0) return FASTAV_OK;
+                              SelectRule rule, const SelectBounds& bounds) {
+  if (batch == 0 || (max_seqlen == 0 && bounds.batch == 0)) return FASTAV_OK;
   if ((rule.order == kSelHighScore || rule.order == kSelLowScore) && !scores && !rule.logits) return fail(FASTAV_EINVAL, "select: this order needs scores");
   if (rule.logits && (max_seqlen > kSelLdsKeys || rule.n_heads > kSelMaxHeads || rule.n_heads < 1 || !rule.ml))
     return fail(FASTAV_EUNSUPPORTED, "select: the fused score finish needs samples of at most %d rows and at most %d heads", kSelLdsKeys, kSelMaxHeads);
@@ -336,9 +339,9 @@ fastav_status_t launch_select(const float* scores, const uint8_t* prot, const in
                                          kSelLdsKeys * (int)sizeof(uint32_t));
       if (e != hipSuccess) return fail(FASTAV_EHIP, "select: hipFuncSetAttribute: %s", hipGetErrorString(e));
     }
-    hipLaunchKernelGGL(k_select<true>, dim3((unsigned)batch), dim3(kSelThreads), shmem, s, scores, prot, cu, cu_out, keep_idx, rule);
+    hipLaunchKernelGGL(k_select<true>, dim3((unsigned)batch), dim3(kSelThreads), shmem, s, scores, prot, cu, cu_out, keep_idx, rule, bounds);
   } else {
-    hipLaunchKernelGGL(k_select<false>, dim3((unsigned)batch), dim3(kSelThreads), 0, s, scores, prot, cu, cu_out, keep_idx, rule);
+    hipLaunchKernelGGL(k_select<false>, dim3((unsigned)batch), dim3(kSelThreads), 0, s, scores, prot, cu, cu_out, keep_idx, rule, bounds);
   }
   return check_launch("select");
 }

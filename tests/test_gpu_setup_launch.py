@@ -58,3 +58,28 @@ def test_output_over_the_input():
     got = _run(dec, w, xd, outputs={"x_out": xd, **outputs})
     assert got["x_out"].data_ptr() == xd.data_ptr()
     assert torch.equal(got["x_out"], want["x_out"]) and torch.equal(got["kept_pos"], want["kept_pos"]) and torch.equal(got["cu_seqlens_out"], want["cu_seqlens_out"])
+
+
+@pytest.mark.parametrize("batch", [1, 32, 33])
+@pytest.mark.parametrize("scored", [True, False])
+def test_select_with_prefix_sums_in_the_arguments(batch, scored):
+    """Up to 32 samples the prefix sums travel with the launch, beyond they are uploaded; empty samples, samples that keep nothing
+    and all of their rows; the caller's prefix sums of the kept rows come out either way."""
+    rng = np.random.default_rng(batch)
+    n = rng.integers(1, 400, batch)
+    n[batch // 2] = 0 if batch > 1 else n[0]
+    cu = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    keep = np.array([0 if b % 5 == 3 else m if b % 5 == 4 else (m + 1) // 2 for b, m in enumerate(n)], dtype=np.int32)
+    T = int(cu[-1])
+    scores = rng.permutation(T).astype(np.float32)
+    rows = rng.standard_normal((T, 3)).astype(np.float32)
+    prot = torch.zeros(T, dtype=torch.uint8, device="cuda")
+    idx, cu_out, (got,) = fa.fastav_select_gather(torch.from_numpy(scores).cuda() if scored else None, prot, cu, keep, [torch.from_numpy(rows).cuda()])
+    want = []
+    for b in range(batch):
+        order = np.argsort(-scores[cu[b]:cu[b + 1]], kind="stable") if scored else np.arange(n[b])
+        want.append(cu[b] + np.sort(order[:keep[b]]))
+    want = np.concatenate(want)
+    assert np.array_equal(idx.cpu().numpy(), want)
+    assert np.array_equal(cu_out.cpu().numpy(), np.concatenate([[0], np.cumsum(keep)]))
+    assert np.array_equal(got.cpu().numpy(), rows[want])
