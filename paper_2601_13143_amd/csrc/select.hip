@@ -3,7 +3,7 @@
 // Tables 2-3 - top attentive, top informative, random - are further orders of the same kernel).
 //
 //   k_select  one 1024-thread workgroup per sample.  The sample's order-preserving 32-bit keys live in LDS;
-//             four 8-bit MSB-first radix passes (per-wave LDS histograms, so that the narrow exponent range
+//             four 8-bit MSB-first radix passes (LDS histograms in eight copies, so that the narrow exponent range
 //             of softmax scores does not serialise on one counter) find the k-th largest key; ties at
 //             the threshold go to the lowest indices; one workgroup scan (two where the keys do not fit in
 //             LDS) turns the keep flags into the ascending list of kept rows.  The positional orders need no
@@ -27,26 +27,27 @@ __device__ __forceinline__ uint32_t score_key(float s) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__device__ __forceinline__ int block_exclusive_scan(int v, int* wave_tot, int& total) {
-  // inclusive scan inside the wave
+// Inclusive prefix sum over a wave, all lanes active: rows of 16 by shifts, then lane 15 of a row into the next row and lane
+// 31 into the upper half.  In the vector ALU; through LDS (shuffles) it is a chain of six round trips.
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);      // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);      // row_bcast 15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);      // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
+// Exclusive prefix sum over the workgroup.  wave_tot must not be in use: a caller that scans twice takes two arrays.
+__device__ __forceinline__ int block_exclusive_scan(int v, int* wave_tot) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(inc, o, kWave);
-    if (lane >= o) inc += t;
-  }
-  __syncthreads();                          // wave_tot may still be read from a previous scan
+  const int inc = wave_inclusive_sum(v);
   if (lane == 63) wave_tot[wave] = inc;
   __syncthreads();
-  int base = 0, tot = 0;
+  int base = 0;
 #pragma unroll
-  for (int w = 0; w < kSelWaves; ++w) {
-    const int t = wave_tot[w];
-    if (w < wave) base += t;
-    tot += t;
-  }
-  total = tot;
+  for (int w = 0; w < kSelWaves; ++w) base += w < wave ? wave_tot[w] : 0;
   return base + inc - v;
 }
 
@@ -83,6 +84,12 @@ __device__ __forceinline__ uint32_t cand_key(const SelectRule& r, const float* s
   return cand_key_of(r, by_score ? scores[row0 + j] : 0.f, sample_key, row0, n, j);
 }
 
+// Bound: latency - one workgroup per sample, so a chain of trips to memory and of barriers (1229 to 2248 rows and 28 to 32
+// heads, kernel time in a prefill of one prompt: 16.7 -> 10.4 us; 2048 rows of given scores 12.3 -> 7.4).  Hence: the loads of the score
+// finish run two steps ahead and start before the first barrier; the first digit is counted as the keys are made; a radix
+// pass is two barriers, with the other histogram cleared meanwhile; and no loop is unrolled further than its loads ask for,
+// because a prefill comes here once a layer and what it does not find in the instruction cache it waits for.
+constexpr int kHistCopies = 8, kHistPitch = 256 + 4;       // copies by lane % 8, a digit's in different banks: scores share few top digits
 template <bool KEYS_IN_LDS>
 __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict__ scores,
                                                         const uint8_t* __restrict__ prot,
@@ -90,13 +97,14 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
                                                         const int32_t* __restrict__ cu_out,
                                                         int32_t* __restrict__ keep_idx, SelectRule rule, SelectBounds bounds) {
   extern __shared__ __align__(16) uint32_t keys[];                      // [n] when KEYS_IN_LDS; key 0 = protected (never a candidate)
-  __shared__ int hist[kSelWaves][256];
-  __shared__ int wave_tot[kSelWaves];
+  __shared__ __align__(16) int hist[2][kHistCopies][kHistPitch];
+  __shared__ int wave_prot[kSelWaves], wave_a[kSelWaves], wave_b[kSelWaves];
   __shared__ uint32_t sh_prefix;
   __shared__ int sh_need;
 
   const int b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool given = bounds.batch > 0;                    // prefix sums in the kernel arguments
   if (given && b == 0)
     for (int i = tid; i <= bounds.batch; i += kSelThreads) bounds.cu_out_dev[i] = bounds.cu_out[i];
@@ -104,191 +112,211 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
   const int out0 = given ? bounds.cu_out[b] : cu_out[b], k_keep = (given ? bounds.cu_out[b + 1] : cu_out[b + 1]) - out0;
   if (n <= 0) return;
   const uint32_t sample_key = mix32(rule.key + kGolden * (uint32_t)(b + 1));
+  const bool positional = rule.order == kSelEarliest || rule.order == kSelLatest;
+
+  auto clear_hist = [&](int buf, int first, int threads) __attribute__((always_inline)) {
+    for (int i = first; i < kHistCopies * kHistPitch / 4; i += threads) ((int4*)&hist[buf][0][0])[i] = int4{0, 0, 0, 0};
+  };
+  auto count_digit = [&](int buf, uint32_t digit) __attribute__((always_inline)) { atomicAdd(&hist[buf][lane % kHistCopies][digit], 1); };
+  // one row: its key to LDS and into the first histogram; returns the wave's count of protected rows (all lanes are here)
+  auto put_key = [&](int j, bool p, float score) __attribute__((always_inline)) -> int {
+    if (j < n && KEYS_IN_LDS) {
+      const uint32_t key = p ? 0u : cand_key_of(rule, score, sample_key, row0, n, j);
+      keys[j] = key;
+      if (key != 0u && !positional) count_digit(0, key >> 24);
+    }
+    return __popcll(__ballot(j < n && p));
+  };
 
   // ---- load keys, count protected rows.  With the attention side output at hand (rule.logits: the last query
   // row's scaled logits per head, rule.ml: that row's (max, sum of exp) per head) Eq. 4 is finished right here -
   // s_j = 1/Hq sum_h exp(L[h][j] - m_h) / l_h, the terms added in head order exactly as k_score_finalize adds them
   // - and goes straight into the key array (and to rule.scores_out for the caller), which saves a launch per prune.
-  int my_prot = 0;
+  int my_prot = 0;                                        // of the wave
+  clear_hist(0, tid, kSelThreads);
   if (KEYS_IN_LDS && rule.logits != nullptr) {
     __shared__ float sh_ml[2 * kSelMaxHeads];
     for (int h = tid; h < rule.n_heads; h += kSelThreads) {
       const float* pm = rule.ml + ((int64_t)b * rule.n_heads + h) * 2;
       sh_ml[2 * h] = pm[0]; sh_ml[2 * h + 1] = 1.0f / pm[1];
     }
+    // A step is sixteen heads of one row per lane; two steps are in flight (the planes of the heads are T floats apart, so
+    // every load is a trip to L2 or beyond, and one workgroup has to cover the whole sample).
+    constexpr int HB = 16;
+    const int H = rule.n_heads, nb = (H + HB - 1) / HB;
+    const int rounds = wave * 64 < n ? (n - wave * 64 + kSelThreads - 1) / kSelThreads : 0;
+    float cur[HB], nxt[HB];
+    bool p_cur = false, p_nxt = false;
+    int q_ask = 0, h_ask = 0;                             // the next step to ask for
+    auto ask = [&](float (&g)[HB], bool& p) __attribute__((always_inline)) {
+      if (q_ask < rounds) {                               // wave-uniform
+        int j = q_ask * kSelThreads + tid;
+        j = j < n ? j : n - 1;
+        const float* lp = rule.logits + row0 + j;
+#pragma unroll
+        for (int u = 0; u < HB; ++u) g[u] = lp[(int64_t)(h_ask + u < H ? h_ask + u : H - 1) * rule.T];
+        p = prot[row0 + j] != 0;
+        h_ask += HB;
+        if (h_ask >= H) { h_ask = 0; ++q_ask; }
+      }
+    };
+    ask(cur, p_cur);
+    ask(nxt, p_nxt);
     __syncthreads();
-    // Two rows per round and sixteen heads per batch: 32 independent loads in flight per thread (the planes of the
-    // heads are T floats apart, so every load is a trip to L2 or beyond, and one workgroup has to cover the whole
-    // sample).  A row's terms are still added in head order.
-    for (int j = tid; j < n; j += 2 * kSelThreads) {
-      const int j1 = j + kSelThreads;
-      const bool two = j1 < n;
-      const float* lp0 = rule.logits + row0 + j;
-      const float* lp1 = rule.logits + row0 + (two ? j1 : j);
-      float sc0 = 0.f, sc1 = 0.f;
-      for (int h0 = 0; h0 < rule.n_heads; h0 += 16) {
-        float g0[16], g1[16];
+    float sc = 0.f;
+    int h0 = 0, q = 0;
+#pragma nounroll
+    for (int st = 0; st < rounds * nb; ++st) {
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          const int h = (h0 + u < rule.n_heads) ? h0 + u : rule.n_heads - 1;
-          g0[u] = lp0[(int64_t)h * rule.T];
-          g1[u] = lp1[(int64_t)h * rule.T];
-        }
+      for (int u = 0; u < HB; ++u)
+        if (h0 + u < H) sc = fmaf(expf(cur[u] - sh_ml[2 * (h0 + u)]), sh_ml[2 * (h0 + u) + 1], sc);
+      h0 += HB;
+      if (h0 >= H) {
+        const int j = q * kSelThreads + tid;
+        sc = sc / (float)H;
+        if (rule.scores_out && j < n) rule.scores_out[row0 + j] = sc;
+        my_prot += put_key(j, p_cur, sc);
+        sc = 0.f;
+        h0 = 0;
+        ++q;
+      }
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          if (h0 + u < rule.n_heads) {
-            sc0 = fmaf(expf(g0[u] - sh_ml[2 * (h0 + u)]), sh_ml[2 * (h0 + u) + 1], sc0);
-            sc1 = fmaf(expf(g1[u] - sh_ml[2 * (h0 + u)]), sh_ml[2 * (h0 + u) + 1], sc1);
-          }
-        }
-      }
-      sc0 = sc0 / (float)rule.n_heads;
-      sc1 = sc1 / (float)rule.n_heads;
-      {
-        const bool p = prot[row0 + j] != 0;
-        my_prot += p ? 1 : 0;
-        if (rule.scores_out) rule.scores_out[row0 + j] = sc0;
-        keys[j] = p ? 0u : cand_key_of(rule, sc0, sample_key, row0, n, j);
-      }
-      if (two) {
-        const bool p = prot[row0 + j1] != 0;
-        my_prot += p ? 1 : 0;
-        if (rule.scores_out) rule.scores_out[row0 + j1] = sc1;
-        keys[j1] = p ? 0u : cand_key_of(rule, sc1, sample_key, row0, n, j1);
-      }
+      for (int u = 0; u < HB; ++u) cur[u] = nxt[u];
+      p_cur = p_nxt;
+      ask(nxt, p_nxt);
     }
   } else {
-    for (int j = tid; j < n; j += kSelThreads) {
-      const bool p = prot[row0 + j] != 0;
-      my_prot += p ? 1 : 0;
-      if (KEYS_IN_LDS) keys[j] = p ? 0u : cand_key(rule, scores, sample_key, row0, n, j);
+    __syncthreads();
+    const bool by_score = rule.order == kSelHighScore || rule.order == kSelLowScore;
+    constexpr int U = 4;                                  // rows asked for at a time
+    for (int j0 = wave * 64; j0 < n; j0 += U * kSelThreads) {
+      bool p[U];
+      float sc[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        int j = j0 + u * kSelThreads + lane;
+        j = j < n ? j : n - 1;
+        p[u] = prot[row0 + j] != 0;
+        sc[u] = KEYS_IN_LDS && by_score ? scores[row0 + j] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) my_prot += put_key(j0 + u * kSelThreads + lane, p[u], sc[u]);
     }
   }
-  int n_prot;
-  block_exclusive_scan(my_prot, wave_tot, n_prot);
+  auto key_at = [&](int j) __attribute__((always_inline)) -> uint32_t {
+    if (KEYS_IN_LDS) return keys[j];
+    return prot[row0 + j] ? 0u : cand_key(rule, scores, sample_key, row0, n, j);
+  };
+  if (!KEYS_IN_LDS && !positional)
+    for (int j = tid; j < n; j += kSelThreads) {
+      const uint32_t key = key_at(j);
+      if (key != 0u) count_digit(0, key >> 24);
+    }
+  if (lane == 0) wave_prot[wave] = my_prot;
+  __syncthreads();
+  int n_prot = 0;
+#pragma unroll
+  for (int w = 0; w < kSelWaves; ++w) n_prot += wave_prot[w];
   int need = k_keep - n_prot;                             // candidates to keep
   if (need < 0) need = 0;
   const int n_cand = n - n_prot;
   if (need > n_cand) need = n_cand;
 
-  // ---- radix select: largest `need` candidate keys.  After the passes: threshold key `prefix`,
-  //      `need_eq` = how many candidates equal to the threshold are kept (lowest indices first).
-  uint32_t prefix = 0, mask = 0;
-  int need_eq = need;
-  int eq_lo = 0;                                          // candidates equal to the threshold are kept from this rank on
-  const bool positional = rule.order == kSelEarliest || rule.order == kSelLatest;
-  if (positional && need > 0 && need < n_cand) {
-    // every candidate carries the same key: the first (earliest) or the last (latest) `need` of them in row order are
-    // kept by the rank rule alone, no pass over the keys is needed
-    prefix = 1u; mask = 0xFFFFFFFFu;
-    eq_lo = rule.order == kSelLatest ? n_cand - need : 0;
-  } else if (need > 0 && need < n_cand) {
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      for (int i = tid; i < kSelWaves * 256; i += kSelThreads) (&hist[0][0])[i] = 0;
-      __syncthreads();
-      for (int j = tid; j < n; j += kSelThreads) {
-        uint32_t key;
-        if (KEYS_IN_LDS) key = keys[j];
-        else key = prot[row0 + j] ? 0u : cand_key(rule, scores, sample_key, row0, n, j);
-        if (key != 0u && (key & mask) == prefix) atomicAdd(&hist[wave][(key >> shift) & 255u], 1);
-      }
-      __syncthreads();
-      if (wave == 0) {
-        // lane owns digits 4*lane .. 4*lane+3; walk from the top digit down until `need_eq` is covered
-        int c[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          int t = 0;
-          for (int w = 0; w < kSelWaves; ++w) t += hist[w][4 * lane + d];
-          c[d] = t;
-        }
-        const int mine = c[0] + c[1] + c[2] + c[3];
-        // suffix sum over lanes: above = total count of digits owned by higher lanes
-        int suf = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int t = __shfl_down(suf, o, kWave);
-          if (lane + o < 64) suf += t;
-        }
-        int above = suf - mine;
-        // the lane whose range crosses need_eq finds the digit
-        if (above < need_eq && need_eq <= suf) {
-          int d = 3;
-          for (; d >= 0; --d) {
-            if (above + c[d] >= need_eq) break;
-            above += c[d];
+  // ---- threshold: a row is kept if it is protected (key 0), if its key > prefix, or if its key == prefix and its rank among
+  // such rows, in row order, lies in [eq_lo, eq_lo + need_eq).
+  uint32_t prefix = need == 0 ? 0xFFFFFFFFu : 0u;         // no key reaches 0xFFFFFFFF; every candidate's exceeds 0 (need == n_cand)
+  int need_eq = 0, eq_lo = 0;
+  if (need > 0 && need < n_cand) {
+    need_eq = need;
+    if (positional) {
+      // every candidate carries the same key: the first (earliest) or the last (latest) `need` of them in row order are
+      // kept by the rank rule alone, no pass over the keys is needed
+      prefix = 1u;
+      eq_lo = rule.order == kSelLatest ? n_cand - need : 0;
+    } else {
+      // radix select of the largest `need` keys, a digit of eight bits at a time from the top
+      uint32_t mask = 0;
+#pragma nounroll
+      for (int shift = 24; shift >= 0; shift -= 8) {
+        const int buf = (shift >> 3) & 1 ? 0 : 1;
+        if (shift < 24) {
+          for (int j = tid; j < n; j += kSelThreads) {
+            const uint32_t key = key_at(j);
+            if (key != 0u && (key & mask) == prefix) count_digit(buf, (key >> shift) & 255u);
           }
-          sh_prefix = prefix | ((uint32_t)(4 * lane + d) << shift);
-          sh_need = need_eq - above;                     // still to take among keys with this digit
+          __syncthreads();
         }
+        if (wave == 0) {
+          // lane owns digits 252 - 4 lane .. + 3, so that lanes count from the top digit down
+          int4 c = {0, 0, 0, 0};
+#pragma unroll
+          for (int w = 0; w < kHistCopies; ++w) {
+            const int4 t = *(const int4*)&hist[buf][w][252 - 4 * lane];
+            c.x += t.x; c.y += t.y; c.z += t.z; c.w += t.w;
+          }
+          const int mine = c.x + c.y + c.z + c.w, inc = wave_inclusive_sum(mine);
+          int above = inc - mine;                           // keys with a digit of a lower lane
+          // the lane whose range crosses need_eq finds the digit
+          if (above < need_eq && need_eq <= inc) {
+            int d = 3;
+            if (above + c.w < need_eq) { above += c.w; d = 2;
+              if (above + c.z < need_eq) { above += c.z; d = 1;
+                if (above + c.y < need_eq) { above += c.y; d = 0; } } }
+            sh_prefix = prefix | ((uint32_t)(252 - 4 * lane + d) << shift);
+            sh_need = need_eq - above;                     // still to take among keys with this digit
+          }
+        } else {
+          clear_hist(buf ^ 1, tid - 64, kSelThreads - 64);  // last read two barriers ago
+        }
+        __syncthreads();
+        prefix = sh_prefix;
+        need_eq = sh_need;
+        mask |= 255u << shift;
       }
-      __syncthreads();
-      prefix = sh_prefix;
-      need_eq = sh_need;
-      mask |= 255u << shift;
-      __syncthreads();
     }
-  } else if (need == 0) {
-    prefix = 0xFFFFFFFFu; mask = 0xFFFFFFFFu; need_eq = 0;   // no candidate passes (keys never reach 0xFFFFFFFF+)
-  } else {
-    prefix = 0; mask = 0xFFFFFFFFu; need_eq = 0;             // need == n_cand: every candidate key (> 0) passes
   }
-  // keep candidate j  <=>  key > prefix, or key == prefix and it is among the first need_eq such rows.
-  const bool take_all = (need == n_cand), take_none = (need == 0);
 
   // ---- flags and ordered output.  Thread t owns the contiguous rows [t*per, (t+1)*per).
-  auto keeps = [&](uint32_t key, int& e) __attribute__((always_inline)) -> bool {
-    if (key == 0u) return true;                            // protected
-    if (take_all) return true;
-    if (take_none) return false;
-    if (key > prefix) return true;
-    if (key == prefix) { const bool kp = e >= eq_lo && e < eq_lo + need_eq; ++e; return kp; }
-    return false;
-  };
   if constexpr (KEYS_IN_LDS) {
-    // The thread's rows come out of LDS once, 16 bytes per read (`per` is rounded up to a multiple of four, so every
-    // thread starts on a 16-byte boundary; word-by-word reads at a stride of `per` words would pile a wave's lanes
-    // on a few banks).  One scan carries both running counts: the rows kept for sure (protected, or above the
-    // threshold) in the low half and the rows equal to the threshold in the high half - either total is at most
-    // kSelLdsKeys = 2^15, so the halves do not run into each other.
-    constexpr int kMaxPer = kSelLdsKeys / kSelThreads;
-    static_assert(kMaxPer % 4 == 0 && kSelLdsKeys <= 32768, "packed scan");
+    // 16 bytes per read (`per` is rounded up to a multiple of four, so every thread starts on a 16-byte boundary; word-by-word
+    // reads at a stride of `per` words would pile a wave's lanes on a few banks).  One scan carries both running counts: the
+    // rows kept for sure (protected, or above the threshold) in the low half and the rows equal to the threshold in the high
+    // half - either total is at most kSelLdsKeys = 2^15, so the halves do not run into each other.
+    static_assert(kSelLdsKeys <= 32768, "packed scan");
     const int per = ((n + kSelThreads - 1) / kSelThreads + 3) & ~3;
-    const int j_lo = tid * per;
-    uint32_t kr[kMaxPer];
+    const int j_lo = tid * per, j_hi = j_lo + per < n ? j_lo + per : n;
+    auto read4 = [&](uint32_t (&k4)[4], int j) __attribute__((always_inline)) {
+      if (j + 3 < n) {
+        const uint4 v = *(const uint4*)(keys + j);
+        k4[0] = v.x; k4[1] = v.y; k4[2] = v.z; k4[3] = v.w;
+      } else {
 #pragma unroll
-    for (int i = 0; i < kMaxPer; i += 4) {
-      if (i < per) {
-        const int j = j_lo + i;
-        if (j + 3 < n) {
-          const uint4 v = *(const uint4*)(keys + j);
-          kr[i] = v.x; kr[i + 1] = v.y; kr[i + 2] = v.z; kr[i + 3] = v.w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) kr[i + e] = (j + e < n) ? keys[j + e] : 0u;
-        }
+        for (int e = 0; e < 4; ++e) k4[e] = j + e < n ? keys[j + e] : 0u;
       }
-    }
-    int sure = 0, eq = 0;
+    };
+    uint32_t counts = 0;
+#pragma nounroll
+    for (int j = j_lo; j < j_hi; j += 4) {
+      uint32_t k4[4];
+      read4(k4, j);
 #pragma unroll
-    for (int i = 0; i < kMaxPer; ++i) {
-      if (i < per && j_lo + i < n) {
-        const uint32_t key = kr[i];
-        const bool cand = key != 0u;
-        eq += (cand && !take_all && !take_none && key == prefix) ? 1 : 0;
-        sure += (!cand || take_all || (!take_none && key > prefix)) ? 1 : 0;
-      }
+      for (int e = 0; e < 4; ++e)
+        if (j + e < n) counts += k4[e] == 0u || k4[e] > prefix ? 1u : k4[e] == prefix ? 0x10000u : 0u;
     }
-    int dummy;
-    const uint32_t before = (uint32_t)block_exclusive_scan((int)(((uint32_t)eq << 16) | (uint32_t)sure), wave_tot, dummy);
+    const uint32_t before = (uint32_t)block_exclusive_scan((int)counts, wave_a);
     const int eq_before = (int)(before >> 16), sure_before = (int)(before & 0xFFFFu);
     const int eq_kept_before = eq_before - eq_lo < 0 ? 0 : (eq_before - eq_lo < need_eq ? eq_before - eq_lo : need_eq);
-    int e = eq_before, o = sure_before + eq_kept_before;
+    int e_rank = eq_before, o = sure_before + eq_kept_before;
+#pragma nounroll
+    for (int j = j_lo; j < j_hi; j += 4) {
+      uint32_t k4[4];
+      read4(k4, j);
 #pragma unroll
-    for (int i = 0; i < kMaxPer; ++i) {
-      if (i < per && j_lo + i < n) {
-        if (keeps(kr[i], e)) {
-          if (o < k_keep) keep_idx[out0 + o] = row0 + j_lo + i;   // o < k_keep always unless k_keep < #protected
+      for (int e = 0; e < 4; ++e) {
+        bool keep = k4[e] == 0u || k4[e] > prefix;
+        if (!keep && k4[e] == prefix) { keep = e_rank >= eq_lo && e_rank < eq_lo + need_eq; ++e_rank; }
+        if (j + e < n && keep) {
+          if (o < k_keep) keep_idx[out0 + o] = row0 + j + e;   // o < k_keep always unless k_keep < #protected
           ++o;
         }
       }
@@ -296,22 +324,23 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
   } else {
     const int per = (n + kSelThreads - 1) / kSelThreads;
     const int j_lo = tid * per, j_hi = (j_lo + per < n) ? j_lo + per : n;
-    auto key_at = [&](int j) __attribute__((always_inline)) -> uint32_t {
-      return prot[row0 + j] ? 0u : cand_key(rule, scores, sample_key, row0, n, j);
+    auto keeps = [&](uint32_t key, int& e) __attribute__((always_inline)) -> bool {
+      if (key == 0u || key > prefix) return true;
+      if (key == prefix) { const bool kp = e >= eq_lo && e < eq_lo + need_eq; ++e; return kp; }
+      return false;
     };
     int eq_cnt = 0;
     for (int j = j_lo; j < j_hi; ++j) {
       const uint32_t key = key_at(j);
       eq_cnt += (key != 0u && key == prefix) ? 1 : 0;
     }
-    int dummy;
-    const int eq_before = block_exclusive_scan(eq_cnt, wave_tot, dummy);
+    const int eq_before = block_exclusive_scan(eq_cnt, wave_a);
     int keep_cnt = 0;
     {
       int e = eq_before;
       for (int j = j_lo; j < j_hi; ++j) keep_cnt += keeps(key_at(j), e) ? 1 : 0;
     }
-    const int keep_before = block_exclusive_scan(keep_cnt, wave_tot, dummy);
+    const int keep_before = block_exclusive_scan(keep_cnt, wave_b);
     int e = eq_before, o = keep_before;
     for (int j = j_lo; j < j_hi; ++j) {
       if (keeps(key_at(j), e)) {

@@ -79,3 +79,36 @@ def test_global_selectors_on_a_sample_longer_than_the_lds_key_buffer(sel_g):
         assert st[f"x_rel_l2_{b}"] <= 2e-5, st
     if sel_g == orc.RANDOM:
         assert not np.array_equal(kept[0][kept[0] < 900][:20], kept[1][:20])
+
+
+@pytest.mark.parametrize("heads", [1, 16, 17, 40])
+def test_score_finish_in_the_selection_at_the_edges_of_its_steps(heads):
+    """The selection finishes the score sixteen heads of 1024 rows at a time: head counts around sixteen, samples around a wave
+    and around one, two and four rounds of the workgroup, ragged.  Against the separate finishing kernel, bit for bit."""
+    m = fi.Model(1, 128, heads, 1, 64, 128, 1.0e4, 1e-6, "f32")
+    lens = [64, 65, 1023, 1024, 1025, 2049, 4101, 3]
+    w = fi.Workload("steps", m, [[(fi.VIDEO, n - 2), (fi.TEXT, 2)] for n in lens], [fi.Prune(0, fi.FINE, 0.6)], seed=67)
+    dec = make_decoder(m, [fi.layer_weights(m, 0, 5)])
+    spans, offs = fi.span_table(w)
+    x = dev(fi.embeddings(w), "f32")
+    res = []
+    try:
+        for fused in (1, 0):
+            fa.fastav_set_option(fa.OPT_FUSED_SCORE_SELECT, fused)
+            o = dec.fastav_prefill(x, fi.cu_seqlens(w), spans, offs, prune_tuples(w), 1, want_trace=True)
+            torch.cuda.synchronize()
+            res.append([o["prune_scores"][0].clone(), o["prune_keep_idx"][0].clone(), o["x_out"].clone()])
+    finally:
+        fa.fastav_set_option(fa.OPT_FUSED_SCORE_SELECT, 1)
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+    assert float(res[0][0].min()) > 0.0
+    cu, s, at = fi.cu_seqlens(w), res[0][0].cpu().numpy(), 0
+    for b, n in enumerate(lens):                                 # the kept video rows are the largest scores, ties to the front
+        sb = s[cu[b]:cu[b + 1]]
+        assert abs(float(sb.sum()) - 1.0) <= 1e-4                # 40 additions and an exp per term, each 2^-24: 3e-6; l the same
+        k = orc.keep_count(n, 0.6, 2)
+        prot = np.zeros(n, bool); prot[-2:] = True
+        want = orc.select_keep(sb, prot, k) + cu[b]
+        assert np.array_equal(res[0][1].cpu().numpy()[at:at + k], want), b
+        at += k
