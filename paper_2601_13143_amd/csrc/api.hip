@@ -491,9 +491,13 @@ fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, cons
   const bool f32_fused = m.dtype == FASTAV_F32 && m.hidden % 4 == 0 && ceil_div(T0, 32) <= 65535;
   void* rope_tab = m.dtype == FASTAV_BF16 || f32_fused ? (void*)(base + ws.rope_table) : nullptr;
   const bool one_setup = outputs_direct && prefill_begin_fits(n_stages, B, in->span_offsets[B]);
+  // the first layer's normalisation rides along unless a prune comes before it
+  const bool first_norm = one_setup && !(n_prunes > 0 && prunes[0].layer == 0 && prunes[0].kind == FASTAV_GLOBAL) &&
+                          prefill_begin_norms(m.hidden, m.dtype, in->x, resid[0], h->w[0].g_attn, hn);
   if (one_setup) {
     FASTAV_TRY(launch_prefill_begin(PrefillSetup{cu_host.data(), n_stages, in->span_offsets, in->spans, B, n_last, m.hidden, m.dtype, T0, in->x, resid[0],
-                                                 cu_dev, out->cu_seqlens_out, pos[0], prot[0], rope_tab, max_len0, m.head_dim, m.rope_base}, s));
+                                                 cu_dev, out->cu_seqlens_out, pos[0], prot[0], rope_tab, max_len0, m.head_dim, m.rope_base,
+                                                 h->w[0].g_attn, first_norm ? hn : nullptr, m.rms_eps}, s));
   } else {
     FASTAV_TRY(upload_small(cu_dev, cu_host.data(), cu_host.size() * 4, s));
     FASTAV_TRY(upload_small(span_off_dev, in->span_offsets, (size_t)(B + 1) * 4, s));
@@ -535,7 +539,7 @@ fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, cons
     const bool side = fine_scored && n_last == 1;
 
     // the previous layer's down projection may have left its split-K partial sums to this normalisation
-    if (!f32_fused) FASTAV_TRY(launch_rmsnorm(resid[cur], W.g_attn, hn, Tl, m.hidden, m.rms_eps, m.dtype, s, &pend_down));
+    if (!f32_fused && !(l == 0 && first_norm)) FASTAV_TRY(launch_rmsnorm(resid[cur], W.g_attn, hn, Tl, m.hidden, m.rms_eps, m.dtype, s, &pend_down));
     pend_down = SplitKPending();
     void* const k_out = out->kv_out ? out->kv_out[2 * l] : nullptr;
     void* const v_out = out->kv_out ? out->kv_out[2 * l + 1] : nullptr;

@@ -80,7 +80,8 @@ fastav_status_t launch_init_tokens(const int32_t* cu, const int32_t* span_offset
                                    int batch, int64_t T, int max_seqlen, int n_last, int32_t* pos, uint8_t* prot,
                                    hipStream_t s);
 // A prefill's set-up in one launch, where schedule and spans fit the kernel arguments: prefix sums of all stages to cu (the last
-// stage's also to cu_out), positions, protected rows, the embeddings as fp32, and (table != nullptr) the rotary table.
+// stage's also to cu_out), positions, protected rows, the embeddings as fp32, (table != nullptr) the rotary table and
+// (norm != nullptr, where prefill_begin_norms says so) norm = rmsnorm(x; gain, eps), the input of the first projection.
 struct PrefillSetup {
   const int32_t* host_cu; int n_stages;             // [n_stages][batch + 1]
   const int32_t* host_span_offsets; const fastav_span_t* host_spans;
@@ -90,7 +91,9 @@ struct PrefillSetup {
   int32_t *cu, *cu_out, *pos;
   uint8_t* prot;
   void* table; int n_pos, head_dim; float base;
+  const void* gain; void* norm; float eps;
 };
+bool prefill_begin_norms(int hidden, int dtype, const void* x, const void* resid, const void* gain, const void* norm);
 bool prefill_begin_fits(int n_stages, int batch, int n_spans);
 fastav_status_t launch_prefill_begin(const PrefillSetup& c, hipStream_t s);
 fastav_status_t launch_to_f32(const void* x, float* y, int64_t n, int dtype, hipStream_t s);

@@ -94,6 +94,9 @@ fastav_status_t launch_to_f32(const void* x, float* y, int64_t n, int dtype, hip
 // spans.  Workgroups in order: one for the prefix sums (to the workspace, the last stage's also to the caller), init_wg for
 // positions and protected rows, f32_wg for the embeddings in fp32, the rest for the rotary table.
 // With the three output copies gone as well: 512 fp32 tokens, 4 layers 194 -> 179 us; one 7B layer at 2048 tokens 656 -> 629.
+// NV > 0 (bf16, rows of up to 1024 * NV elements): a workgroup of the embeddings takes one row, and the first layer's
+// normalisation is made from the registers it passes through instead of by a launch that reads the fp32 rows back (2048 rows
+// of 4096: 13.6 + 11.0 us for two launches, 16.0 for one); sums and products are k_rmsnorm_reg's, in its order.
 struct PrefillBegin {
   uint32_t n_cu, last_cu, span_off_at, spans_at;   // words of all prefix sums, first of the last stage's, of the span offsets, of the spans
   int batch, n_last, init_wg, f32_wg, n_pos, half;
@@ -104,9 +107,13 @@ struct PrefillBegin {
   uint8_t* prot;
   float2* table;
   double neg_log2_base_2_over_dh;
+  const void* gain;
+  void* norm;
+  int hidden;
+  float eps;
 };
 // elements per thread of the conversion: 16 bytes of input
-template <typename T>
+template <typename T, int NV>
 __global__ __launch_bounds__(256) void k_prefill_begin(PrefillBegin a, SmallPayload p) {
   int wg = blockIdx.x;
   const int tid = threadIdx.x;
@@ -135,7 +142,44 @@ __global__ __launch_bounds__(256) void k_prefill_begin(PrefillBegin a, SmallPayl
     return;
   }
   wg -= a.init_wg;
-  if (wg < a.f32_wg) {
+  if (NV > 0 && wg < a.f32_wg) {
+    __shared__ float red[4];
+    const int n4 = a.hidden >> 2;
+    const bf16x4_t* xr = (const bf16x4_t*)a.x + (int64_t)wg * n4;
+    f32x4_t* rr = (f32x4_t*)a.resid + (int64_t)wg * n4;
+    bf16x4_t* yr = (bf16x4_t*)a.norm + (int64_t)wg * n4;
+    constexpr int R = NV > 0 ? NV : 1;
+    f32x4_t v[R];
+    bf16x4_t gv[R];
+    float ss = 0.f;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      const int i = tid + u * 256;
+      bf16x4_t t = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
+      gv[u] = t;
+      if (i < n4) { t = xr[i]; gv[u] = ((const bf16x4_t*)a.gain)[i]; }
+      v[u] = f32x4_t{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
+    }
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      if (tid + u * 256 < n4) rr[tid + u * 256] = v[u];
+      ss += v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2] + v[u][3] * v[u][3];
+    }
+    ss = wave_sum(ss);
+    if ((tid & 63) == 0) red[tid >> 6] = ss;
+    __syncthreads();
+    const float tot = red[0] + red[1] + red[2] + red[3];
+    const float r = 1.0f / sqrtf(tot / (float)a.hidden + a.eps);
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      bf16x4_t o;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o[c] = (bf16_t)(v[u][c] * r * (float)gv[u][c]);
+      if (tid + u * 256 < n4) yr[tid + u * 256] = o;
+    }
+    return;
+  }
+  if (NV == 0 && wg < a.f32_wg) {
     constexpr int V = 16 / sizeof(T);
     const int64_t step = (int64_t)a.f32_wg * 256 * V;
     for (int64_t i = ((int64_t)wg * 256 + tid) * V; i < a.n_elems; i += step) {
@@ -162,6 +206,10 @@ bool prefill_begin_fits(int n_stages, int batch, int n_spans) {
   return (int64_t)(n_stages + 1) * (batch + 1) + 3 * (int64_t)n_spans <= (int64_t)(sizeof(SmallPayload) / 4);
 }
 
+bool prefill_begin_norms(int hidden, int dtype, const void* x, const void* resid, const void* gain, const void* norm) {
+  return dtype == FASTAV_BF16 && hidden % 4 == 0 && hidden <= 8192 && ((uintptr_t)x | (uintptr_t)gain | (uintptr_t)norm) % 8 == 0 && (uintptr_t)resid % 16 == 0;
+}
+
 fastav_status_t launch_prefill_begin(const PrefillSetup& c, hipStream_t s) {
   SmallPayload p;
   PrefillBegin a;
@@ -179,13 +227,17 @@ fastav_status_t launch_prefill_begin(const PrefillSetup& c, hipStream_t s) {
   a.batch = c.batch; a.n_last = c.n_last; a.n_elems = c.T * c.hidden;
   a.init_wg = (int)ceil_div(c.T, 256);
   const int64_t wgs = ceil_div(a.n_elems, 256 * (c.dtype == FASTAV_BF16 ? 8 : 4));
-  a.f32_wg = (int)(wgs < 16384 ? wgs : 16384);
+  a.f32_wg = c.norm != nullptr ? (int)c.T : (int)(wgs < 16384 ? wgs : 16384);
+  a.gain = c.gain; a.norm = c.norm; a.hidden = c.hidden; a.eps = c.eps;
   a.n_pos = c.table != nullptr ? c.n_pos : 0; a.half = c.head_dim / 2;
   a.x = c.x; a.resid = c.resid; a.cu = c.cu; a.cu_out = c.cu_out; a.pos = c.pos; a.prot = c.prot; a.table = (float2*)c.table;
   a.neg_log2_base_2_over_dh = -log2((double)c.base) * 2.0 / (double)c.head_dim;
   const unsigned blocks = (unsigned)(1 + a.init_wg + a.f32_wg + ceil_div((int64_t)a.n_pos * a.half, 256));
-  if (c.dtype == FASTAV_BF16) hipLaunchKernelGGL(k_prefill_begin<bf16_t>, dim3(blocks), dim3(256), 0, s, a, p);
-  else hipLaunchKernelGGL(k_prefill_begin<float>, dim3(blocks), dim3(256), 0, s, a, p);
+#define FASTAV_BEGIN(TT, NV) hipLaunchKernelGGL((k_prefill_begin<TT, NV>), dim3(blocks), dim3(256), 0, s, a, p)
+  if (c.norm != nullptr) { if (c.hidden <= 4096) FASTAV_BEGIN(bf16_t, 4); else FASTAV_BEGIN(bf16_t, 8); }
+  else if (c.dtype == FASTAV_BF16) FASTAV_BEGIN(bf16_t, 0);
+  else FASTAV_BEGIN(float, 0);
+#undef FASTAV_BEGIN
   return check_launch("prefill_begin");
 }
 

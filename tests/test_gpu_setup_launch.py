@@ -49,6 +49,15 @@ def test_setup_and_outputs(batch, prunes, dtype, tol):
     _check(w, weights, x, _run(make_decoder(w.model, weights), w, dev(x, dtype)), tol)
 
 
+@pytest.mark.parametrize("hidden", [64, 1028, 4096, 4100, 8192, 8196])
+@pytest.mark.parametrize("prune", [[], [fi.Prune(0, fi.GLOBAL, 0.5)]])
+def test_first_normalisation_in_the_setup(hidden, prune):
+    """The first layer's RMSNorm is made by the set-up for rows of up to 4096 and up to 8192 elements, by its own launch beyond and
+    where a prune comes before it; rows that end inside a workgroup's last round of loads."""
+    w, weights, x = _case([[(fi.VIDEO, 30), (fi.TEXT, 3)], [(fi.AUDIO, 7), (fi.TEXT, 2)]], prune, "bf16", hidden=hidden)
+    _check(w, weights, x, _run(make_decoder(w.model, weights), w, dev(x, "bf16")), 1e-2)
+
+
 def test_output_over_the_input():
     """x_out in the memory of x (an fp32 model without a prune): the residual stream then stays in the workspace."""
     w, weights, x = _case([[(fi.VIDEO, 40), (fi.TEXT, 9)]], [], "f32")
