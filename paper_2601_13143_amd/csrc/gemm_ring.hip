@@ -336,11 +336,19 @@ struct RingPlan { int bm, bn, splits; };
 //   128 -> 104; 16512 x 2048 77-79 -> 61-66, 20480 x 5120 178-189 -> 147-156; in one round they win, 89 against 95),
 //   and not with half of the CUs idle (200 rows, 6144 gate/up columns in 96 tiles: 24 -> 34).
 // - residual products, K shared out over one round of workgroups: 128 columns where a share then keeps 16 stages or
-//   more (down, 82 rows 49 + 4.7 -> 29 + 4.9 and 39 + 4.6 -> 26 + 4.8, 232 rows 54 + 6 -> 40 + 7 and 44 + 7 -> 35 + 7;
-//   beyond 256 rows both take 65), else 64 columns and fewer, longer shares (O, 116 rows 17 + 4.6 -> 11 + 4 and
+//   more (down, 82 rows 49 + 4.7 -> 29 + 4.9 and 39 + 4.6 -> 26 + 4.8, 232 rows 54 + 6 -> 40 + 7 and 44 + 7 -> 35 + 7),
+//   else 64 columns and fewer, longer shares (O, 116 rows 17 + 4.6 -> 11 + 4 and
 //   18 + 4.4 -> 13 + 4, 331 rows 19 + 7 -> 18 + 4 and 25 + 9 -> 20 + 5).  Not: more than 48 tile columns of 128 and 193 rows
 //   or more (8192 x 12288, 224 rows: 72 -> 74) or long shares (8192 x 28672, 112 stages, 100 / 160 / 192 rows: 120 -> 113,
 //   126 -> 132, 132 -> 142); 193-256 rows whose 64-column tiles leave no second share (5120 x 5120: 33 -> 40).
+// - the same beyond 256 rows: several tile rows of 128 x 128 where two shares or more keep 24 to 47 stages, fewer by as much as
+//   CUs stay idle, else of 192 x 128 where they keep 16 to 31 (with the sum of the partial tiles, 331 / 460 / 576 rows:
+//   4096 x 4096 33 / 38 / - -> 30 / 31 / -, 1024 x 16384 52 / 54 / 53 -> 27 / 29 / 34, 2560 x 6912 32 / 35 / 39 -> 26 / 32 / 36,
+//   2048 x 8192 35 / 36 / 39 -> 27 / 30 / 35, 4608 x 4608 35 / - / - -> 32 / - / -, 3584 x 3584 - / 30 / 36 -> - / 28 / 31; idle
+//   CUs: 40 stages on 192 of them, 4096 x 5120, 34 -> 35 at 331 rows, and on all of them 38 -> 33 at 400).  Longer shares
+//   gain less and less (192 x 128, 331 rows: 4096 x 14336, 56 stages, 64 -> 59 to 62; 8192 x 8192, 64 stages, 68 -> 69;
+//   3584 x 18944, 74 stages, 69 -> 69 to 74), one share nothing (4096 x 4096, 576 rows: 41 -> 42), and shorter ones lose to
+//   64-column tiles (2048 x 2048, 8 stages: 16.1 -> 16.7).
 // - without room for the partial tiles, 64-row tiles and 128 x 64 win all the same (4096 x 14336, 64 rows: 122 -> 74;
 //   4096 x 4096, 100 rows 41 -> 29, 224 rows 41 -> 30), the others do not (160 rows 39 -> 36 and 49 -> 52; 128 columns:
 //   4096 x 14336, 224 rows 131 -> 193); those leave unless half of their shares find room.
@@ -353,6 +361,20 @@ static RingPlan ring_plan(int m, int n, int k, int epilogue, size_t room) {
     if (m <= rows[i]) one = rows[i];
   auto tiles = [&](int bm, int cols, int bn) { return (int64_t)((m + bm - 1) / bm) * ((cols + bn - 1) / bn); };
   if (epilogue == FASTAV_EPI_RESADD) {
+    auto cut = [&](RingPlan p) {                        // to the shares whose partial tiles find room
+      const int64_t fits = (int64_t)(room / ((size_t)m * n * sizeof(float)));
+      if (p.splits > fits) {
+        if (!(p.bm == 64 || (p.bm == 128 && p.bn == 64)) && fits * 2 < p.splits) return no;
+        p.splits = fits < 1 ? 1 : (int)fits;
+      }
+      return p;
+    };
+    for (int bm = 128; one == 0 && bm <= 192; bm += 64) {
+      const int64_t t = tiles(bm, n, 128), fill = kNumCUs / t;
+      const int splits = (int)(fill < 16 ? fill : 16);
+      const int stages = splits >= 2 ? k / 64 / splits : 0;
+      if (bm == 128 ? stages >= 24 && stages * kNumCUs < 48 * t * splits : stages >= 16 && stages < 32) return cut({bm, 128, splits});
+    }
     const int64_t t128 = tiles(one ? one : 256, n, 128);
     const bool long_k = t128 <= kNumCUs && (k / 64) / (kNumCUs / t128) >= 16;
     if (long_k && one == 0) return no;
@@ -369,12 +391,7 @@ static RingPlan ring_plan(int m, int n, int k, int epilogue, size_t room) {
       if (splits > 16) splits = 16;
       p = {bm, 64, splits < 1 ? 1 : splits};
     }
-    const int64_t fits = (int64_t)(room / ((size_t)m * n * sizeof(float)));
-    if (p.splits > fits) {
-      if (!(p.bm == 64 || (p.bm == 128 && p.bn == 64)) && fits * 2 < p.splits) return no;
-      p.splits = fits < 1 ? 1 : (int)fits;
-    }
-    return p;
+    return cut(p);
   }
   const int cols = epilogue == FASTAV_EPI_SWIGLU ? 2 * n : n;
   for (int i = 0; i < 3; ++i) {
