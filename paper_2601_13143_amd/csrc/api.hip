@@ -414,6 +414,33 @@ fastav_status_t fastav_workspace_bytes(fastav_handle_t h, int64_t max_total_toke
 
 #define FASTAV_TRY(expr) do { fastav_status_t st__ = (expr); if (st__ != FASTAV_OK) return st__; } while (0)
 
+// Whether x_out, kept_pos_out and cu_seqlens_out share no byte with a buffer that the call reads or writes before its end: a
+// caller may place them over one of those (x in particular), because they are the call's last writes.
+static bool outputs_stand_alone(const fastav_model_t& m, const fastav_batch_t* in, const fastav_prune_t* prunes, int n_prunes, const int64_t* T_stage,
+                                const void* workspace, size_t workspace_bytes, const fastav_prefill_out_t* out) {
+  const size_t es = m.dtype == FASTAV_BF16 ? 2 : 4, hidden = (size_t)m.hidden, kd = (size_t)m.n_kv_heads * m.head_dim;
+  const struct { const void* p; size_t bytes; } outs[3] = {{out->x_out, (size_t)T_stage[n_prunes] * hidden * 4},
+                                                           {out->kept_pos_out, (size_t)T_stage[n_prunes] * 4},
+                                                           {out->cu_seqlens_out, (size_t)(in->batch + 1) * 4}};
+  auto apart = [&](const void* p, size_t bytes) {
+    for (const auto& o : outs)
+      if (p && (uintptr_t)o.p < (uintptr_t)p + bytes && (uintptr_t)p < (uintptr_t)o.p + o.bytes) return false;
+    return true;
+  };
+  bool ok = apart(in->x, (size_t)T_stage[0] * hidden * es) && apart(workspace, workspace_bytes);
+  for (int i = 0; i < n_prunes; ++i)
+    ok = ok && (!out->prune_scores_out || apart(out->prune_scores_out[i], (size_t)T_stage[i] * 4)) &&
+         (!out->prune_keep_idx_out || apart(out->prune_keep_idx_out[i], (size_t)T_stage[i + 1] * 4));
+  int stage = 0;
+  for (int l = 0; ok && l < m.n_layers; ++l) {
+    while (stage < n_prunes && prunes[stage].layer == l) ++stage;
+    const size_t rows = (size_t)T_stage[stage];
+    ok = (!out->kv_out || (apart(out->kv_out[2 * l], rows * kd * es) && apart(out->kv_out[2 * l + 1], rows * kd * es))) &&
+         (!out->layer_x_out || apart(out->layer_x_out[l], rows * hidden * 4));
+  }
+  return ok;
+}
+
 fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, const fastav_prune_t* prunes,
                                int32_t n_prunes, int32_t n_last, void* workspace, size_t workspace_bytes,
                                const fastav_prefill_out_t* out, void* stream) {
@@ -480,11 +507,11 @@ fastav_status_t fastav_prefill(fastav_handle_t h, const fastav_batch_t* in, cons
   void* gscr = ws.gemm_scratch_bytes ? (void*)(base + ws.gemm_scratch) : nullptr;
 
   // The residual stream and the positions of the last stage live in the caller's outputs: the last prune compacts into them
-  // (without a prune the set-up writes them), and nothing is left to copy at the end.  Where x_out lies over x, or the positions
-  // at odd addresses, they stay in the workspace and are copied as the last step.
-  const char *x0 = (const char*)in->x, *x1 = x0 + (size_t)T0 * m.hidden * (m.dtype == FASTAV_BF16 ? 2 : 4);
-  const char *y0 = (const char*)out->x_out, *y1 = y0 + (size_t)T_stage[n_stages - 1] * m.hidden * 4;
-  const bool outputs_direct = (y1 <= x0 || x1 <= y0) && (uintptr_t)out->kept_pos_out % 4 == 0 && (uintptr_t)out->cu_seqlens_out % 4 == 0;
+  // (without a prune the set-up writes them), and nothing is left to copy at the end.  Where one of the three outputs shares
+  // memory with another buffer of the call, or the positions or prefix sums lie at odd addresses, they stay in the workspace
+  // and are copied as the last step.
+  const bool outputs_direct = (uintptr_t)out->kept_pos_out % 4 == 0 && (uintptr_t)out->cu_seqlens_out % 4 == 0 &&
+                              outputs_stand_alone(m, in, prunes, n_prunes, T_stage.data(), workspace, ws.total, out);
   if (n_prunes == 0 && outputs_direct) { resid[0] = out->x_out; pos[0] = out->kept_pos_out; }
   // rotary (cos, sin) of every original position, once: tokens keep their positions through every prune
   // fp32 models: RMSNorm and RoPE ride in the projections (16-byte loads of the rows and gains)

@@ -69,6 +69,37 @@ def test_output_over_the_input():
     assert torch.equal(got["x_out"], want["x_out"]) and torch.equal(got["kept_pos"], want["kept_pos"]) and torch.equal(got["cu_seqlens_out"], want["cu_seqlens_out"])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("prunes", [[], [fi.Prune(0, fi.FINE, 0.5)], [fi.Prune(0, fi.GLOBAL, 0.7), fi.Prune(1, fi.FINE, 0.6)]])
+@pytest.mark.parametrize("shared", ["kept_pos in x", "cu in x", "kept_pos over the last kept rows", "x_out over a cache", "kept_pos in a layer's output"])
+def test_outputs_that_share_memory_with_another_buffer(shared, prunes, dtype):
+    """The hidden states, positions and prefix sums are the call's last writes, whatever buffer of the call their memory was before."""
+    w, weights, x = _case([[(fi.VIDEO, 300), (fi.TEXT, 9)], [(fi.AUDIO, 55), (fi.TEXT, 3)]], prunes, dtype, hidden=64)
+    dec = make_decoder(w.model, weights)
+    xd = dev(x, dtype)
+    want = _run(dec, w, xd.clone(), want_kv=True, want_trace=True, want_layers=True)
+    o = {k: v if not torch.is_tensor(v) else torch.empty_like(v) for k, v in want.items()}
+    o["kv"] = [tuple(torch.empty_like(t) for t in kv) for kv in want["kv"]]
+    o["prune_keep_idx"] = [torch.empty_like(t) for t in want["prune_keep_idx"]]
+    o["layer_x"] = [torch.empty_like(t) for t in want["layer_x"]]
+    words = lambda t, n: t.view(-1).view(torch.int32)[-n:]
+    if shared == "kept_pos in x":
+        o["kept_pos"] = words(xd, o["kept_pos"].numel())
+    elif shared == "cu in x":
+        o["cu_seqlens_out"] = words(xd, o["cu_seqlens_out"].numel())
+    elif shared == "kept_pos over the last kept rows":
+        o["kept_pos"] = (o["prune_keep_idx"] or [o["kept_pos"]])[-1]
+    elif shared == "x_out over a cache":
+        k = torch.empty(max(want["kv"][0][0].numel() * want["kv"][0][0].element_size(), o["x_out"].numel() * 4) // 4, dtype=torch.float32, device="cuda")
+        o["x_out"] = k[:o["x_out"].numel()].view(o["x_out"].shape)
+        o["kv"][0] = (k.view(want["kv"][0][0].dtype)[:want["kv"][0][0].numel()].view(want["kv"][0][0].shape), o["kv"][0][1])
+    else:
+        o["kept_pos"] = words(o["layer_x"][0], o["kept_pos"].numel())
+    got = _run(dec, w, xd, outputs=o)
+    for k in ("x_out", "kept_pos", "cu_seqlens_out"):
+        assert torch.equal(got[k], want[k]), k
+
+
 @pytest.mark.parametrize("batch", [1, 32, 33])
 @pytest.mark.parametrize("scored", [True, False])
 def test_select_with_prefix_sums_in_the_arguments(batch, scored):
