@@ -790,6 +790,7 @@ fastav_status_t fastav_select_gather(const float* scores, const uint8_t* protect
   if (n_tensors > 0 && (!src || !dst || !row_bytes)) return fail(FASTAV_EINVAL, "src/dst/row_bytes is NULL");
   if (workspace_bytes < fastav_select_workspace_bytes(batch) || ((uintptr_t)workspace % 4))
     return fail(FASTAV_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, fastav_select_workspace_bytes(batch));
+  if ((uintptr_t)cu_seqlens_out % 4) return fail(FASTAV_EINVAL, "cu_seqlens_out must be 4-byte aligned");
   if (cu_seqlens[0] != 0) return fail(FASTAV_EINVAL, "cu_seqlens[0] must be 0");
   std::vector<int32_t> cu_out(batch + 1);
   cu_out[0] = 0;

@@ -220,13 +220,17 @@ def test_score_and_select_reject_bad_arguments():
     cu = np.array([0, 10, 30], dtype=np.int32)
     kc = np.array([5, 25], dtype=np.int32)
     ip = lambda a: a.ctypes.data_as(C.POINTER(C.c_int32))
-    g = lambda **k: lib.fastav_select_gather(4096, k.get("prot", 4096), ip(k.get("cu", cu)), ip(k.get("kc", kc)), 2, k.get("nt", 0),
-                                             None, None, None, 4096, 4096, 4096, k.get("wsb", 256), None)
+    g = lambda **k: lib.fastav_select_gather(4096, k.get("prot", 4096), ip(k.get("cu", cu)), ip(k.get("kc", kc)), len(k.get("cu", cu)) - 1,
+                                             k.get("nt", 0), None, None, None, 4096, k.get("cu_out", 4096), 4096, k.get("wsb", 256), None)
     assert g(prot=None) == B.EINVAL
     assert g(kc=np.array([5, 25], dtype=np.int32)) == B.EINVAL and b"exceeds" in lib.fastav_last_error()   # 25 > 20 rows
     assert g(kc=np.array([-1, 2], dtype=np.int32)) == B.EINVAL
     assert g(cu=np.array([0, 10, 5], dtype=np.int32)) == B.EINVAL
     assert g(nt=9) == B.EINVAL and g(nt=1) == B.EINVAL and g(wsb=4, kc=np.array([5, 15], dtype=np.int32)) == B.EWORKSPACE
+    # misaligned prefix sums, with and beyond the 32 samples whose prefix sums travel in the kernel arguments
+    for batch in (1, 2, 32, 33):
+        assert g(cu=np.arange(0, 10 * batch + 1, 10, dtype=np.int32), kc=np.full(batch, 5, dtype=np.int32), cu_out=4098) == B.EINVAL, batch
+        assert b"align" in lib.fastav_last_error()
 
 
 @pytest.mark.parametrize("cfg", [1, 3, 5])
