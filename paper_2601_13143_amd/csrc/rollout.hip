@@ -26,6 +26,7 @@ struct MapArgs {
   float2* stats;                // [Hq][n]: a row's maximum (log2 domain) and the reciprocal of its sum of exp2
   bf16_t* a_out;                // [n, ld]; columns up to n_cols are written
   int64_t ld; int n_cols;
+  bool lines;                   // rows of a_out lie at 16-byte addresses
 };
 
 // Q operand (B of S^T = K Q^T): lane = query l32, k-chunk hf of k-step s.  K operand (A): lane = key l32.
@@ -272,8 +273,8 @@ __global__ __launch_bounds__(HG * 256, 4) void k_attn_map(MapArgs a) {
   if (row >= 64 || q0 + row >= a.n) return;
   const bf16x8_t o = *(const bf16x8_t*)(tile + row * 72 + col);
   bf16_t* dst = a.a_out + (int64_t)(q0 + row) * a.ld + j0 + col;
-  // n_cols is a multiple of 4; a pitch that is no multiple of 8 leaves rows at 8-byte addresses
-  if (a.ld % 8 == 0 && j0 + col + 8 <= a.n_cols) *(bf16x8_t*)dst = o;
+  // n_cols is a multiple of 4; a pitch that is no multiple of 8, or a base off a 16-byte boundary, leaves rows at 8-byte addresses
+  if (a.lines && j0 + col + 8 <= a.n_cols) *(bf16x8_t*)dst = o;
   else {
     if (j0 + col + 4 <= a.n_cols) *(bf16x4_t*)dst = bf16x4_t{o[0], o[1], o[2], o[3]};
     if (j0 + col + 8 <= a.n_cols) *(bf16x4_t*)(dst + 4) = bf16x4_t{o[4], o[5], o[6], o[7]};
@@ -304,6 +305,7 @@ fastav_status_t launch_attention_map(const void* q, int64_t q_stride, const void
   a.q = (const bf16_t*)q; a.k = (const bf16_t*)k; a.qs = q_stride; a.ks = k_stride; a.n = n; a.Hq = Hq; a.Hkv = Hkv;
   a.scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
   a.stats = stats; a.a_out = (bf16_t*)a_out; a.ld = ld; a.n_cols = lower ? (n + 63) / 64 * 64 : n;
+  a.lines = ld % 8 == 0 && (uintptr_t)a_out % 16 == 0;
   // the causal Q K^T products: once for the statistics, once for the map
   ProfScope prof(FASTAV_PROF_ATTENTION, (have_stats ? 1.0 : 2.0) * 2.0 * Hq * dh * (double)n * ((double)n + 1.0) * 0.5, s);
   const dim3 g1((unsigned)Hq, (unsigned)ceil_div(n, 64));

@@ -1,4 +1,6 @@
 """GPU parity of the attention-rollout analysis (Eq. 2-3) against the CPU oracle, through the C ABI."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -150,3 +152,18 @@ def test_rollout_at_the_edges_of_its_tiles(n):
 def test_attention_map_with_more_tiles_than_cus(Hq, Hkv, dh, n):
     """Beyond 256 tiles the heads are dealt over two waves a block instead of four; head counts that no share divides."""
     test_attention_map_matches_oracle(Hq, Hkv, dh, n)
+
+
+@pytest.mark.parametrize("n", [64, 200, 1480, 1476])
+def test_attention_map_into_memory_off_a_16_byte_boundary(n):
+    """The map's rows may lie at 8-byte addresses: the base 8 bytes past a 16-byte boundary, or a pitch that is no multiple of 16 bytes."""
+    m = fa.make_model(1, 64, 4, 2, 64, 64)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    q, k = (torch.randn((n, h, 64), device="cuda", generator=gen).bfloat16() for h in (4, 2))
+    want = fa.fastav_attention_map(m, q, k)
+    buf = torch.full((n * n + 8,), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(fa.lib().fastav_attention_map_workspace_bytes(n, 4), dtype=torch.uint8, device="cuda")
+    fa.binding._check(fa.lib().fastav_attention_map(C.byref(m), q.data_ptr(), q.stride(0), k.data_ptr(), k.stride(0), n, buf.data_ptr() + 8, ws.data_ptr(),
+                                                    ws.numel(), torch.cuda.current_stream().cuda_stream))
+    assert torch.equal(buf[4:-4].view(n, n), want)
+    assert bool((buf[:4] == 7.0).all()) and bool((buf[-4:] == 7.0).all())
