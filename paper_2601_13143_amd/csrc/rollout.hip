@@ -26,6 +26,7 @@ struct MapArgs {
   float2* stats;                // [Hq][n]: a row's maximum (log2 domain) and the reciprocal of its sum of exp2
   bf16_t* a_out;                // [n, ld]; columns up to n_cols are written
   int64_t ld; int n_cols;
+  bool lower;                   // tiles above the diagonal are not written
   bool lines;                   // rows of a_out lie at 16-byte addresses
 };
 
@@ -281,6 +282,84 @@ __global__ __launch_bounds__(HG * 256, 4) void k_attn_map(MapArgs a) {
   }
 }
 
+// The map of a short prompt: a workgroup makes 32 rows x 64 keys, wave w sums heads [w Hq / 8, (w + 1) Hq / 8) with the operands
+// read straight from memory in operand layout.  Bound by latency: there is no copy to wait for and no
+// barrier until the waves' sums meet, and twice as many workgroups as of 64 x 64 tiles.
+// grid (query tiles of 32, key tiles of 64)
+constexpr int kMapWaves = 8;
+template <int DH>
+__global__ __launch_bounds__(kMapWaves * 64) void k_attn_map_short(MapArgs a) {
+  constexpr int NS = DH / 16;
+  __shared__ f32x4_t part[kMapWaves][8][64];            // [wave][16-byte piece kb * 4 + r4][lane]
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int q0 = (int)blockIdx.x * 32, j0 = (int)blockIdx.y * 64;
+  const bool visible = j0 <= q0 + 31;                   // else the tile lies above the diagonal: zeros
+  if (!visible && a.lower) return;
+  if (visible) {
+    const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const int qr = q0 + l32 < a.n ? q0 + l32 : a.n - 1;
+    const int G = a.Hq / a.Hkv;
+    const int h0 = a.Hq * wave / kMapWaves, h1 = a.Hq * (wave + 1) / kMapWaves;
+    float acc[2][16];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[kb][r] = 0.f;
+    bf16x8_t kf[2][NS], qn[NS];
+    float2 sn = make_float2(0.f, 0.f);
+    int g_of = -1;
+    if (h0 < h1) {
+      load_q_frags<DH>(a, qr, h0, hf, qn);
+      sn = a.stats[(int64_t)h0 * a.n + qr];
+    }
+    for (int h = h0; h < h1; ++h) {
+      bf16x8_t qf[NS];
+#pragma unroll
+      for (int st = 0; st < NS; ++st) qf[st] = qn[st];
+      const float m = sn.x, inv_l = sn.y;
+      if (h / G != g_of) {
+        g_of = h / G;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          const int key = j0 + kb * 32 + l32;
+          load_k_frags<DH>(a, key < a.n ? key : a.n - 1, g_of, hf, kf[kb]);
+        }
+      }
+      const int hn = h + 1 < h1 ? h + 1 : h;
+      load_q_frags<DH>(a, qr, hn, hf, qn);
+      sn = a.stats[(int64_t)hn * a.n + qr];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        f32x16_t s = zero16;
+#pragma unroll
+        for (int st = 0; st < NS; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb][st], qf[st], s, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[kb][r] += __builtin_amdgcn_exp2f(fmaf(s[r], a.scale_log2, -m)) * inv_l;
+      }
+    }
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        part[wave][kb * 4 + r4][lane] = f32x4_t{acc[kb][4 * r4], acc[kb][4 * r4 + 1], acc[kb][4 * r4 + 2], acc[kb][4 * r4 + 3]};
+  }
+  __syncthreads();
+  // wave w finishes piece w: keys j0 + (w / 4) * 32 + (w % 4) * 8 + hf * 4 .. + 3 of row q0 + l32
+  const int qi = q0 + l32;
+  if (qi >= a.n) return;
+  f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+  if (visible)
+#pragma unroll
+    for (int w = 0; w < kMapWaves; ++w) v += part[w][wave][lane];
+  const float inv_h = 1.0f / (float)a.Hq;
+  const int key0 = j0 + (wave >> 2) * 32 + (wave & 3) * 8 + hf * 4;
+  bf16x4_t o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (bf16_t)((key0 + e <= qi) ? v[e] * inv_h : 0.f);
+  if (key0 < a.n_cols) *(bf16x4_t*)(a.a_out + (int64_t)qi * a.ld + key0) = o;      // n_cols is a multiple of 4
+}
+
 template <int DH, int HG>
 static fastav_status_t launch_map(const MapArgs& a, unsigned tiles, hipStream_t s) {
   // two stages of the rows per share; the sums and the bf16 tile at the end need less (16 KB a share but the first, 9 KB)
@@ -291,6 +370,25 @@ static fastav_status_t launch_map(const MapArgs& a, unsigned tiles, hipStream_t 
   }
   hipLaunchKernelGGL((k_attn_map<DH, HG>), dim3(tiles), dim3(HG * 256), shmem, s, a);
   return check_launch("attention_map");
+}
+
+// Which of the two: the short form's time goes with the rows it reads (32 per head, 64 per key head and wave), that of the
+// 64 x 64 tiles with their chain of copies (a quarter of the heads and of the key heads).  So heads of 64 are short up to 896
+// tokens, heads of 128 up to 832 where there are fewer heads than waves or many to a key head.  fastav_attention_map with its
+// statistics, us, short / tiles:
+//   tokens            256          512          832          896          960
+//   16/16 of 64    14.0 / 17.3  15.1 / 18.2  17.5 / 19.6  18.8 / 19.8  24.5 / 20.5
+//   64/8  of 64    18.5 / 27.3  22.7 / 31.4  30.7 / 38.0  33.0 / 39.8  45.0 / 41.6
+//   1/1   of 64     8.6 / 10.7   9.7 / 11.8  11.7 / 12.9  12.7 / 13.1  13.4 / 13.6
+//   4/2   of 128   13.7 / 15.7  15.6 / 17.5  19.1 / 19.7  20.7 / 20.1  23.2 / 21.1
+//   32/8  of 128   23.1 / 25.4  25.1 / 27.4  35.5 / 36.5  37.3 / 37.1  50.2 / 39.0
+//   28/4  of 128   22.5 / 23.5  24.5 / 25.5  33.2 / 32.8  36.0 / 34.2  47.7 / 35.2
+//   8/2   of 128   17.2 / 16.9  19.2 / 18.9  22.5 / 21.1  24.2 / 21.4  30.5 / 22.5
+//   16/16 of 128   22.7 / 22.3  24.7 / 24.1  28.6 / 27.1  30.4 / 27.5  42.1 / 28.8
+//   32/32 of 128   33.4 / 30.7  36.4 / 34.3  45.8 / 43.2  47.5 / 43.5  71.2 / 45.4
+// Inside a rollout (a layer with all its launches, 512 tokens): 16/16 of 64 68.5 / 72.0, 32/8 of 128 162.7 / 165.5.
+static bool map_is_short(int n, int Hq, int Hkv, int dh) {
+  return dh == 64 ? n <= 896 : n <= 832 && (Hq < kMapWaves || (Hq >= 24 && Hq >= 4 * Hkv));
 }
 
 size_t attention_map_stats_bytes(int n, int Hq) { return align_up((size_t)n * Hq * 2 * sizeof(float), 256); }
@@ -305,17 +403,24 @@ fastav_status_t launch_attention_map(const void* q, int64_t q_stride, const void
   a.q = (const bf16_t*)q; a.k = (const bf16_t*)k; a.qs = q_stride; a.ks = k_stride; a.n = n; a.Hq = Hq; a.Hkv = Hkv;
   a.scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
   a.stats = stats; a.a_out = (bf16_t*)a_out; a.ld = ld; a.n_cols = lower ? (n + 63) / 64 * 64 : n;
+  a.lower = lower;
   a.lines = ld % 8 == 0 && (uintptr_t)a_out % 16 == 0;
   // the causal Q K^T products: once for the statistics, once for the map
   ProfScope prof(FASTAV_PROF_ATTENTION, (have_stats ? 1.0 : 2.0) * 2.0 * Hq * dh * (double)n * ((double)n + 1.0) * 0.5, s);
   const dim3 g1((unsigned)Hq, (unsigned)ceil_div(n, 64));
+  if (!have_stats) {
+    if (dh == 128) hipLaunchKernelGGL(k_attn_rowstats<128>, g1, dim3(kStatWaves * 64), 0, s, a);
+    else hipLaunchKernelGGL(k_attn_rowstats<64>, g1, dim3(kStatWaves * 64), 0, s, a);
+  }
+  if (map_is_short(n, Hq, Hkv, dh)) {
+    const dim3 g2((unsigned)ceil_div(n, 32), (unsigned)ceil_div(n, 64));
+    if (dh == 128) hipLaunchKernelGGL(k_attn_map_short<128>, g2, dim3(kMapWaves * 64), 0, s, a);
+    else hipLaunchKernelGGL(k_attn_map_short<64>, g2, dim3(kMapWaves * 64), 0, s, a);
+    return check_launch("attention_map");
+  }
   const unsigned nt = (unsigned)ceil_div(n, 64), below = nt * (nt + 1) / 2, g2 = lower ? below : nt * nt;
   const bool few = below <= 256;
-  if (dh == 128) {
-    if (!have_stats) hipLaunchKernelGGL(k_attn_rowstats<128>, g1, dim3(kStatWaves * 64), 0, s, a);
-    return few ? launch_map<128, 4>(a, g2, s) : launch_map<128, 2>(a, g2, s);
-  }
-  if (!have_stats) hipLaunchKernelGGL(k_attn_rowstats<64>, g1, dim3(kStatWaves * 64), 0, s, a);
+  if (dh == 128) return few ? launch_map<128, 4>(a, g2, s) : launch_map<128, 2>(a, g2, s);
   return few ? launch_map<64, 4>(a, g2, s) : launch_map<64, 2>(a, g2, s);
 }
 

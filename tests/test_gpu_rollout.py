@@ -167,3 +167,10 @@ def test_attention_map_into_memory_off_a_16_byte_boundary(n):
                                                     ws.numel(), torch.cuda.current_stream().cuda_stream))
     assert torch.equal(buf[4:-4].view(n, n), want)
     assert bool((buf[:4] == 7.0).all()) and bool((buf[-4:] == 7.0).all())
+
+
+@pytest.mark.parametrize("Hq,Hkv,dh,n", [(6, 3, 64, 896), (6, 3, 64, 900), (4, 2, 128, 832), (4, 2, 128, 836), (24, 6, 128, 200), (24, 8, 128, 200), (8, 2, 128, 68)])
+def test_attention_map_on_both_sides_of_the_short_form(Hq, Hkv, dh, n):
+    """Short prompts take 32 x 64 tiles read straight from memory, up to 896 tokens (heads of 64) or 832 (few heads of 128, or many
+    to a key head)."""
+    test_attention_map_matches_oracle(Hq, Hkv, dh, n)
