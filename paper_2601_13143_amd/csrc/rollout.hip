@@ -283,7 +283,7 @@ __global__ __launch_bounds__(HG * 256, 4) void k_attn_map(MapArgs a) {
 }
 
 // The map of a short prompt: a workgroup makes 32 rows x 64 keys, wave w sums heads [w Hq / 8, (w + 1) Hq / 8) with the operands
-// read straight from memory in operand layout.  Bound by latency: there is no copy to wait for and no
+// read straight from memory in operand layout, by 64-bit addresses.  Bound by latency: there is no copy to wait for and no
 // barrier until the waves' sums meet, and twice as many workgroups as of 64 x 64 tiles.
 // grid (query tiles of 32, key tiles of 64)
 constexpr int kMapWaves = 8;
@@ -412,7 +412,9 @@ fastav_status_t launch_attention_map(const void* q, int64_t q_stride, const void
     if (dh == 128) hipLaunchKernelGGL(k_attn_rowstats<128>, g1, dim3(kStatWaves * 64), 0, s, a);
     else hipLaunchKernelGGL(k_attn_rowstats<64>, g1, dim3(kStatWaves * 64), 0, s, a);
   }
-  if (map_is_short(n, Hq, Hkv, dh)) {
+  // the 64 x 64 tiles address the rows of a tile by 32-bit byte offsets from its first
+  const bool wide = q_stride >= (1 << 25) || k_stride >= (1 << 25);
+  if (wide || map_is_short(n, Hq, Hkv, dh)) {
     const dim3 g2((unsigned)ceil_div(n, 32), (unsigned)ceil_div(n, 64));
     if (dh == 128) hipLaunchKernelGGL(k_attn_map_short<128>, g2, dim3(kMapWaves * 64), 0, s, a);
     else hipLaunchKernelGGL(k_attn_map_short<64>, g2, dim3(kMapWaves * 64), 0, s, a);

@@ -174,3 +174,16 @@ def test_attention_map_on_both_sides_of_the_short_form(Hq, Hkv, dh, n):
     """Short prompts take 32 x 64 tiles read straight from memory, up to 896 tokens (heads of 64) or 832 (few heads of 128, or many
     to a key head)."""
     test_attention_map_matches_oracle(Hq, Hkv, dh, n)
+
+
+def test_attention_map_of_rows_far_apart():
+    """Keys 68 MB apart: the rows of one tile lie further from each other than a 32-bit byte offset reaches."""
+    n, pitch = 840, 34_100_000
+    m = fa.make_model(1, 64, 8, 2, 128, 64)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    q, k = (torch.randn((n, h, 128), device="cuda", generator=gen).bfloat16() for h in (8, 2))
+    apart = torch.empty((n - 1) * pitch + 256, dtype=torch.bfloat16, device="cuda").as_strided((n, 2, 128), (pitch, 128, 1))
+    apart.copy_(k)
+    got, want = host(fa.fastav_attention_map(m, q, apart)), host(fa.fastav_attention_map(m, q, k))
+    assert rel_l2(got, want) <= 1e-3                       # the heads' sums in another order, entries rounded to bf16
+    assert np.all(np.triu(got, 1) == 0.0)
