@@ -278,12 +278,14 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
 
   // ---- flags and ordered output.  Thread t owns the contiguous rows [t*per, (t+1)*per).
   if constexpr (KEYS_IN_LDS) {
-    // 16 bytes per read (`per` is rounded up to a multiple of four, so every thread starts on a 16-byte boundary; word-by-word
-    // reads at a stride of `per` words would pile a wave's lanes on a few banks).  One scan carries both running counts: the
-    // rows kept for sure (protected, or above the threshold) in the low half and the rows equal to the threshold in the high
-    // half - either total is at most kSelLdsKeys = 2^15, so the halves do not run into each other.
+    // 16 bytes per read.  `per` is an odd number of such pieces: every thread starts on a 16-byte boundary and a wave's lanes
+    // read 16 different slots (at an even number they meet in a few banks, all of them in two at 32 rows a thread: 33 samples of
+    // 16384 / 30000 / 32768 rows by position 18.9 / 39.5 / 42.3 -> 16.5 / 26.5 / 27.6 us, by score 23.9 / 49.0 / 52.5 ->
+    // 22.2 / 35.2 / 36.8).  One scan carries both running counts: the rows kept for sure (protected, or above the threshold) in
+    // the low half and the rows equal to the threshold in the high half - either total is at most kSelLdsKeys = 2^15, so the
+    // halves do not run into each other.
     static_assert(kSelLdsKeys <= 32768, "packed scan");
-    const int per = ((n + kSelThreads - 1) / kSelThreads + 3) & ~3;
+    const int per = 4 * ((n + 4 * kSelThreads - 1) / (4 * kSelThreads) | 1);
     const int j_lo = tid * per, j_hi = j_lo + per < n ? j_lo + per : n;
     auto read4 = [&](uint32_t (&k4)[4], int j) __attribute__((always_inline)) {
       if (j + 3 < n) {

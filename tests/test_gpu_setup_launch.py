@@ -123,3 +123,20 @@ def test_select_with_prefix_sums_in_the_arguments(batch, scored):
     assert np.array_equal(idx.cpu().numpy(), want)
     assert np.array_equal(cu_out.cpu().numpy(), np.concatenate([[0], np.cumsum(keep)]))
     assert np.array_equal(got.cpu().numpy(), rows[want])
+
+
+@pytest.mark.parametrize("n", [4097, 8193, 16385, 28673, 30000, 32768, 32769])
+@pytest.mark.parametrize("scored", [True, False])
+def test_selection_of_long_samples(n, scored):
+    """Rows dealt to the threads in odd numbers of 16-byte pieces (4 to 36 rows a thread), up to the last sample whose keys fit LDS
+    and one beyond; equal scores across the cut."""
+    rng = np.random.default_rng(n)
+    cu, keep = np.array([0, n, n + 700], dtype=np.int32), np.array([n * 2 // 3, 333], dtype=np.int32)
+    scores = np.floor(rng.random(n + 700) * 50).astype(np.float32)
+    prot = rng.random(n + 700) < 0.02
+    idx, _, _ = fa.fastav_select_gather(torch.from_numpy(scores).cuda() if scored else None, torch.from_numpy(prot.astype(np.uint8)).cuda(), cu, keep)
+    want = []
+    for b in range(2):
+        s = np.where(prot[cu[b]:cu[b + 1]], np.inf, scores[cu[b]:cu[b + 1]] if scored else 0.0)
+        want.append(cu[b] + np.sort(np.argsort(-s, kind="stable")[:keep[b]]))
+    assert np.array_equal(idx.cpu().numpy(), np.concatenate(want))
