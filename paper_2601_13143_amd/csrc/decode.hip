@@ -975,18 +975,33 @@ size_t decode_attn_workspace_bytes(int batch, int Hq, int dh, int max_splits) {
 }
 
 // Keys per split.  A workgroup's four waves take 64 keys each, so shares of 256 keys keep all of them at work; the sums of the
-// waves meet in LDS, those of the splits in the merge.  Where that makes fewer than 192 workgroups the keys are
-// cut finer instead, one wave at work in each: the loads in flight count then.  A step's time per layer in us, finest
-// shares (about four workgroups per CU, whatever is left of them for a wave) against 256 keys: 8 prompts of 5000 (the ragged
-// batch) 125.2 / 121.4, 4 of 3000 112.8 / 110.0, 7 of 6000 with 4 KV heads 135.9 / 131.0, 2 of 6000 (192 workgroups) 114.7 / 113.9;
-// one of 4096 (136) 94.8 / 95.3, one of 512 (16) 94.0 / 95.4.
-static int decode_attn_chunk(int batch, int Hkv, int max_keys) {
-  const int64_t groups = (int64_t)batch * Hkv;
-  if (ceil_div(max_keys, 256) * groups >= 192) return (int)(ceil_div(ceil_div(max_keys, 64), 256) * 256);
-  const int64_t want = (1024 + groups - 1) / groups, chunks = ceil_div(max_keys, 64);
-  int64_t splits = want < chunks ? want : chunks;
+// waves meet in LDS, those of the splits in the merge.  The finest shares (about four workgroups per CU, whatever is left of them
+// for a wave) are better where the loads in flight are few, or where shares of 256 end in an uneven second round.
+// A layer's time in us with caches that come from HBM (hidden 512, so that attention is most of it), finest / 256 keys:
+// - fewer than 192 workgroups of 256, or keys for fewer than 128: 1 x 4096 keys, 28/4 heads of 128 (68 workgroups) 25.2 / 27.5,
+//   4 x 1500 (96) 33.4 / 34.8, 1 x 6000, 32/4 heads of 64 (96) 22.5 / 23.1, 12 x 310, 32/8 of 128 (192 with keys for 116) 34.6 / 35.8;
+//   from 192 to 256: 4 x 3012, 28/4 of 128 40.2 / 36.1, 8 x 1988 42.6 / 37.9,
+//   1 x 8132, 32/8 of 128 30.2 / 29.3, 4 x 4036, 32/4 of 64 35.6 / 29.6
+// - 257 to 400, a second round of up to a half: heads of 64 2 x 2500, 16/16 27.3 / 28.6, 4 x 2244, 32/8 29.0 / 30.1, 1 x 5572,
+//   16/16 24.9 / 26.3; heads of 128 take 192 keys there: 2 x 10180, 28/4 finest 39.1, 256 41.5, 192 39.1; 1 x 12228, 32/8 32.3,
+//   33.0, 32.4; 2 x 5060, 32/8 38.0, 37.7, 36.4
+// - beyond: 2 x 7108, 32/8 of 128 42.3 / 38.3, 8 x 6000 68.7 / 65.1, 16 x 4096 89.0 / 80.9, 8 x 16000, 16/16 of 64 132 / 113, 8 x 3524,
+//   32/4 of 64 36.4 / 33.7.  Not with more than four query heads of 64 to a key head once the finest are longer than 384:
+//   8 x 12300, 32/4 47.8 / 48.7, 8 x 16000 53.6 / 54.9
+// - beyond 16384 keys 64 splits ask for more than 256 keys.  The fewest that do (a multiple of 64), which for small batches are
+//   the finest: 1 x 16600, 32/8 of 128 37.5, with 512 keys 40.4; 2 x 20000, 28/4 46.9, 51.0; 4 x 16600, 16/16 of 64 finest 76.3,
+//   fewest 71.6, 512 73.4; 8 x 16600, 32/8 136.5, 131.8, 130.8.  With more than four query heads to a key head the finest:
+//   8 x 16600, 28/4 of 128 88.8, 91.2, 91.0, 32/4 of 64 54.4, 57.1, 54.7.
+static int decode_attn_chunk(int batch, int Hq, int Hkv, int dh, int max_keys) {
+  const int64_t groups = (int64_t)batch * Hkv, want = (1024 + groups - 1) / groups, blocks = ceil_div(max_keys, 64);
+  int64_t splits = want < blocks ? want : blocks;
   if (splits > 64) splits = 64;
-  return (int)(ceil_div(ceil_div(max_keys, splits), 64) * 64);
+  const int64_t finest = ceil_div(ceil_div(max_keys, splits), 64) * 64, fewest = ceil_div(blocks, 64) * 64;   // fewest: 64 splits
+  const int64_t workgroups = ceil_div(max_keys, 256) * groups;
+  const bool many_heads = Hq > 4 * Hkv;
+  if (workgroups < 192 || max_keys * groups < 128 * 256 || (many_heads && (fewest > 256 || (dh == 64 && finest > 384)))) return (int)finest;
+  if (workgroups > 256 && workgroups <= 400 && fewest <= 192) return dh == 64 ? (int)finest : 192;
+  return (int)(fewest > 256 ? fewest : 256);
 }
 
 fastav_status_t launch_decode_attention(const void* q, const void* k_self, const void* v_self, int64_t q_stride,
@@ -1008,7 +1023,7 @@ fastav_status_t launch_decode_attention(const void* q, const void* k_self, const
   a.k_gen = (const bf16_t*)k_gen; a.v_gen = (const bf16_t*)v_gen; a.gen_len = gen_len; a.gen_cap = gen_cap;
   a.Hq = Hq; a.Hkv = Hkv;
   const int max_keys = max_prefix + gen_len + 1;
-  a.chunk = decode_attn_chunk(batch, Hkv, max_keys);
+  a.chunk = decode_attn_chunk(batch, Hq, Hkv, dh, max_keys);
   a.splits = (int)ceil_div(max_keys, a.chunk);          // at most 64
   a.scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
   a.part = part;

@@ -276,12 +276,14 @@ def test_decode_step_head_layouts(hq, hkv, dh, batch):
     assert_close(host(r["x_out"]), want, "bf16", scale=float(np.sqrt(np.mean(want ** 2))), what=f"decode Hq{hq} Hkv{hkv} dh{dh} B{batch}")
 
 
-def _steps_with_generated_cache(m, batch, n_prefix, steps, seed, gen_cap=4):
-    """Consecutive decode steps on random caches of ragged lengths, with the generated-token caches, against the oracle: hidden
-    states, and the appended keys and values of all layers and steps."""
+def _steps_with_generated_cache(m, batch, n_prefix, steps, seed, gen_cap=4, longest=None):
+    """Consecutive decode steps on random caches of ragged lengths (below n_prefix; the first sample's `longest` where given), with
+    the generated-token caches, against the oracle: hidden states, and the appended keys and values of all layers and steps."""
     rng = np.random.default_rng(seed)
     weights = [{k: v.astype(np.float64) for k, v in fi.layer_weights(m, l, seed).items()} for l in range(m.n_layers)]
     lens = rng.integers(1, n_prefix, size=(m.n_layers, batch)).astype(np.int32)
+    if longest is not None:
+        lens[:, 0] = longest
     draw = lambda *s: fi.round_bf16(rng.standard_normal(s).astype(np.float32))
     kv = [tuple(draw(int(lens[l].sum()), m.n_kv_heads, m.head_dim) for _ in range(2)) for l in range(m.n_layers)]
     x_steps = [draw(batch, m.hidden) for _ in range(steps)]
@@ -329,8 +331,17 @@ def test_decode_step_hidden_above_the_resident_limit(batch, hq, hkv, dh):
 
 @pytest.mark.parametrize("batch,hq,hkv,dh,n_prefix", [(16, 16, 8, 64, 260), (16, 8, 4, 128, 770), (6, 16, 8, 64, 1030), (3, 32, 32, 64, 520), (1, 8, 8, 64, 16600)])
 def test_decode_attention_in_shares_of_256_keys(batch, hq, hkv, dh, n_prefix):
-    """192 workgroups or more: shares of 256 keys (512 beyond 64 of them), samples that end at, before and inside a share."""
+    """Shares of 256 keys from 192 workgroups on, the finest below; samples that end at, before and inside a share."""
     _steps_with_generated_cache(fi.Model(1, 512, hq, hkv, dh, 512, 1.0e4, 1e-6, "bf16"), batch, n_prefix, 2, 23)
+
+
+@pytest.mark.parametrize("batch,hq,hkv,dh,longest", [
+    (12, 8, 8, 64, 311), (4, 8, 8, 64, 2047), (16, 4, 4, 64, 1100), (8, 8, 8, 128, 1400), (16, 20, 4, 64, 6400), (3, 4, 4, 64, 16383), (3, 4, 4, 64, 16384),
+    (4, 8, 1, 64, 16700), (1, 8, 8, 64, 33000)])
+def test_decode_attention_on_both_sides_of_its_rule(batch, hq, hkv, dh, longest):
+    """192 workgroups with few keys in half of them, 256 workgroups of 256 keys, the uneven second round (finest shares or 192 keys), many heads of 64 to a key head, 64 shares of 256
+    keys and one key more, and the fewest and the finest shares beyond, where a share does not give every wave the same."""
+    _steps_with_generated_cache(fi.Model(1, 512, hq, hkv, dh, 512, 1.0e4, 1e-6, "bf16"), batch, 300, 2, 29, longest=longest)
 
 
 def test_decode_step_rejects_bad_arguments():
