@@ -345,7 +345,12 @@ struct RingPlan { int bm, bn, splits; };
 //   CUs stay idle, else of 192 x 128 where they keep 16 to 31 (with the sum of the partial tiles, 331 / 460 / 576 rows:
 //   4096 x 4096 33 / 38 / - -> 30 / 31 / -, 1024 x 16384 52 / 54 / 53 -> 27 / 29 / 34, 2560 x 6912 32 / 35 / 39 -> 26 / 32 / 36,
 //   2048 x 8192 35 / 36 / 39 -> 27 / 30 / 35, 4608 x 4608 35 / - / - -> 32 / - / -, 3584 x 3584 - / 30 / 36 -> - / 28 / 31; idle
-//   CUs: 40 stages on 192 of them, 4096 x 5120, 34 -> 35 at 331 rows, and on all of them 38 -> 33 at 400).  Longer shares
+//   CUs: 40 stages on 192 of them, 4096 x 5120, 34 -> 35 at 331 rows, and on all of them 38 -> 33 at 400).  Where the
+//   64-column tiles are the alternative and not the large ones, 192 x 128 needs two and a half times their shares (300-560 rows,
+//   shares of both: 4096 x 2048 1 / 2 21.0 -> 25.3, 5120 x 2560 1 / 2 25.6 -> 30.3, 2304 x 4096 2 / 4 23.9 -> 25.2,
+//   1152 x 9216 4 / 9 24.7 -> 25.5, 512 x 18944 10 / 16 23.6 -> 26.6; 2048 x 5632 2 / 5 29.3 -> 27.0, 3072 x 4608 1 / 3 a
+//   fifth faster): as many workgroups and no more, which write twice the partial tiles.  128 x 128 needs more shares than theirs
+//   or nine tenths of the CUs (4096 x 3584 2 / 2 on 192 CUs 23.8 -> 25.0, 1792 x 4608 3 / 3 on 210 22.8 -> 23.4).  Longer shares
 //   gain less and less (192 x 128, 331 rows: 4096 x 14336, 56 stages, 64 -> 59 to 62; 8192 x 8192, 64 stages, 68 -> 69;
 //   3584 x 18944, 74 stages, 69 -> 69 to 74), one share nothing (4096 x 4096, 576 rows: 41 -> 42), and shorter ones lose to
 //   64-column tiles (2048 x 2048, 8 stages: 16.1 -> 16.7).
@@ -369,29 +374,35 @@ static RingPlan ring_plan(int m, int n, int k, int epilogue, size_t room) {
       }
       return p;
     };
-    for (int bm = 128; one == 0 && bm <= 192; bm += 64) {
-      const int64_t t = tiles(bm, n, 128), fill = kNumCUs / t;
-      const int splits = (int)(fill < 16 ? fill : 16);
-      const int stages = splits >= 2 ? k / 64 / splits : 0;
-      if (bm == 128 ? stages >= 24 && stages * kNumCUs < 48 * t * splits : stages >= 16 && stages < 32) return cut({bm, 128, splits});
-    }
-    const int64_t t128 = tiles(one ? one : 256, n, 128);
-    const bool long_k = t128 <= kNumCUs && (k / 64) / (kNumCUs / t128) >= 16;
-    if (long_k && one == 0) return no;
-    RingPlan p;
-    if (long_k && one > 64) {
-      p = {one, 128, kNumCUs / t128 < 16 ? (int)(kNumCUs / t128) : 16};
-      if (t128 > 48 && (m > 192 || (m > 128 && (k / 64) / p.splits >= 64))) return no;
-    } else {
+    auto narrow = [&]() -> RingPlan {                   // 64-column tiles
       const int bm = m <= 64 ? 64 : m <= 128 ? 128 : m <= 192 ? 192 : m <= 256 ? 128 : 192;
       const int64_t t64 = tiles(bm, n, 64);
       if (t64 > kNumCUs || (m > 192 && m <= 256 && t64 > kNumCUs / 2)) return no;
       int splits = (int)(kNumCUs / t64);
       if (splits > k / 64 / 8) splits = k / 64 / 8;     // a share is at least 8 stages
       if (splits > 16) splits = 16;
-      p = {bm, 64, splits < 1 ? 1 : splits};
+      return {bm, 64, splits < 1 ? 1 : splits};
+    };
+    const int64_t t128 = tiles(one ? one : 256, n, 128);
+    const bool long_k = t128 <= kNumCUs && (k / 64) / (kNumCUs / t128) >= 16;
+    if (one == 0) {
+      const RingPlan other = long_k ? no : narrow();
+      for (int bm = 128; bm <= 192; bm += 64) {
+        const int64_t t = tiles(bm, n, 128), fill = kNumCUs / t;
+        const int splits = (int)(fill < 16 ? fill : 16);
+        const int stages = splits >= 2 ? k / 64 / splits : 0;
+        if (!(bm == 128 ? stages >= 24 && stages * kNumCUs < 48 * t * splits : stages >= 16 && stages < 32)) continue;
+        if (other.bm != 0 && (bm == 128 ? splits <= other.splits && t * splits < 224 : 2 * splits < 5 * other.splits)) continue;
+        return cut({bm, 128, splits});
+      }
+      return other.bm == 0 ? no : cut(other);
     }
-    return cut(p);
+    if (long_k && one > 64) {
+      const RingPlan p = {one, 128, kNumCUs / t128 < 16 ? (int)(kNumCUs / t128) : 16};
+      return t128 > 48 && (m > 192 || (m > 128 && (k / 64) / p.splits >= 64)) ? no : cut(p);
+    }
+    const RingPlan p = narrow();
+    return p.bm == 0 ? no : cut(p);
   }
   const int cols = epilogue == FASTAV_EPI_SWIGLU ? 2 * n : n;
   for (int i = 0; i < 3; ++i) {

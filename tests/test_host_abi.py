@@ -104,6 +104,21 @@ def test_few_row_products_leave_the_ring_kernel_where_the_large_tiles_are_faster
     assert plan(331, 18944, 3584, fa.EPI_SWIGLU) == (384, 160, 1) and plan(385, 18944, 3584, fa.EPI_SWIGLU) == fa.LINEAR_TILES
 
 
+def test_residual_products_keep_the_64_column_tiles_where_wider_ones_win_no_cus():
+    """The measured lines of ring_plan beyond 256 rows: where 64-column tiles are the alternative, 192 x 128 tiles need two and a
+    half times their shares of K and 128 x 128 tiles more shares or 224 workgroups."""
+    def plan(m, n, k, room=None):
+        p = fa.fastav_linear_plan(m, n, k, fa.EPI_RESADD, fa.BF16, room)
+        return (p.tile_rows, p.tile_cols, p.splits) if p.kernel == fa.LINEAR_RING else p.kernel
+    assert plan(387, 512, 18944) == (192, 64, 10) and plan(300, 640, 18432) == (192, 64, 12)
+    assert plan(448, 1024, 11008) == (192, 64, 5) and plan(385, 1280, 8704) == (192, 64, 4) and plan(420, 1152, 9216) == (192, 64, 4)
+    assert plan(448, 4096, 2048) == (192, 64, 1) and plan(500, 4608, 2560) == (192, 64, 1) and plan(448, 2304, 4096) == (192, 64, 2)
+    assert plan(290, 4096, 3584) == (192, 64, 2) and plan(513, 1792, 4608) == (192, 64, 3)
+    assert plan(500, 2048, 5632) == (192, 128, 5) and plan(500, 3072, 4608) == (192, 128, 3) and plan(331, 5120, 3584) == (128, 128, 2)
+    assert plan(331, 1536, 10240) == (192, 128, 10) and plan(560, 1024, 18432) == (192, 128, 10)      # the large tiles otherwise
+    assert plan(384, 2304, 12800) == (192, 128, 7) and plan(513, 512, 19456) == (128, 128, 12)
+
+
 def test_schedule_n_last_counts_non_text_tail_once():
     # last 3 positions: one audio + two text -> protected = 4 text + 1 audio
     cu = [0, 20]
