@@ -393,7 +393,9 @@ static RingPlan ring_plan(int m, int n, int k, int epilogue, size_t room) {
         const int stages = splits >= 2 ? k / 64 / splits : 0;
         if (!(bm == 128 ? stages >= 24 && stages * kNumCUs < 48 * t * splits : stages >= 16 && stages < 32)) continue;
         if (other.bm != 0 && (bm == 128 ? splits <= other.splits && t * splits < 224 : 2 * splits < 5 * other.splits)) continue;
-        return cut({bm, 128, splits});
+        const RingPlan wide = cut({bm, 128, splits});
+        if (wide.bm != 0) return wide;                  // else, without the room, as before these tiles
+        break;
       }
       return other.bm == 0 ? no : cut(other);
     }

@@ -117,6 +117,9 @@ def test_residual_products_keep_the_64_column_tiles_where_wider_ones_win_no_cus(
     assert plan(500, 2048, 5632) == (192, 128, 5) and plan(500, 3072, 4608) == (192, 128, 3) and plan(331, 5120, 3584) == (128, 128, 2)
     assert plan(331, 1536, 10240) == (192, 128, 10) and plan(560, 1024, 18432) == (192, 128, 10)      # the large tiles otherwise
     assert plan(384, 2304, 12800) == (192, 128, 7) and plan(513, 512, 19456) == (128, 128, 12)
+    # room for some of the partial tiles only: the 64-column tiles that need fewer of them
+    assert plan(514, 512, 18432) == (128, 128, 12) and plan(514, 512, 18432, 5 * 4 * 514 * 512) == (192, 64, 5)
+    assert plan(514, 512, 18432, 6 * 4 * 514 * 512) == (128, 128, 6) and plan(514, 512, 18432, 4 * 4 * 514 * 512) == fa.LINEAR_TILES
 
 
 def test_schedule_n_last_counts_non_text_tail_once():
