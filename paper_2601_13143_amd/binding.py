@@ -147,16 +147,23 @@ def _check(st: int) -> None:
         raise FastavError(st, lib().fastav_last_error().decode())
 
 
-try:                                                     # the stream's address without a Stream object around it: 2.8 -> 0.3 us
-    from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
-except ImportError:
-    _cuda_getCurrentRawStream = None
+def _raw_stream_calls(torch_version: str):
+    """(current raw stream of a device, current device) of this torch release, or None.  The two names are private to torch: they
+    are used with the release whose meaning of them the tests check, any other takes the public call (a Stream object: 2.8 us
+    instead of 0.3)."""
+    if torch_version.split("+")[0].split(".")[:2] != ["2", "10"]:
+        return None
+    raw, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    return (raw, device) if raw and device else None
+
+
+_raw_calls = _raw_stream_calls(torch.__version__)
 
 
 def _stream() -> int:
-    if _cuda_getCurrentRawStream is None or not torch.cuda.is_initialized():
+    if _raw_calls is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return _cuda_getCurrentRawStream(_cuda_getDevice())
+    return _raw_calls[0](_raw_calls[1]())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

@@ -140,3 +140,16 @@ def test_selection_of_long_samples(n, scored):
         s = np.where(prot[cu[b]:cu[b + 1]], np.inf, scores[cu[b]:cu[b + 1]] if scored else 0.0)
         want.append(cu[b] + np.sort(np.argsort(-s, kind="stable")[:keep[b]]))
     assert np.array_equal(idx.cpu().numpy(), np.concatenate(want))
+
+
+def test_calls_go_to_the_current_stream():
+    """The stream handed to the library is torch's current one: default, side streams, nested, and back."""
+    public = lambda: torch.cuda.current_stream().cuda_stream
+    assert fa.binding._stream() == public()
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(a):
+        assert fa.binding._stream() == public() == a.cuda_stream
+        with torch.cuda.stream(b):
+            assert fa.binding._stream() == public() == b.cuda_stream != a.cuda_stream
+        assert fa.binding._stream() == a.cuda_stream
+    assert fa.binding._stream() == public()

@@ -330,3 +330,10 @@ def test_decode_step_refuses_caches_and_head_groups_before_any_launch(heads, off
         assert lib.fastav_decode_step(h, C.byref(di), fake, fake, need.value, None) == status
         assert word in lib.fastav_last_error()
     lib.fastav_destroy(h)
+
+
+@pytest.mark.parametrize("version,known", [("2.10.0+rocm7.0", True), ("2.10.1", True), ("2.1.0", False), ("2.11.0", False), ("2.9.1+rocm6.4", False), ("3.10.0", False)])
+def test_private_stream_call_is_used_with_the_release_it_was_checked_with(version, known):
+    calls = B._raw_stream_calls(version)
+    assert calls is None or (known and len(calls) == 2 and all(callable(c) for c in calls))
+    assert known or calls is None
