@@ -90,7 +90,9 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
   const int g = h / G;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, so control flow stays scalar
-  const int wave = wave_wg & 3, grp = wave_wg >> 2;               // 32-row block of the query tile, key group
+  // 32-row block of the query tile, key group.  Pairs have a constant group, which gives them back the loop they had before there
+  // were groups (4096 tokens of 32 heads 142.1 -> 140.4 us, 1900 of 60 heads 74.6 -> 73.8); single tiles lose by it at many tiles.
+  const int wave = PAIRED ? wave_wg : wave_wg & 3, grp = PAIRED ? 0 : wave_wg >> 2;
   const int l32 = lane & 31, hf = lane >> 5;
   // first K / V row of this sample and KV head; rows are then addressed with 32-bit byte offsets (the
   // launcher checks that a sample's K/V rows span less than 2 GB)
