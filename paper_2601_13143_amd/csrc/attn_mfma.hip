@@ -391,13 +391,22 @@ __global__ __launch_bounds__(256 * KG, 2) void k_attn_mfma(AttnArgs a) {
 //   pairs      13.9  18.6  32.1  35.8  50.4  73.9  81.3   100 139.7   248   695   2015
 //   split       9.6  11.6  23.1  24.8  46.0  60.9  70.4  94.3 151.8   226   654   2074
 // The split form wins while its workgroups find a CU each (256), and beyond that as long as the items are long against
-// their start and merge (ten tiles or more) and there are no more than two for a CU; heads of 64 cost half as much per
-// key, so the line lies at twice that.  Three prompts of 331 (288 items): split 19.5, tiles 14.4; two of 1024 (512 items)
-// 33.2 against 31.4.  Pairs win where they fill one round of 512 (4096 tokens, 32 heads; 4600 tokens, 28 heads 156 against 163).
+// their start and merge (ten tiles or more) and there are no more than two for a CU.  Three prompts of 331 (288 items): split
+// 19.5, tiles 14.4; two of 1024 (512 items) 33.2 against 31.4.  Heads of 64 cost half as much per key and leave room for two
+// workgroups on a CU: split against tiles
+//   items             288    320    384    480    512    512    576    640    640    704    832    896    768   1024   1024   1536
+//   tiles a prompt      3      5      6      5      4      8      9     10     20     11     13     14     16     16     32     24
+//   tiles             9.7   14.2   16.5   15.3   13.3   20.5   23.6   26.5   44.2   26.7   36.8   40.5   41.5   50.1   90.3   94.3
+//   split            10.0   12.6   14.8   14.9   13.4   18.7   22.8   25.7   38.8   28.4   37.2   40.8   40.8   48.9   84.0   93.5
+// so there the lines are 576 items from five tiles on, 672 from ten and 1024 from sixteen.
+// Pairs win where they fill one round of 512 (4096 tokens, 32 heads; 4600 tokens, 28 heads 156 against 163).  At two and more
+// whole rounds the tiles even out as well (pairs always, before / tiles: 8192 tokens 508 / 505, two prompts of 4096 273 / 273,
+// three 409 / 405, 12288 1132 / 1130, 16384 1964 / 1981).
 enum AttnForm { kAttnTiles, kAttnPaired, kAttnSplit };
 static AttnForm attn_form(int n_qtiles, int n_pairs, int dh, bool side, bool even) {
   const int64_t items = (int64_t)n_qtiles * n_pairs, pairs = (int64_t)((n_qtiles + 1) / 2) * n_pairs;
-  if (n_qtiles >= 3 && (items <= 256 || (n_qtiles >= 10 && items <= (dh == 64 ? 1024 : 512)))) return kAttnSplit;
+  const int64_t split_to = n_qtiles < 3 ? 0 : dh == 64 ? (n_qtiles < 5 ? 256 : n_qtiles < 10 ? 576 : n_qtiles < 16 ? 672 : 1024) : n_qtiles < 10 ? 256 : 512;
+  if (items <= split_to) return kAttnSplit;
   return !side && even && pairs >= 480 && pairs <= 512 ? kAttnPaired : kAttnTiles;
 }
 

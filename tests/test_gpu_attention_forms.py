@@ -29,11 +29,12 @@ def _reference(q, k, v, lens):
 
 
 # tiles: fewer than three query tiles, or more items than CUs; split: up to 256 items, ten tiles and up to 512 items
-# (1024 for heads of 64); pairs: 480 to 512 pairs of even samples
+# (heads of 64: 576 from five tiles on, 672 from ten, 1024 from sixteen); pairs: 480 to 512 pairs of even samples
 @pytest.mark.parametrize("Hq,Hkv,dh,lens", [
     (8, 2, 128, [256]), (8, 2, 128, [257]), (8, 2, 128, [384]), (8, 2, 128, [385, 1, 130]), (8, 8, 64, [319]), (28, 4, 128, [331]),
     (32, 8, 128, [1024]), (32, 8, 128, [1025]), (32, 8, 128, [1153]), (16, 4, 64, [1300]), (32, 8, 128, [331, 300, 290]),
-    (64, 8, 64, [250] * 8), (60, 6, 128, [129] * 8), (64, 8, 64, [250] * 7 + [100])])
+    (64, 8, 64, [250] * 8), (60, 6, 128, [129] * 8), (64, 8, 64, [250] * 7 + [100]),
+    (64, 8, 64, [600, 590]), (64, 8, 64, [512, 500]), (48, 8, 64, [1300]), (64, 8, 64, [1409]), (16, 4, 64, [1930, 1700, 1600])])
 def test_forms_against_float64(Hq, Hkv, dh, lens):
     rng = np.random.default_rng(Hq + dh + sum(lens))
     T = sum(lens)
