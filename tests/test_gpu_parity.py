@@ -293,9 +293,9 @@ def test_attention_and_last_row_side_output(dtype, Hq, Hkv, dh, lens):
 
 
 def _attention_case(qkv, Hq, Hkv, dh, lens, rows_per_sample=None, what=""):
-    """Runs fastav_attention with the side output on a fused [T, (Hq+2Hkv)dh] bf16-representable buffer and compares
-    O (all rows, or the given rows of each sample), the last row's logits, (max, sum) and the Eq. 4 scores they
-    imply against the oracle."""
+    """Runs fastav_attention with and without the side output (which may take another form of the kernel) on a fused
+    [T, (Hq+2Hkv)dh] bf16-representable buffer and compares O (all rows, or the given rows of each sample), the last row's
+    logits, (max, sum) and the Eq. 4 scores they imply against the oracle."""
     T = sum(lens)
     t = dev(qkv, "bf16")
     q = t.as_strided((T, Hq, dh), (t.stride(0), dh, 1))
@@ -304,8 +304,9 @@ def _attention_case(qkv, Hq, Hkv, dh, lens, rows_per_sample=None, what=""):
     m = fa.make_model(1, 64, Hq, Hkv, dh, 64, dtype=fa.BF16)
     cu = _cu(lens)
     o, ll, ml = fa.fastav_attention(m, q, k, v, torch.from_numpy(cu).cuda(), max(lens), want_last=True)
+    plain = fa.fastav_attention(m, q, k, v, torch.from_numpy(cu).cuda(), max(lens))
     torch.cuda.synchronize()
-    got, ll, ml = host(o), host(ll), host(ml)
+    got, ll, ml, plain = host(o), host(ll), host(ml), host(plain)
     assert np.isfinite(got).all() and np.isfinite(ml).all()
     q3 = qkv[:, :Hq * dh].reshape(T, Hq, dh)
     k3 = qkv[:, Hq * dh:(Hq + Hkv) * dh].reshape(T, Hkv, dh)
@@ -316,10 +317,12 @@ def _attention_case(qkv, Hq, Hkv, dh, lens, rows_per_sample=None, what=""):
         if rows_per_sample is None:
             want = orc.causal_gqa_attention(q3[sl].astype(np.float64), k3[sl].astype(np.float64), v3[sl].astype(np.float64))
             assert_close(got[sl], want, "bf16", what=f"{what} attention sample {b}")
+            assert_close(plain[sl], want, "bf16", what=f"{what} attention sample {b}, no side output")
         else:
             rows = [r for r in rows_per_sample[b] if 0 <= r < n]
             want = orc.causal_gqa_attention_rows(q3[sl], k3[sl], v3[sl], rows)
             assert_close(got[sl][rows], want, "bf16", what=f"{what} attention sample {b} rows {rows[:4]}..")
+            assert_close(plain[sl][rows], want, "bf16", what=f"{what} attention sample {b} rows {rows[:4]}.., no side output")
         s_side = np.zeros(n)
         for h in range(Hq):
             z = (k3[sl, h // G].astype(np.float64) @ q3[cu[b + 1] - 1, h].astype(np.float64)) / np.sqrt(dh)
@@ -364,11 +367,22 @@ def test_attention_running_max_climbs_across_key_tiles(dh, Hq, Hkv, log2_per_til
     _attention_case(qkv, Hq, Hkv, dh, lens, what=f"ramp {log2_per_tile}/tile, every other row flat")
 
 
-@pytest.mark.parametrize("dh,Hq,Hkv", [(128, 8, 2), (64, 4, 2)])
+@pytest.mark.parametrize("dh,Hq,Hkv,lens", [(128, 16, 4, [700, 333, 64, 129]), (64, 32, 8, [700, 333, 64, 129]), (128, 40, 8, [600] * 4),
+                                            (64, 40, 8, [600] * 4), (128, 40, 8, [700] * 4)])
+@pytest.mark.parametrize("log2_per_tile", [7.5, 20.0])
+def test_attention_running_max_climbs_in_single_and_paired_tiles(dh, Hq, Hkv, lens, log2_per_tile):
+    """The same with enough heads and samples for the forms that do not split the keys: a query tile per workgroup, and (four even
+    samples, without the side output) pairs of tiles, of an odd count of tiles and of an even one."""
+    qkv = _ramped_qkv(sum(lens), Hq, Hkv, dh, int(dh + Hq + log2_per_tile * 10), log2_per_tile / 64.0, lens, row_mix=log2_per_tile > 8.0)
+    _attention_case(qkv, Hq, Hkv, dh, lens, what=f"ramp {log2_per_tile}/tile")
+
+
+@pytest.mark.parametrize("dh,Hq,Hkv", [(128, 8, 2), (64, 4, 2), (128, 32, 8), (64, 64, 16)])
 def test_attention_one_dominant_late_key(dh, Hq, Hkv):
     """One key far down the sequence outweighs everything before it (the closed form the oracle is pinned with):
     rows at and after it return that key's value, the last row's scores are one-hot on it, and the rows before it
-    are ordinary.  The maximum jumps by hundreds of log2 units in the middle of a tile."""
+    are ordinary.  The maximum jumps by hundreds of log2 units in the middle of a tile.  Few heads split the keys over two groups
+    of waves, many take a tile per workgroup."""
     lens = [600, 257]
     T = sum(lens)
     rng = np.random.default_rng(dh)
@@ -397,9 +411,10 @@ def test_attention_one_dominant_late_key(dh, Hq, Hkv):
 
 @pytest.mark.parametrize("n,Hq,Hkv,dh", [(4096, 32, 8, 128), (16384, 28, 4, 128)])
 def test_attention_and_score_at_benchmark_lengths_on_sampled_rows(n, Hq, Hkv, dh):
-    """The sequence lengths the benchmark runs (64 and 256 key tiles, query-tile pairs far apart): attention output on
-    a sample of rows the oracle evaluates one by one (tile edges, the paired tiles' first and last rows, random
-    rows), the last row's side output, and the standalone Eq. 4 kernel over the whole sequence."""
+    """The sequence lengths the benchmark runs (64 and 256 key tiles): attention output on a sample of rows the oracle
+    evaluates one by one (tile edges, first and last tiles, random rows), with the side output (single tiles) and without
+    (4096 tokens: pairs of tiles far apart), the last row's side output, and the standalone Eq. 4 kernel over the
+    whole sequence."""
     rng = np.random.default_rng(n + Hq)
     qkv = rng.standard_normal((n, (Hq + 2 * Hkv) * dh)).astype(np.float32)
     qkv[:, :(Hq + Hkv) * dh] *= 1.3
@@ -416,6 +431,15 @@ def test_attention_and_score_at_benchmark_lengths_on_sampled_rows(n, Hq, Hkv, dh
         assert abs(got.sum() - 1.0) < 1e-4
         assert np.max(np.abs(got - want)) * n <= 1e-3 * max(1.0, want.max() * n) and rel_l2(got, want) <= 1e-4, \
             (n_last, np.max(np.abs(got - want)) * n, rel_l2(got, want))
+
+
+@pytest.mark.parametrize("n,Hq,Hkv,dh", [(1900, 60, 6, 128), (1860, 60, 12, 64)])
+def test_attention_pairs_of_an_odd_number_of_tiles(n, Hq, Hkv, dh):
+    """480 pairs of fifteen tiles: the middle tile of a long sample stands alone."""
+    qkv = np.random.default_rng(n).standard_normal((n, (Hq + 2 * Hkv) * dh)).astype(np.float32)
+    qkv[:, :(Hq + Hkv) * dh] *= 1.3
+    rows = sorted(set(list(range(0, n, 127)) + [895, 896, 960, 1023, 1024, n - 1]))
+    _attention_case(fi.round_bf16(qkv), Hq, Hkv, dh, [n], rows_per_sample=[rows], what=f"n={n}")
 
 
 # ------------------------------------------------------------------------------------ prefill end to end

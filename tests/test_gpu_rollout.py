@@ -148,6 +148,25 @@ def test_rollout_at_the_edges_of_its_tiles(n):
         assert np.all(np.triu(got, 1) == 0.0)
 
 
+@pytest.mark.parametrize("Hq,Hkv,dh,n", [(4, 2, 128, 1476), (8, 4, 64, 1476), (4, 4, 64, 900), (20, 4, 128, 396), (2, 1, 64, 2052), (60, 12, 128, 1300), (64, 8, 64, 1412)])
+def test_rollout_with_the_statistics_of_every_attention_form(Hq, Hkv, dh, n):
+    """Ragged prompts whose map takes the 64 x 64 tiles of two waves' shares (beyond 256 tiles) or of four, and the short form; row
+    statistics from attention with split keys and with a tile per workgroup of many key tiles; the step's sums over up to nine slices
+    a wave; heads of 64 and of 128."""
+    m = fi.Model(2, 256, Hq, Hkv, dh, 256, 1.0e4, 1e-6, "bf16")
+    w = fi.Workload("roll", m, [[(fi.TEXT, 4), (fi.VIDEO, n - 4)]], [], seed=n)
+    weights = [fi.layer_weights(m, l, 19) for l in range(m.n_layers)]
+    for W in weights:
+        W["wq"] = fi.round_bf16((W["wq"] * 6.0).astype(np.float32))
+        W["wk"] = fi.round_bf16((W["wk"] * 6.0).astype(np.float32))
+    x = fi.embeddings(w)
+    want = orc.attention_rollout(m, weights, x, 0.6)
+    got = host(make_decoder(m, weights).fastav_rollout(dev(x, "bf16"), 0.6, 2))
+    assert rel_l2(got, want[1]) <= 1e-2, rel_l2(got, want[1])          # the bound of the rollout above
+    assert np.max(np.abs(got.sum(axis=1) - 1.0)) <= 1e-2
+    assert np.all(np.triu(got, 1) == 0.0)
+
+
 @pytest.mark.parametrize("Hq,Hkv,dh,n", [(3, 1, 128, 1412), (5, 5, 64, 1476), (1, 1, 64, 68)])
 def test_attention_map_with_more_tiles_than_cus(Hq, Hkv, dh, n):
     """Beyond 256 tiles the heads are dealt over two waves a block instead of four; head counts that no share divides."""
