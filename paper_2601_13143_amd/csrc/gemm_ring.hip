@@ -23,7 +23,7 @@ __device__ __forceinline__ int ring_col(int n0, int c, bool half_heads) {
   return (n0 & ~127) + 32 * ((n0 >> 6) & 1) + (c & 31) + ((c & 32) << 1);
 }
 
-template <int BM, int BN, int TM, int KS, int NS, int EPI>
+template <int BM, int BN, int TM, int KS, int NS, int EPI, bool ROT>
 __global__ __launch_bounds__(BM / (16 * TM) * KS * 64) void k_gemm_ring(GemmArgs g) {
   constexpr int WM = BM / (16 * TM), NW = WM * KS;
   constexpr int TN = BN / 16;
@@ -54,10 +54,8 @@ __global__ __launch_bounds__(BM / (16 * TM) * KS * 64) void k_gemm_ring(GemmArgs
   const int kt0 = (int)((int64_t)kt_all * split / g.splits);
   const int KT = (int)((int64_t)kt_all * (split + 1) / g.splits) - kt0;
 
-  // Gate and up rows at a pitch of whole 4 KB, every workgroup at the same k: the rows then meet in a few memory channels, so
-  // each workgroup starts its walk of K elsewhere (weights of 28672 x 4096, 48 / 82 / 117 / 166 rows: 52 / 53 / 55 / 62 ->
-  // 46 / 48 / 51 / 59 us; rows of other pitches, the other products and the large tiles gain nothing).
-  const int rot = EPI == FASTAV_EPI_SWIGLU && K % 2048 == 0 ? pid * 5 % KT : 0;
+  // Where this workgroup starts its walk of K (launch_ring).
+  const int rot = ROT ? (int)((int64_t)tile_n * KT / g.tiles_n) : 0;
 
   const bf16_t* wbase = g.W[0];
   int seg_start = 0, seg = 0;
@@ -103,7 +101,7 @@ __global__ __launch_bounds__(BM / (16 * TM) * KS * 64) void k_gemm_ring(GemmArgs
   }
   auto copies = [&](int t, int slot) __attribute__((always_inline)) {   // past the last stage: the last one again, unread
     int at = (t < KT ? t : KT - 1) + rot;
-    if (EPI == FASTAV_EPI_SWIGLU && at >= KT) at -= KT;
+    if (ROT && at >= KT) at -= KT;
     const uint32_t so = (uint32_t)(at * 128);
     const uint32_t dst = lds0 + (uint32_t)slot * SLOT + (uint32_t)wave * 1024u;
 #pragma unroll
@@ -303,17 +301,30 @@ __global__ __launch_bounds__(BM / (16 * TM) * KS * 64) void k_gemm_ring(GemmArgs
   }
 }
 
+template <int BM, int BN, int TM, int KS, int NS, int EPI, bool ROT>
+static fastav_status_t launch_ring(const GemmArgs& g, hipStream_t s) {
+  constexpr int shmem = NS * (BM + BN) * 128;
+  hipError_t e = hipFuncSetAttribute((const void*)k_gemm_ring<BM, BN, TM, KS, NS, EPI, ROT>, hipFuncAttributeMaxDynamicSharedMemorySize, shmem);
+  if (e != hipSuccess) return fail(FASTAV_EHIP, "gemm: hipFuncSetAttribute: %s", hipGetErrorString(e));
+  hipLaunchKernelGGL((k_gemm_ring<BM, BN, TM, KS, NS, EPI, ROT>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(BM / (16 * TM) * KS * 64), shmem, s, g);
+  return check_launch("gemm_ring");
+}
 template <int BM, int BN, int TM, int KS, int NS, int EPI>
 static fastav_status_t launch_ring(GemmArgs g, int splits, hipStream_t s) {
   constexpr int OUT_BN = EPI == FASTAV_EPI_SWIGLU ? BN / 2 : BN;
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = (g.N + OUT_BN - 1) / OUT_BN;
   g.splits = splits;
-  constexpr int shmem = NS * (BM + BN) * 128;
-  hipError_t e = hipFuncSetAttribute((const void*)k_gemm_ring<BM, BN, TM, KS, NS, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, shmem);
-  if (e != hipSuccess) return fail(FASTAV_EHIP, "gemm: hipFuncSetAttribute: %s", hipGetErrorString(e));
-  hipLaunchKernelGGL((k_gemm_ring<BM, BN, TM, KS, NS, EPI>), dim3((unsigned)(g.tiles_m * g.tiles_n * splits)), dim3(BM / (16 * TM) * KS * 64), shmem, s, g);
-  return check_launch("gemm_ring");
+  // Gate and up rows at a pitch of whole 4 KB, every workgroup at the same k: the rows then meet in a few memory channels, so
+  // each tile column starts its walk of K elsewhere, evenly over K.  us, all at the same k / spread, 17 / 48 / 82 / 117 / 166 / 256
+  // rows of 28672 x 4096: 52.5 / 51.5 / 48.9 / 52.2 / 61.4 / 68 -> 43.9 / 44.3 / 47.2 / 50.3 / 58.8 / 67; 48 rows of
+  // 16384 x 2048 16.5 -> 15.0; five stages further a column instead: 64 rows of 28672 x 4096 45.5 -> 47.0, spread 44.5.  Rows of
+  // other pitches, the other products and the large tiles gain nothing.  Not with several tile rows: they share a panel of
+  // weights in L2 while they walk it together (each workgroup elsewhere: 8192 x 8192, 300 rows 62 -> 103, 2048 x 4096, 576 rows
+  // 24 -> 27; each tile column elsewhere: 24.7).
+  if constexpr (EPI == FASTAV_EPI_SWIGLU)
+    if (g.K % 2048 == 0 && g.tiles_m == 1) return launch_ring<BM, BN, TM, KS, NS, EPI, true>(g, s);
+  return launch_ring<BM, BN, TM, KS, NS, EPI, false>(g, s);
 }
 
 // Weights of fewer elements stay with the large tiles: there is little to gain (1024 x 1024 and 1536 x 1024, 48 to 500 rows,

@@ -35,6 +35,9 @@ CASES = [         # epilogue, rows, columns, K, (tile rows, tile columns, K shar
     (fa.EPI_SWIGLU, 100, 14336, 2048, (128, 128, 1)), (fa.EPI_SWIGLU, 250, 14336, 4096, (256, 128, 1)),   # K walked from another place
     (fa.EPI_RESADD, 257, 4096, 4096, (128, 128, 2)), (fa.EPI_RESADD, 512, 2048, 8256, (128, 128, 4)), (fa.EPI_RESADD, 331, 2560, 6912, (128, 128, 4)),
     (fa.EPI_RESADD, 576, 3584, 3648, (192, 128, 3)), (fa.EPI_RESADD, 513, 2560, 6912, (192, 128, 4)),   # several tile rows of 128 columns
+    (fa.EPI_SWIGLU, 48, 8192, 2048, (64, 64, 1)), (fa.EPI_SWIGLU, 100, 8192, 2048, (128, 64, 1)), (fa.EPI_SWIGLU, 129, 8192, 2048, (192, 64, 1)),
+    (fa.EPI_SWIGLU, 60, 14336, 2048, (64, 128, 1)), (fa.EPI_SWIGLU, 60, 18944, 2048, (64, 160, 1)), (fa.EPI_SWIGLU, 300, 18944, 2048, (384, 160, 1)),
+    (fa.EPI_SWIGLU, 450, 2048, 2048, (128, 64, 1)),                            # several tile rows: all from the first stage
     (fa.EPI_SWIGLU, 385, 18944, 256, TILES), (fa.EPI_SWIGLU, 145, 8192, 512, TILES),
 ]
 
