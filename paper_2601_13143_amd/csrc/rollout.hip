@@ -1,16 +1,15 @@
 // Attention rollout (Eq. 2-3 of the paper): the offline analysis that tells FastAV where to prune globally.
 //
-//   A^l  = mean over heads of the causal attention weights of layer l        (k_attn_rowstats + k_attn_map)
+//   A^l  = mean over heads of the causal attention weights of layer l        (k_attn_rowstats + k_attn_map, k_attn_map_short)
 //   R^l  = (alpha A^l + (1 - alpha) I) R^{l-1}                               (k_rollout_step)
 //
-// The head-mean map is formed without ever holding a per-head n x n map: a first pass computes every query
-// row's softmax (max, sum) per head by streaming K through the matrix cores (S^T = K Q^T tiles, running
-// max / sum per lane, like the prefill attention but with no values), a second pass recomputes each 32 x 64
-// tile of logits for every head, turns it into probabilities with those (max, sum) and accumulates the mean
-// in registers, so A is written exactly once (bf16, the operand type of the GEMM that consumes it).  Both
-// passes read Q and K straight from global memory in MFMA operand layout (they are served by L2: a tile of
-// one head is a few KB and is reused by the neighbouring workgroups); LDS holds only what the eight waves of a
-// workgroup, which share out the keys or the heads, sum at the end.
+// The head-mean map is formed without ever holding a per-head n x n map, from every query row's softmax (max, 1 / sum)
+// per head.  A rollout has those from the layer's own attention launch; its last layer, whose attention nobody needs, and
+// a direct call make them in a pass of their own, which streams K through the matrix cores (S^T = K Q^T tiles, running max
+// and sum per lane, like the prefill attention but with no values).  The map then recomputes each tile of logits for every
+// head, turns it into probabilities and accumulates the mean in registers, so A is written exactly once (bf16, the operand
+// type of the step that consumes it): 64 x 64 tiles whose rows of Q and K pass through LDS, or for short prompts 32 x 64
+// tiles read straight from memory in operand layout, as the statistics are.
 //
 // The rollout is kept transposed, RT = (R^l)^T: RT_new = RT (alpha A + (1 - alpha) I)^T = alpha (RT A^T) + (1 - alpha) RT, so
 // that both operands are read along their rows.  RT is carried in fp32 with a bf16 copy as the matrix operand.
@@ -138,9 +137,9 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_attn_rowstats(MapArgs a) {
 // layout, the 32 rows of a load lie in 32 cache lines at one offset, which one bank of the vector cache serves one after the
 // other (a row pitch 16 bytes off the line size alone made the map a third faster).  So the rows of the next heads are
 // copied to LDS in whole lines while the present ones are computed, and the keys of a group of query heads on the same way,
-// from where they go to registers.  A block's 16 sums, its keys and a head's rows are 128 registers: two workgroups of eight waves (HG = 2)
-// on a CU, so that the 528 tiles of 2048 tokens are one round.  Up to 256 tiles a workgroup has a CU to itself and takes
-// sixteen (HG = 4), which halves its chain.
+// from where they go to registers.  A block's 16 sums, its keys and a head's rows are 128 registers and a stage of both halves 32 KB: two workgroups
+// of eight waves (HG = 2) on a CU, 512 of the 528 tiles of 2048 tokens at once; the last 16, on the diagonal and shorter, follow
+// as CUs come free.  Up to 256 tiles a workgroup has a CU to itself and takes sixteen waves (HG = 4), which halves its chain.
 // 2048 tokens, 32 / 8 heads of 128, inside a rollout: 94 -> 49 us; 3600 tokens alone 205 -> 85.
 // Order: the tiles below the diagonal, in a contiguous run per XCD (block id % 8) which shares the query rows in its L2; then
 // the tiles on the diagonal, which are three quarters of one; then, where the caller wants them, the zeros above it.

@@ -353,6 +353,15 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
   }
 }
 
+// Every sample whose keys fit LDS has its score finished here.  That is a launch less, worth 1 to 4 us up to about 1000 rows;
+// beyond, one workgroup reading all heads' logits costs more than the launch saves, now that the selection on given scores
+// is short.  A prune of one prompt in a prefill, separate launches against this one, us:
+//   rows             331   512  1024  1350  1700  2048  3000  4096  8192  16384
+//    8 heads of 128 +3.9  +3.1  +1.6  +0.9  +0.2  -0.5  -3.2  -4.5   -13    -32
+//   28              +2.4  +2.7  +1.1  -1.6  -3.6  -4.8   -11   -15   -34    -86
+//   32              +3.1  +3.0  +0.7  -3.1  -3.5  -5.5   -11   -15   -39    -93
+//   64              +3.8  +3.8  -0.6  -5.3  -8.4   -13   -23   -36   -87   -260
+// The line is not drawn there: it is where the kernel's LDS ends.
 bool select_fuses_score(int max_seqlen, int n_heads) { return max_seqlen <= kSelLdsKeys && n_heads >= 1 && n_heads <= kSelMaxHeads; }
 
 fastav_status_t launch_select(const float* scores, const uint8_t* prot, const int32_t* cu, const int32_t* cu_out,
